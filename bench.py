@@ -112,13 +112,14 @@ def kernel_template(name: str, shapes, es: int, n) -> list:
     if name in ("ns_predict", "ns_pressure_rhs", "ns_correct"):
         return [f"k_{name}<{t}>"]
     if name == "ghost_dphi":
-        return [f"k_point_phit<{t}>", f"k_ghost_dg<{t}>", f"k_patch_dq<{t}>"]
+        # (from the second step of a call on, phi~ at the listed points is part of the face pass)
+        return [f"k_ghost_dg<{t}>", f"k_patch_dq<{t}>"]
     if name == "ghost_fill_C":
         return [f"k_fill_static<{t}>"]
     if name == "ghost_fill_u":
         return [f"k_vel_ghosts<{t}>", f"k_vel_faces<{t}>"]
     if name == "ghost_fills":
-        return [f"k_fill_static_vel<{t}>", f"k_vel_faces<{t}>"]
+        return [f"k_fill_static_vel<{t}>", f"k_vel_faces_dphi<{t}, true>"]
     return []
 
 

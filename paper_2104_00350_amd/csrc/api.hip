@@ -703,7 +703,7 @@ extern "C" int ch_ib_state_get(ch_ib_state *st, int field, void *dst, int dst_on
 
 // One step of the state's scheme; the explicit scheme's first step after (re)initialisation has no
 // previous rate.
-static hipError_t enqueue_one_step(ch_ib_state *st, chib::KernelTimer *tm) {
+static hipError_t enqueue_one_step(ch_ib_state *st, chib::KernelTimer *tm, chib::StepLink *link = nullptr) {
   chib::Plan &p = st->plan;
   hipError_t e = hipSuccess;
   chib::Plan q = p;   // the order-parameter part
@@ -723,11 +723,13 @@ static hipError_t enqueue_one_step(ch_ib_state *st, chib::KernelTimer *tm) {
                     : chib::enqueue_explicit_step<float>(q, st->cur, !st->r_valid, tm);
     if (e == hipSuccess) st->r_valid = 1;
   } else {
-    e = st->es == 8 ? chib::enqueue_step<double>(q, st->cur, tm) : chib::enqueue_step<float>(q, st->cur, tm);
+    e = st->es == 8 ? chib::enqueue_step<double>(q, st->cur, tm, link)
+                    : chib::enqueue_step<float>(q, st->cur, tm, link);
   }
   if (e != hipSuccess || !p.ns) return e;
-  e = st->es == 8 ? chib::enqueue_momentum<double>(p, 1 - st->cur, st->ns_first, tm)
-                  : chib::enqueue_momentum<float>(p, 1 - st->cur, st->ns_first, tm);
+  chib::StepLink *mlink = p.explicit_ab2 ? nullptr : link;
+  e = st->es == 8 ? chib::enqueue_momentum<double>(p, 1 - st->cur, st->ns_first, tm, mlink)
+                  : chib::enqueue_momentum<float>(p, 1 - st->cur, st->ns_first, tm, mlink);
   if (e != hipSuccess) return e;
   st->ns_first = 0;
   // p^(n+1) is in W: it becomes p^n, p^n becomes p^(n-1), and p^(n-1)'s buffer the workspace
@@ -744,8 +746,10 @@ extern "C" int ch_ib_step(ch_ib_state *st, int n_steps) {
   if (st->sticky) return fail(st->sticky, "state is in an error state");
   int rc = ensure_init(st);
   if (rc) return rc;
+  chib::StepLink link;
   for (int i = 0; i < n_steps; ++i) {
-    hipError_t e = enqueue_one_step(st, nullptr);
+    link.next = i + 1 < n_steps;
+    hipError_t e = enqueue_one_step(st, nullptr, &link);
     if (e != hipSuccess) return hip_fail(st, e, "step");
     st->cur = 1 - st->cur;
     st->step++;
@@ -770,9 +774,11 @@ extern "C" int ch_ib_step_timed(ch_ib_state *st, int n_steps, int max_kernels, d
       if (e == hipSuccess) ++created;   // only events that exist are destroyed below
     }
   // all steps are enqueued back to back; one wait at the end
+  chib::StepLink link;
   for (int s = 0; s < n_steps && e == hipSuccess; ++s) {
     tms[s].n = 0;
-    e = enqueue_one_step(st, &tms[s]);
+    link.next = s + 1 < n_steps;
+    e = enqueue_one_step(st, &tms[s], &link);
     if (e != hipSuccess) break;
     st->cur = 1 - st->cur;
     st->step++;
@@ -1296,8 +1302,10 @@ extern "C" int ch_ib_batch_step(ch_ib_batch *b, int n_steps) {
   for (ch_ib_state *s : b->seq) {
     const hipStream_t own = s->plan.stream;
     s->plan.stream = b->stream;
+    chib::StepLink link;
     for (int i = 0; i < n_steps && e == hipSuccess; ++i) {
-      e = enqueue_one_step(s, nullptr);
+      link.next = i + 1 < n_steps;
+      e = enqueue_one_step(s, nullptr, &link);
       if (e == hipSuccess) {
         s->cur = 1 - s->cur;
         s->step++;

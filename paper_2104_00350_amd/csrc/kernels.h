@@ -120,7 +120,18 @@ struct KernelTimer {
   hipError_t end(hipStream_t s) { return hipEventRecord(ev[n], s); }
 };
 
-template <typename T> hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm = nullptr);
+// Consecutive semi-implicit steps of one call: with `next` the step's last kernel also runs the first
+// kernel of the following step's ghost patch (dphi_done on return, taken over by that step).
+struct StepLink {
+  bool next = false;
+  bool dphi_done = false;
+};
+struct NextStep {   // the following step's C^n and C^(n-1)
+  const void *Cn = nullptr, *Cp = nullptr;
+};
+
+template <typename T>
+hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm = nullptr, StepLink *link = nullptr);
 template <typename T> hipError_t enqueue_initial_fill(const Plan &p, int cur);
 template <typename T> hipError_t tune_shapes(Plan &p, int cur, int reps);
 // One explicit Adams-Bashforth step (first: no previous rate, forward Euler) from C[cur] into C[1-cur].
@@ -138,18 +149,20 @@ template <typename T> hipError_t enqueue_diag(const Plan &p, int cur);
 // Pressure solve in place on W: W <- the zero-mean p with lap_h p = W (zero flux through the box walls).
 template <typename T> hipError_t enqueue_poisson(const Plan &p);
 // Velocity ghost fill (slip and no-penetration) on the faces p.F with the order parameter Cfin.
-template <typename T> hipError_t enqueue_velocity_fill(const Plan &p, const void *Cfin);
+template <typename T>
+hipError_t enqueue_velocity_fill(const Plan &p, const void *Cfin, const NextStep *next = nullptr);
 // Momentum step on the new order parameter C[cur] (prediction, penalisation, velocity fill,
 // pressure, correction); first: no previous convective term.  Leaves p^(n+1) in W.
-template <typename T> hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm = nullptr);
+template <typename T>
+hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm = nullptr, StepLink *link = nullptr);
 
 // One grouped step over a batch of 2D cases (see the batched kernels).
 struct BatchLaunch {
   const void *descs = nullptr;   // device array of per-case descriptors
-  static constexpr int kPhases = 7;
+  static constexpr int kPhases = 6;
   const int *off = nullptr;      // device [kPhases][n+1] per-phase tile offsets
   int n = 0;
-  unsigned total[kPhases] = {0, 0, 0, 0, 0, 0, 0};
+  unsigned total[kPhases] = {0, 0, 0, 0, 0, 0};
   size_t lds[4] = {0, 0, 0, 0};  // rhs, solve, out; y-marching rhs (0 unless every case allows it)
   int radix_rhs = 8, unroll = 2, radix_neu = 16, radix_out = 16;  // shared by all cases (unroll 3: y-march)
   hipStream_t stream = nullptr;

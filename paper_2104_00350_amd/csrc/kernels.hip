@@ -52,18 +52,68 @@ struct RhsCoef {
 // G becomes g_G + dg_G, dg_G = (phi~_M - phi~_G)/Cn^2 with phi~ = C~^3 - C~ - Cn^2 lap_h C~ the
 // explicit chemical potential of the step (k_ghost_dphi).  Through lap_h(g) that changes Q by
 // -2d dg_G/h^2 at the ghost and by +dg_G/h^2 at each face neighbour: a sparse patch over the
-// ghosts and their neighbours, listed sorted by cell with the first entry of every x-row, and its
-// value dq per entry (k_patch_dq).  The rhs kernels add it in LDS before their x transform.
-// dq == nullptr: no patch.
+// ghosts and their neighbours, listed sorted by cell with the first entry of every x-row.  The rhs
+// kernels add it in LDS before their x transform: the z-march reads its value dq per entry
+// (k_patch_dq), the line-tiled and y-marching kernels form it from dg themselves.
+// row == nullptr: no patch.
 template <typename T>
 struct RhsPatch {
   const int *row;    // [rows + 1]
   const int *cell;   // [np]
-  const T *dq;       // [np]
+  const int *ref;    // [2d+1][np]: own ghost index, then the ghosts at +e_a and -e_a per axis, or -1
+  const T *dg;       // [ghosts]
+  const T *dq;       // [np] (z-march only)
+  int np;
+  T inv_h2;
 };
 
-// Adds the patch entries [e0, e1) of the x-rows line0 .. line0 + L - 1 to a line tile in LDS
-// (row l at l * pitch, element i at i + i/16); one entry per thread, no two entries share a cell.
+// One entry's dq: the neighbouring ghosts' dg in a fixed order (+e_a, -e_a per axis), then the own one.
+template <typename T, int D>
+__device__ __forceinline__ T patch_dq(const int (&id)[2 * D + 1], const T *__restrict__ dg, T inv_h2) {
+  T acc = T(0);
+#pragma unroll
+  for (int j = 1; j < 2 * D + 1; ++j) {
+    const T v = dg[id[j] < 0 ? 0 : id[j]];
+    acc += id[j] < 0 ? T(0) : v;
+  }
+  const T own = dg[id[0] < 0 ? 0 : id[0]];
+  acc -= id[0] < 0 ? T(0) : T(2 * D) * own;
+  return acc * inv_h2;
+}
+
+// The patch entries of the x-rows line0 .. line0 + L - 1 of a line tile in LDS (row l at l * pitch,
+// element i at i + i/16); one entry per thread, no two entries share a cell.  The list range and the
+// thread's first entry are requested by the constructor, before the tile's stencil loads, so that only
+// the gather of dg is left when the tile is complete: forming dq here costs the small grids less than
+// the launch of k_patch_dq did (2D 128 x 64: 2.1 us of a 37 us step).
+template <typename T, int D>
+struct TilePatch {
+  int e0 = 0, e1 = 0, c = 0;
+  int id[2 * D + 1];
+  __device__ __forceinline__ void take(const RhsPatch<T> &rp, int e) {
+    c = rp.cell[e];
+#pragma unroll
+    for (int j = 0; j < 2 * D + 1; ++j) id[j] = rp.ref[(int64_t)j * rp.np + e];
+  }
+  __device__ __forceinline__ TilePatch(const RhsPatch<T> &rp, int64_t line0, int L) {
+    if (!rp.row) return;
+    e0 = rp.row[line0];
+    e1 = rp.row[line0 + L];
+    if (e0 + (int)threadIdx.x < e1) take(rp, e0 + (int)threadIdx.x);
+  }
+  // (the caller has written the tile and holds it behind a barrier)
+  __device__ __forceinline__ void add(T *__restrict__ s, const RhsPatch<T> &rp, int64_t line0, int lnx, int pitch) {
+    for (int e = e0 + (int)threadIdx.x; e < e1; e += blockDim.x) {
+      if (e >= e0 + (int)blockDim.x) take(rp, e);
+      const int l = (int)((c >> lnx) - line0);
+      const int i = c & ((1 << lnx) - 1);
+      const T dq = patch_dq<T, D>(id, rp.dg, rp.inv_h2);
+      s[l * pitch + i + (i >> 4)] += dq;
+    }
+  }
+};
+
+// The same from dq per entry (z-march).
 template <typename T>
 __device__ __forceinline__ void patch_tile(T *__restrict__ s, const RhsPatch<T> &rp, int64_t line0, int lnx,
                                            int pitch, int e0, int e1) {
@@ -74,7 +124,6 @@ __device__ __forceinline__ void patch_tile(T *__restrict__ s, const RhsPatch<T> 
     s[l * pitch + i + (i >> 4)] += rp.dq[e];
   }
 }
-
 
 // ---------------------------------------------------------------------------------------
 // Register DFTs of length R in {2, 4, 8, 16}, natural order in and out.  Forward uses
@@ -481,6 +530,7 @@ __device__ __forceinline__ void rhs_xdht_body(unsigned char *smem_raw, const T *
   const int line0 = tile * L;
   const int tot = L << dm.lnx;
   const int pitch = line_pitch(nx);
+  TilePatch<T, D> patch(rp, line0, L);
   // U cells per iteration so that their loads are in flight together
   for (int e0 = threadIdx.x; e0 < tot; e0 += U * blockDim.x) {
     T q[U];
@@ -512,9 +562,9 @@ __device__ __forceinline__ void rhs_xdht_body(unsigned char *smem_raw, const T *
       }
     }
   }
-  if (rp.dq) {   // the ghost patch of the tile's lines
+  if (patch.e1 > patch.e0) {   // the ghost patch of the tile's lines
     __syncthreads();
-    patch_tile(s, rp, line0, dm.lnx, pitch, rp.row[line0], rp.row[line0 + L]);
+    patch.add(s, rp, line0, dm.lnx, pitch);
   }
   __syncthreads();
   lds_fft<T, E, false, MAXR>(s, dm.lnx, logL - 1, 2 * pitch, 1, pitch, 1, false, twr, twi);
@@ -567,6 +617,7 @@ __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__
   T *xr = fb + L * pitch;                             // 2 rows x nx: C~ of the current row
   const int y0 = tile * L;
   const int tid = threadIdx.x;
+  TilePatch<T, 2> patch(rp, y0, L);
   const T s1 = T(1) + cf.S;
   const T klap = cf.inv_h2 * cf.inv_cn2;
   auto g = [&](T v) { return v * (v * v - s1); };
@@ -634,9 +685,9 @@ __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__
       }
     }
   }
-  if (rp.dq) {   // the ghost patch of the tile's rows
+  if (patch.e1 > patch.e0) {   // the ghost patch of the tile's rows
     __syncthreads();
-    patch_tile(fb, rp, y0, dm.lnx, pitch, rp.row[y0], rp.row[y0 + L]);
+    patch.add(fb, rp, y0, dm.lnx, pitch);
   }
   __syncthreads();
   lds_fft<T, tile_elems<T>(), false, R>(fb, dm.lnx, logL - 1, 2 * pitch, 1, pitch, 1, false, twr, twi);
@@ -783,7 +834,7 @@ __global__ __launch_bounds__(kThreads, (L == 2 && XM == 1 && R == 4) ? 3 : 1) vo
   // ghost patch (SPLIT: added by the caller afterwards): the entries of the tile's rows of a plane
   // are requested one plane ahead and added to its Q tile after the stencil
   constexpr int PF = 2;
-  const bool patch = !SPLIT && rp.dq != nullptr;
+  const bool patch = !SPLIT && rp.row != nullptr;
   int e_lo = 0, e_hi = 0, n_lo = 0, n_hi = 0, pc[PF], npc[PF];
   T pd[PF], npd[PF];
   auto range_of = [&](int z, int &lo, int &hi) {
@@ -1695,6 +1746,30 @@ __global__ __launch_bounds__(kThreads) void k_vel_faces(T *__restrict__ F0, T *_
   vel_faces_body<T>(F0, F1, F2, UG, G, f_cell, f_axis, f_gL, f_gR, stashL, stashR, NF, blockIdx.x);
 }
 
+// K7b together with the first kernel of the next step's ghost patch: the face means read the ghost
+// velocities and write faces, the patch reads the filled C, so blocks [0, nbf) take the faces and the
+// others phi~ at the listed points (POINTS) or dg.  One launch less per step: 256^3 FP64 6.4 + 9.0 us
+// apart, 10 us together; 2D steps are a chain of launches of 2-5 us each.
+template <typename T, bool POINTS>
+__global__ __launch_bounds__(kThreads) void k_vel_faces_dphi(
+    T *__restrict__ F0, T *__restrict__ F1, T *__restrict__ F2, const T *__restrict__ UG, int64_t G,
+    const int *__restrict__ f_cell, const int *__restrict__ f_axis, const int *__restrict__ f_gL,
+    const int *__restrict__ f_gR, const T *__restrict__ stashL, const T *__restrict__ stashR, int64_t NF, unsigned nbf,
+    const T *__restrict__ Cn, const T *__restrict__ Cp, const int *__restrict__ cell, T *__restrict__ out, int64_t nu,
+    const int *__restrict__ ap, const T *__restrict__ w, int K, Dims dm, int d, T cn2, T inv_h2, T inv_cn2) {
+  if (blockIdx.x < nbf) {
+    vel_faces_body<T>(F0, F1, F2, UG, G, f_cell, f_axis, f_gL, f_gR, stashL, stashR, NF, blockIdx.x);
+    return;
+  }
+  const int64_t b = blockIdx.x - nbf;
+  if constexpr (POINTS) {
+    const int64_t u = b * blockDim.x + threadIdx.x;
+    if (u < nu) out[u] = phit_at(Cn, Cp, (int64_t)cell[u], dm, d, cn2, inv_h2);
+  } else {
+    ghost_dphi_body<T>(Cn, Cp, cell, ap, w, out, G, K, dm, d, cn2, inv_h2, inv_cn2, b);
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // Chemical potential phi = C^3 - C - Cn^2 lap_h C on every cell, then the mirror value at
 // the ghosts (dphi/dn = 0).
@@ -2194,29 +2269,51 @@ inline RhsPatch<T> make_patch(const Plan &p) {
   if (p.G > 0 && p.NP > 0 && p.pl_dq) {
     rp.row = p.pl_row;
     rp.cell = p.pl_cell;
+    rp.ref = p.pl_ref;
+    rp.dg = (const T *)p.dg;
     rp.dq = (const T *)p.pl_dq;
+    rp.np = (int)p.NP;
+    rp.inv_h2 = (T)(1.0 / (p.h * p.h));
   }
   return rp;
 }
 
-// dg of every ghost from C^n, C^(n-1), then dq of every patched cell (before the rhs pass of a
-// semi-implicit step).
+// phi~ at the listed points first, one evaluation per point (3D, where many ghosts share averaging
+// points: 256^3 sphere 29.8 -> 23.5 us with the gather), or inside the gather (2D: one launch less)
+inline bool dphi_points(const Plan &p) { return p.d == 3 && p.NU && p.pt_phi; }
+
+inline bool has_patch(const Plan &p) { return p.G > 0 && p.NP > 0 && p.dg; }
+
+// The first kernel of the ghost patch: phi~ at the listed points, or dg itself.
 template <typename T>
-hipError_t launch_ghost_patch(const Plan &p, const T *Cn, const T *Cp) {
-  if (p.G == 0 || p.NP == 0 || !p.dg) return hipSuccess;
+hipError_t launch_dphi(const Plan &p, const T *Cn, const T *Cp) {
+  if (!has_patch(p)) return hipSuccess;
   const Dims dm = make_dims(p);
-  if (p.NU && p.pt_phi) {
+  if (dphi_points(p))
     hipLaunchKernelGGL((k_point_phit<T>), dim3(blocks_for(p.NU)), dim3(kThreads), 0, p.stream, Cn, Cp, p.pt_cell,
                        (T *)p.pt_phi, p.NU, dm, p.d, (T)(p.Cn * p.Cn), (T)(1.0 / (p.h * p.h)));
-    hipLaunchKernelGGL((k_ghost_dg<T>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream,
-                       (const T *)p.pt_phi, p.pt_idx, (const T *)p.wg, (T *)p.dg, p.G, p.K, (T)(1.0 / (p.Cn * p.Cn)));
-  } else {
+  else
     hipLaunchKernelGGL((k_ghost_dphi<T>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream, Cn, Cp, p.gidx,
                        p.apg, (const T *)p.wg, (T *)p.dg, p.G, p.K, dm, p.d, (T)(p.Cn * p.Cn), (T)(1.0 / (p.h * p.h)),
                        (T)(1.0 / (p.Cn * p.Cn)));
+  return hipGetLastError();
+}
+
+// dg of every ghost from C^n, C^(n-1) (before the rhs pass of a semi-implicit step); need_dq: then dq
+// of every patched cell; dphi_done: launch_dphi's kernel ran at the end of the step before.
+template <typename T>
+hipError_t launch_ghost_patch(const Plan &p, const T *Cn, const T *Cp, bool need_dq, bool dphi_done = false) {
+  if (!has_patch(p)) return hipSuccess;
+  if (!dphi_done) {
+    hipError_t e = launch_dphi<T>(p, Cn, Cp);
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_patch_dq<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, p.pl_ref,
-                     (const T *)p.dg, (T *)p.pl_dq, p.NP, 2 * p.d + 1, (T)(2 * p.d), (T)(1.0 / (p.h * p.h)));
+  if (dphi_points(p))
+    hipLaunchKernelGGL((k_ghost_dg<T>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream,
+                       (const T *)p.pt_phi, p.pt_idx, (const T *)p.wg, (T *)p.dg, p.G, p.K, (T)(1.0 / (p.Cn * p.Cn)));
+  if (need_dq)
+    hipLaunchKernelGGL((k_patch_dq<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, p.pl_ref,
+                       (const T *)p.dg, (T *)p.pl_dq, p.NP, 2 * p.d + 1, (T)(2 * p.d), (T)(1.0 / (p.h * p.h)));
   return hipGetLastError();
 }
 
@@ -2224,7 +2321,7 @@ hipError_t launch_ghost_patch(const Plan &p, const T *Cn, const T *Cp) {
 template <typename T>
 hipError_t launch_rhs_patch(const Plan &p, T *Q) {
   const RhsPatch<T> rp = make_patch<T>(p);
-  if (!rp.dq) return hipSuccess;
+  if (!rp.row) return hipSuccess;
   hipLaunchKernelGGL((k_rhs_patch<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, Q, rp.cell, rp.dq, p.NP);
   return hipGetLastError();
 }
@@ -2388,6 +2485,9 @@ void launch_zm_variant(const Plan &p, const T *Cn, const T *Cp, int zc_log) {
                      (const T *)p.twr[0], (const T *)p.twi[0], make_patch<T>(p));
 }
 
+// Whether pass 0 in this shape takes the z-march, whose patch comes as dq per entry.
+inline bool rhs_reads_dq(const Plan &p, const Plan::Shape &sh) { return p.d == 3 && sh.unroll >= 3 && zm_ok(p); }
+
 // Stencil-only z-march (the rhs Q into W, no transform) with L rows per tile.
 template <typename T, int XM>
 void launch_zm_split(const Plan &p, const T *Cn, const T *Cp, int logL, int zc_log) {
@@ -2420,7 +2520,7 @@ void launch_zm_xm(const Plan &p, const T *Cn, const T *Cp, int logL, int radix, 
 template <typename T, int D>
 hipError_t launch_rhs(const Plan &p, const T *Cn, const T *Cp, const Plan::Shape &sh, bool split_only = false) {
   constexpr int E = tile_elems<T>();
-  if (D == 3 && sh.unroll >= 3 && zm_ok(p)) {
+  if (D == 3 && rhs_reads_dq(p, sh)) {
     int logL = sh.log_tile < 1 ? 1 : (sh.log_tile > 3 ? 3 : sh.log_tile);
     if (p.n[0] == 512 && logL > 2) logL = 2;   // two 512-wide planes of C~ and x faces plus the tile stay in LDS
     while ((1 << logL) > p.n[1]) --logL;
@@ -2500,8 +2600,26 @@ hipError_t launch_ghost_fill(const Plan &p, T *Cout, int init) {
   return hipGetLastError();
 }
 
+// The face means of the velocity fill; next (the new C and the C before it) adds the first kernel of
+// the next step's ghost patch to the launch.
 template <typename T>
-hipError_t launch_velocity_faces(const Plan &p) {
+hipError_t launch_velocity_faces(const Plan &p, const NextStep *next) {
+  if (next && p.NF && has_patch(p)) {
+    const Dims dm = make_dims(p);
+    const unsigned nbf = blocks_for(p.NF);
+    const bool pts = dphi_points(p);
+#define CHIB_FACES_DPHI(P)                                                                                           \
+  hipLaunchKernelGGL((k_vel_faces_dphi<T, P>), dim3(nbf + blocks_for(P ? p.NU : p.G * 16)), dim3(kThreads), 0,       \
+                     p.stream, (T *)p.F[0], (T *)p.F[1], (T *)p.F[2], (const T *)p.UG, p.G, p.f_cell, p.f_axis,      \
+                     p.f_gL, p.f_gR, (const T *)p.stashL, (const T *)p.stashR, p.NF, nbf, (const T *)next->Cn,       \
+                     (const T *)next->Cp, P ? p.pt_cell : p.gidx, (T *)(P ? p.pt_phi : p.dg), p.NU, p.apg,           \
+                     (const T *)p.wg, p.K, dm, p.d, (T)(p.Cn * p.Cn), (T)(1.0 / (p.h * p.h)),                        \
+                     (T)(1.0 / (p.Cn * p.Cn)))
+    if (pts) CHIB_FACES_DPHI(true);
+    else CHIB_FACES_DPHI(false);
+#undef CHIB_FACES_DPHI
+    return hipGetLastError();
+  }
   if (p.NF)
     hipLaunchKernelGGL((k_vel_faces<T>), dim3(blocks_for(p.NF)), dim3(kThreads), 0, p.stream, (T *)p.F[0],
                        (T *)p.F[1], (T *)p.F[2], (const T *)p.UG, p.G, p.f_cell, p.f_axis, p.f_gL, p.f_gR,
@@ -2511,7 +2629,7 @@ hipError_t launch_velocity_faces(const Plan &p) {
 
 // Static condition with the velocity fill: C ghosts and ghost velocities in one launch, then the faces.
 template <typename T>
-hipError_t launch_static_fills(const Plan &p, T *Cout) {
+hipError_t launch_static_fills(const Plan &p, T *Cout, const NextStep *next) {
   const Dims dm = make_dims(p);
   const unsigned nbc = blocks_for(p.G * 16), nbg = blocks_for(p.G * 16);
   const T cb = (T)(p.cos_t / (1.4142135623730951 * p.Cn));
@@ -2522,11 +2640,11 @@ hipError_t launch_static_fills(const Plan &p, T *Cout) {
                      (T *)p.stashR, p.NF, dm, p.d, (T)(0.5 / p.h), (T)p.Cn, (T)p.cos_t, (T)(1.0 / p.Ca),
                      (T)(1.0 / p.mu), (T)p.ls, nbc, nbg);
   hipError_t e = hipGetLastError();
-  return e == hipSuccess ? launch_velocity_faces<T>(p) : e;
+  return e == hipSuccess ? launch_velocity_faces<T>(p, next) : e;
 }
 
 template <typename T>
-hipError_t launch_velocity_fill(const Plan &p, const T *Cfin) {
+hipError_t launch_velocity_fill(const Plan &p, const T *Cfin, const NextStep *next = nullptr) {
   if (!p.vel_fill || p.G == 0) return hipSuccess;
   const Dims dm = make_dims(p);
   const unsigned nbg = blocks_for(p.G * 16);
@@ -2536,11 +2654,8 @@ hipError_t launch_velocity_fill(const Plan &p, const T *Cfin) {
                      p.K, p.f_cell, p.f_axis, p.f_gL, p.f_gR, (T *)p.stashL, (T *)p.stashR, p.NF, dm, p.d,
                      (T)(0.5 / p.h), (T)p.Cn, (T)p.cos_t, (T)(1.0 / p.Ca), (T)(1.0 / p.mu), (T)p.ls,
                      p.dynamic ? 1 : 0, nbg);
-  if (p.NF)
-    hipLaunchKernelGGL((k_vel_faces<T>), dim3(blocks_for(p.NF)), dim3(kThreads), 0, p.stream, (T *)p.F[0],
-                       (T *)p.F[1], (T *)p.F[2], (const T *)p.UG, p.G, p.f_cell, p.f_axis, p.f_gL, p.f_gR,
-                       (const T *)p.stashL, (const T *)p.stashR, p.NF);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_velocity_faces<T>(p, next) : e;
 }
 
 }  // namespace
@@ -2548,25 +2663,25 @@ hipError_t launch_velocity_fill(const Plan &p, const T *Cfin) {
 // The fills that end a step, on the new field C: ghost values of C, then the velocity fill
 // (with the static condition both in one launch plus the face pass).
 template <typename T>
-hipError_t launch_step_fills(const Plan &p, T *C, KernelTimer *tm) {
+hipError_t launch_step_fills(const Plan &p, T *C, KernelTimer *tm, const NextStep *next) {
   hipError_t e = hipSuccess;
   auto mark = [&](const char *name) {
     if (tm && e == hipSuccess) e = tm->mark(name, p.stream);
   };
   if (!p.dynamic && p.vel_fill && p.G) {
     mark("ghost_fills");
-    if (e == hipSuccess) e = launch_static_fills<T>(p, C);
+    if (e == hipSuccess) e = launch_static_fills<T>(p, C, next);
   } else {
     mark("ghost_fill_C");
     if (e == hipSuccess) e = launch_ghost_fill<T>(p, C, 0);
     if (p.vel_fill && p.G) mark("ghost_fill_u");
-    if (e == hipSuccess) e = launch_velocity_fill<T>(p, C);
+    if (e == hipSuccess) e = launch_velocity_fill<T>(p, C, next);
   }
   return e;
 }
 
 template <typename T>
-hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm) {
+hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm, StepLink *link) {
   const T *Cn = (const T *)p.C[cur];
   T *Cp = (T *)p.C[1 - cur];
   hipError_t e = hipSuccess;
@@ -2576,7 +2691,7 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm) {
   const bool split = p.d == 3 && p.shape[0].unroll >= 6 && zm_ok(p);
   if (p.G) {
     mark("ghost_dphi");
-    if (e == hipSuccess) e = launch_ghost_patch<T>(p, Cn, Cp);
+    if (e == hipSuccess) e = launch_ghost_patch<T>(p, Cn, Cp, rhs_reads_dq(p, p.shape[0]), link && link->dphi_done);
   }
   mark(split ? "rhs_stencil" : "rhs_xdht");
   if (e == hipSuccess)
@@ -2588,7 +2703,11 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm) {
   if (e == hipSuccess) e = launch_spectral_tail<T>(p, tm);
   mark("xdht_out");
   if (e == hipSuccess) e = launch_xdht<T>(p, (const T *)p.W, Cp, p.shape[3]);
-  if (e == hipSuccess) e = launch_step_fills<T>(p, Cp, tm);
+  // another semi-implicit step follows: the first kernel of its ghost patch joins the face pass
+  const NextStep nx{Cp, Cn};
+  const bool join = link && link->next && p.vel_fill && p.NF && has_patch(p);
+  if (e == hipSuccess) e = launch_step_fills<T>(p, Cp, tm, join ? &nx : nullptr);
+  if (link) link->dphi_done = join && e == hipSuccess;
   if (tm && e == hipSuccess) e = tm->end(p.stream);
   return e;
 }
@@ -2645,7 +2764,7 @@ hipError_t tune_shapes(Plan &p, int cur, int reps) {
   };
   const T *Cn = (const T *)p.C[cur];
   const T *Cp = (const T *)p.C[1 - cur];
-  e = launch_ghost_patch<T>(p, Cn, Cp);   // the rhs candidates read the ghost patch
+  e = launch_ghost_patch<T>(p, Cn, Cp, true);   // the rhs candidates read the ghost patch
   auto rhs = [&]() { return p.d == 2 ? launch_rhs<T, 2>(p, Cn, Cp, p.shape[0]) : launch_rhs<T, 3>(p, Cn, Cp, p.shape[0]); };
   // pass 0: fused rhs
   if (e == hipSuccess) {
@@ -2761,7 +2880,7 @@ hipError_t enqueue_rhs(const Plan &p, int cur, void *out) {
   const Dims dm = make_dims(p);
   const RhsCoef<T> cf = make_coef<T>(p);
   const T *F2 = (const T *)(p.d == 3 ? adv_face(p, 2) : adv_face(p, 1));
-  hipError_t e = launch_ghost_patch<T>(p, (const T *)p.C[cur], (const T *)p.C[1 - cur]);
+  hipError_t e = launch_ghost_patch<T>(p, (const T *)p.C[cur], (const T *)p.C[1 - cur], true);
   if (e != hipSuccess) return e;
   if (p.d == 2)
     hipLaunchKernelGGL((k_rhs_only<T, 2>), dim3(blocks_for(p.N)), dim3(kThreads), 0, p.stream, (const T *)p.C[cur],
@@ -2792,8 +2911,8 @@ hipError_t enqueue_poisson(const Plan &p) {
 }
 
 template <typename T>
-hipError_t enqueue_velocity_fill(const Plan &p, const void *Cfin) {
-  return launch_velocity_fill<T>(p, (const T *)Cfin);
+hipError_t enqueue_velocity_fill(const Plan &p, const void *Cfin, const NextStep *next) {
+  return launch_velocity_fill<T>(p, (const T *)Cfin, next);
 }
 
 template <typename T>
@@ -2860,8 +2979,8 @@ template int max_log_tile<double>(const Plan &, int);
 template int max_log_tile<float>(const Plan &, int);
 template hipError_t tune_shapes<double>(Plan &, int, int);
 template hipError_t tune_shapes<float>(Plan &, int, int);
-template hipError_t enqueue_step<double>(const Plan &, int, KernelTimer *);
-template hipError_t enqueue_step<float>(const Plan &, int, KernelTimer *);
+template hipError_t enqueue_step<double>(const Plan &, int, KernelTimer *, StepLink *);
+template hipError_t enqueue_step<float>(const Plan &, int, KernelTimer *, StepLink *);
 template hipError_t enqueue_initial_fill<double>(const Plan &, int);
 template hipError_t enqueue_initial_fill<float>(const Plan &, int);
 template hipError_t enqueue_ghost_refresh<double>(const Plan &, int);
@@ -2872,8 +2991,8 @@ template hipError_t enqueue_solve<double>(const Plan &, const void *, void *);
 template hipError_t enqueue_solve<float>(const Plan &, const void *, void *);
 template hipError_t enqueue_poisson<double>(const Plan &);
 template hipError_t enqueue_poisson<float>(const Plan &);
-template hipError_t enqueue_velocity_fill<double>(const Plan &, const void *);
-template hipError_t enqueue_velocity_fill<float>(const Plan &, const void *);
+template hipError_t enqueue_velocity_fill<double>(const Plan &, const void *, const NextStep *);
+template hipError_t enqueue_velocity_fill<float>(const Plan &, const void *, const NextStep *);
 template <typename T>
 hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer *tm) {
   if (!p.R) return hipErrorInvalidValue;
@@ -2904,7 +3023,7 @@ hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer 
                          ipe, dt, first, p.N);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) e = launch_step_fills<T>(p, Cnext, tm);
+  if (e == hipSuccess) e = launch_step_fills<T>(p, Cnext, tm, nullptr);
   if (tm && e == hipSuccess) e = tm->end(p.stream);
   return e;
 }
@@ -2956,9 +3075,7 @@ struct CaseDesc {
   T *stashL, *stashR;
   unsigned nbg;
   RhsPatch<T> rp;          // dphi/dn = 0 at the ghosts: the rhs patch
-  T *dg, *pl_dq;           // [G], [NP]: written by kb_dphi, kb_dq
-  const int *pl_ref;       // [5][NP]
-  int64_t NP;
+  T *dg;                   // [G]: written by kb_dphi
   T cn2, inv_h2, inv_cn2;
 };
 
@@ -2984,7 +3101,7 @@ __global__ __launch_bounds__(kThreads) void kb_rhs(const CaseDesc<T> *__restrict
                                d.logL_rhs, d.twr0, d.twi0, (int)(blockIdx.x - off[c]), d.rp);
 }
 
-// dg of every ghost of every case, then dq of every patched cell, before the rhs pass.
+// dg of every ghost of every case, before the rhs pass.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void kb_dphi(const CaseDesc<T> *__restrict__ cs, const int *__restrict__ off,
                                                     int n, int parity) {
@@ -2992,23 +3109,6 @@ __global__ __launch_bounds__(kThreads) void kb_dphi(const CaseDesc<T> *__restric
   const CaseDesc<T> &d = cs[c];
   ghost_dphi_body<T>(d.C[parity], d.C[1 - parity], d.gidx, d.ap, d.w, d.dg, d.G, d.K, d.dm, 2, d.cn2, d.inv_h2,
                      d.inv_cn2, (int64_t)(blockIdx.x - off[c]));
-}
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void kb_dq(const CaseDesc<T> *__restrict__ cs, const int *__restrict__ off,
-                                                  int n) {
-  const int c = find_case(off, n, blockIdx.x);
-  const CaseDesc<T> &d = cs[c];
-  const int64_t e = (int64_t)(blockIdx.x - off[c]) * blockDim.x + threadIdx.x;
-  if (e >= d.NP) return;
-  T acc = T(0);
-  for (int j = 1; j < 5; ++j) {
-    const int id = d.pl_ref[(int64_t)j * d.NP + e];
-    if (id >= 0) acc += d.dg[id];
-  }
-  const int own = d.pl_ref[e];
-  if (own >= 0) acc -= T(4) * d.dg[own];
-  d.pl_dq[e] = acc * d.inv_h2;
 }
 
 template <typename T, int R>
@@ -3134,9 +3234,6 @@ void fill_case_desc(const Plan &p, int cur, void *desc_host) {
   d.nbg = blocks_for(p.G * 16);
   d.rp = make_patch<T>(p);
   d.dg = (T *)p.dg;
-  d.pl_dq = (T *)p.pl_dq;
-  d.pl_ref = p.pl_ref;
-  d.NP = p.NP;
   d.cn2 = (T)(p.Cn * p.Cn);
   d.inv_h2 = (T)(1.0 / (p.h * p.h));
   d.inv_cn2 = (T)(1.0 / (p.Cn * p.Cn));
@@ -3148,7 +3245,7 @@ size_t case_desc_bytes() {
   return sizeof(CaseDesc<T>);
 }
 
-// Per-phase tile counts of one case (0 rhs, 1 neumann, 2 out, 3 fill, 4 dphi, 5 velf, 6 dq) and the
+// Per-phase tile counts of one case (0 rhs, 1 neumann, 2 out, 3 fill, 4 dphi, 5 velf) and the
 // LDS bytes of its tiles (0 rhs, 1 neumann, 2 out).
 template <typename T>
 void case_tiles(const Plan &p, int *tiles, size_t *lds) {
@@ -3161,10 +3258,9 @@ void case_tiles(const Plan &p, int *tiles, size_t *lds) {
   tiles[2] = p.n[1] >> lo;
   const bool vf = p.vel_fill && p.G > 0;
   tiles[3] = (int)blocks_for(p.G * 16) + (vf ? (int)(blocks_for(p.G * 16) + blocks_for(p.NF)) : 0);
-  const bool pt = make_patch<T>(p).dq != nullptr;
+  const bool pt = make_patch<T>(p).row != nullptr;
   tiles[4] = pt ? (int)blocks_for(p.G * 16) : 0;   // (the ghost velocities run inside phase 3)
   tiles[5] = vf ? (int)blocks_for(p.NF) : 0;
-  tiles[6] = pt ? (int)blocks_for(p.NP) : 0;
   lds[0] = (size_t)(1 << lr) * line_pitch(p.n[0]) * sizeof(T);
   lds[1] = (size_t)col_tile(p.n[1], 1 << lb) * sizeof(T);
   lds[2] = (size_t)(1 << lo) * line_pitch(p.n[0]) * sizeof(T);
@@ -3179,10 +3275,9 @@ hipError_t enqueue_batch_step(const BatchLaunch &bl, int parity) {
   const int *off = bl.off;
   auto O = [&](int ph) { return off + ph * (n + 1); };
   const unsigned nb0 = bl.total[0], nb1 = bl.total[1], nb2 = bl.total[2];
-  const unsigned nb3 = bl.total[3], nb4 = bl.total[4], nb5 = bl.total[5], nb6 = bl.total[6];
+  const unsigned nb3 = bl.total[3], nb4 = bl.total[4], nb5 = bl.total[5];
   const bool r8 = bl.radix_rhs <= 8, u2 = bl.unroll >= 2;
   if (nb4) hipLaunchKernelGGL((kb_dphi<T>), dim3(nb4), dim3(kThreads), 0, bl.stream, cs, O(4), n, parity);
-  if (nb6) hipLaunchKernelGGL((kb_dq<T>), dim3(nb6), dim3(kThreads), 0, bl.stream, cs, O(6), n);
   if (bl.unroll == 3 && bl.lds[3]) {
     if (r8) hipLaunchKernelGGL((kb_rhs_ym<T, 8>), dim3(nb0), dim3(kThreads), bl.lds[3], bl.stream, cs, O(0), n, parity);
     else hipLaunchKernelGGL((kb_rhs_ym<T, 16>), dim3(nb0), dim3(kThreads), bl.lds[3], bl.stream, cs, O(0), n, parity);

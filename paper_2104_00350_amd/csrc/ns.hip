@@ -634,7 +634,7 @@ FaceSet<T> faces(void *const *f, int d) {
 }  // namespace
 
 template <typename T>
-hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm) {
+hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, StepLink *link) {
   hipError_t e = hipSuccess;
   auto mark = [&](const char *name) {
     if (tm && e == hipSuccess) e = tm->mark(name, p.stream);
@@ -671,7 +671,11 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm) 
     Plan q = p;
     for (int a = 0; a < 3; ++a) q.F[a] = p.Us[a];
     q.vel_fill = 1;
-    e = enqueue_velocity_fill<T>(q, C);
+    // (semi-implicit: the order parameter of the next step's patch is complete already)
+    const NextStep nx{p.C[cur], p.C[1 - cur]};
+    const bool join = link && link->next && p.NF && p.NP > 0 && p.dg;
+    e = enqueue_velocity_fill<T>(q, C, join ? &nx : nullptr);
+    if (link) link->dphi_done = join && e == hipSuccess;
   }
   mark("ns_pressure_rhs");
   if (e == hipSuccess) {
@@ -705,7 +709,7 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm) 
   return e;
 }
 
-template hipError_t enqueue_momentum<double>(const Plan &, int, int, KernelTimer *);
-template hipError_t enqueue_momentum<float>(const Plan &, int, int, KernelTimer *);
+template hipError_t enqueue_momentum<double>(const Plan &, int, int, KernelTimer *, StepLink *);
+template hipError_t enqueue_momentum<float>(const Plan &, int, int, KernelTimer *, StepLink *);
 
 }  // namespace chib

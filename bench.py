@@ -65,8 +65,10 @@ def algorithmic_bytes(name: str, cells: int, d: int, es: int, G: int, NF: int, d
         return cells * es * (d + 4)
     if name == "ns_poisson":                         # d + (d - 1) passes, one read and one write each
         return cells * es * 2 * (2 * d - 1)
-    if name == "ns_correct":                         # u^n, u** (d each), C, p^(n+1), p^n, p^(n-1) in; u^(n+1), 2u^(n+1) - u^n out
-        return cells * es * (4 * d + 4)
+    if name == "ns_div_poisson":                     # equal densities: u** (d) into the first pass, then as above
+        return cells * es * (2 * (2 * d - 1) + d - 1)
+    if name == "ns_correct":                         # matched fluids: u^n, u** (d each), p^(n+1) in;
+        return cells * es * (4 * d + 1)              # u^(n+1), 2u^(n+1) - u^n out
     return 0.0
 
 
@@ -109,8 +111,10 @@ def kernel_template(name: str, shapes, es: int, n) -> list:
         stride = nx * (n[1] if len(n) == 3 else 1)
         fixed = (8, lb) if (n[-1] == 256 and (256 << lb) == E and stride * 256 * es < 2 ** 32) else (0, 0)
         return [f"k_neumann_solve<{t}, {E}, {r if r == 8 else 16}, {fixed[0]}, {fixed[1]}>"]
-    if name in ("ns_predict", "ns_pressure_rhs", "ns_correct"):
-        return [f"k_{name}<{t}>"]
+    if name in ("ns_predict", "ns_correct"):         # (matched fluids)
+        return [f"k_{name}_zm<{t}, true>"]
+    if name == "ns_pressure_rhs":
+        return [f"k_ns_pressure_rhs_zm<{t}>"]
     if name == "ghost_dphi":
         # (from the second step of a call on, phi~ at the listed points is part of the face pass)
         return [f"k_ghost_dg<{t}>", f"k_patch_dq<{t}>"]

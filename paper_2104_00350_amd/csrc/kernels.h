@@ -146,8 +146,9 @@ template <typename T> hipError_t enqueue_phi(const Plan &p, int cur, void *out);
 template <typename T>
 hipError_t enqueue_scalar_fill(const Plan &p, void *f, double a, double b, double g, const void *g_ghost);
 template <typename T> hipError_t enqueue_diag(const Plan &p, int cur);
-// Pressure solve in place on W: W <- the zero-mean p with lap_h p = W (zero flux through the box walls).
-template <typename T> hipError_t enqueue_poisson(const Plan &p);
+// Pressure solve into W: the zero-mean p with lap_h p = W (zero flux through the box walls), or, given the d
+// face fields of a velocity, lap_h p = fac h div_h(velocity) with the divergence formed on the way in.
+template <typename T> hipError_t enqueue_poisson(const Plan &p, void *const *vel = nullptr, double fac = 0);
 // Velocity ghost fill (slip and no-penetration) on the faces p.F with the order parameter Cfin.
 template <typename T>
 hipError_t enqueue_velocity_fill(const Plan &p, const void *Cfin, const NextStep *next = nullptr);

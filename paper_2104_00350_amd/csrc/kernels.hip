@@ -254,17 +254,17 @@ __device__ __forceinline__ int lds_at(int b, int n, int ps, int ns, int padw) {
 // LDS slot dst(e): every thread issues kBatch independent loads before its LDS stores, so a tile
 // costs one memory round trip per batch rather than one per element.
 constexpr int kBatch = 8;
-template <typename T, typename Src, typename Dst>
+template <typename T, int NB = kBatch, typename Src, typename Dst>
 __device__ __forceinline__ void stage_tile(T *__restrict__ s, int tot, Src src, Dst dst) {
-  for (int e0 = threadIdx.x; e0 < tot; e0 += kBatch * blockDim.x) {
-    T v[kBatch];
+  for (int e0 = threadIdx.x; e0 < tot; e0 += NB * blockDim.x) {
+    T v[NB];
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
+    for (int k = 0; k < NB; ++k) {
       const int e = e0 + k * blockDim.x;
       v[k] = e < tot ? src(e) : T(0);
     }
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
+    for (int k = 0; k < NB; ++k) {
       const int e = e0 + k * blockDim.x;
       if (e < tot) s[dst(e)] = v[k];
     }
@@ -979,6 +979,27 @@ __global__ __launch_bounds__(kThreads, (L == 2 && XM == 1 && R == 4) ? 3 : 1) vo
   }
 }
 
+// Hartley transform of a tile of L = 2^logL lines of length 2^lnx in LDS (behind a barrier), stored to out.
+template <typename T, int E, int MAXR>
+__device__ __forceinline__ void xdht_tile(T *__restrict__ s, T *__restrict__ out, int line0, int lnx, int logL,
+                                          const T *__restrict__ twr, const T *__restrict__ twi) {
+  const int nx = 1 << lnx, pitch = line_pitch(nx);
+  lds_fft<T, E, false, MAXR>(s, lnx, logL - 1, 2 * pitch, 1, pitch, 1, false, twr, twi);
+  T *dst = out + (int64_t)line0 * nx;
+  const int half = 1 << (logL + lnx - 1);
+  for (int e = threadIdx.x; e < half; e += blockDim.x) {
+    const int b = e >> lnx;
+    const int kx = e & (nx - 1);
+    const int kk = (nx - kx) & (nx - 1);
+    const T *pb = s + b * 2 * pitch;
+    const int ak = kx + (kx >> 4), an = kk + (kk >> 4);
+    const T p = pb[ak], q = pb[pitch + ak], r = pb[an], sv = pb[pitch + an];
+    T *o = dst + (int64_t)(2 * b) * nx + kx;
+    o[0] = (p - q + r + sv) * T(0.5);
+    o[nx] = (p + q - r + sv) * T(0.5);
+  }
+}
+
 // K5 (and the forward x pass of the SOLVE stage): Hartley transform of L consecutive
 // contiguous lines of length nx from `in` to `out`.
 template <typename T, int E, int MAXR = 16, int CLN = 0, int CLB = 0>
@@ -1019,20 +1040,7 @@ __device__ __forceinline__ void xdht_body(unsigned char *smem_raw, const T *__re
     });
   }
   __syncthreads();
-  lds_fft<T, E, false, MAXR>(s, lnx, logL - 1, 2 * pitch, 1, pitch, 1, false, twr, twi);
-  T *dst = out + (int64_t)line0 * nx;
-  const int half = tot >> 1;
-  for (int e = threadIdx.x; e < half; e += blockDim.x) {
-    const int b = e >> lnx;
-    const int kx = e & (nx - 1);
-    const int kk = (nx - kx) & (nx - 1);
-    const T *pb = s + b * 2 * pitch;
-    const int ak = kx + (kx >> 4), an = kk + (kk >> 4);
-    const T p = pb[ak], q = pb[pitch + ak], r = pb[an], sv = pb[pitch + an];
-    T *o = dst + (int64_t)(2 * b) * nx + kx;
-    o[0] = (p - q + r + sv) * T(0.5);
-    o[nx] = (p + q - r + sv) * T(0.5);
-  }
+  xdht_tile<T, E, MAXR>(s, out, line0, lnx, logL, twr, twi);
 }
 
 template <typename T, int E, int MAXR = 16, int CLN = 0, int CLB = 0>
@@ -1040,6 +1048,84 @@ __global__ __launch_bounds__(kThreads) void k_xdht(const T *__restrict__ in, T *
                                                    int logL, const T *__restrict__ twr, const T *__restrict__ twi) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   xdht_body<T, E, MAXR, CLN, CLB>(smem_raw, in, out, lnx, logL, twr, twi, xcd_tile(blockIdx.x, gridDim.x));
+}
+
+// The forward x pass of the pressure solve on the divergence of a face field, fac (u_a[c] - u_a[c - e_a])
+// summed over the axes (no normal velocity on the box walls): the right-hand side of equal densities
+// never goes to memory (256^3 FP64: rhs pass 279 us and transform 43 us before, together 110).
+template <typename T, int D, int E, int MAXR, int CLN = 0, int CLB = 0>
+__global__ __launch_bounds__(kThreads) void k_div_xdht(const T *__restrict__ U0, const T *__restrict__ U1,
+                                                       const T *__restrict__ U2, T *__restrict__ out, Dims dm, T fac,
+                                                       int logL, const T *__restrict__ twr, const T *__restrict__ twi) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int lnx = CLN ? CLN : dm.lnx;
+  if constexpr (CLB != 0) logL = CLB;
+  T *s = reinterpret_cast<T *>(smem_raw);
+  const int nx = 1 << lnx, pitch = line_pitch(nx);
+  const int line0 = xcd_tile(blockIdx.x, gridDim.x) << logL;
+  if constexpr (D == 3 && CLN != 0 && CLB != 0) {
+    // fixed size: 16 bytes of every field per thread; the x neighbour of a thread's first value is the last
+    // one of the lane below (the first lane of a wave asks for it)
+    constexpr int CP = 16 / (int)sizeof(T);
+    typedef T FV __attribute__((ext_vector_type(CP)));
+    constexpr int RS = (CP * kThreads) >> CLN, KR = (1 << CLB) / RS, KB = KR < 4 ? KR : 4;
+    static_assert(RS >= 1 && KR % KB == 0, "fixed-size tile");
+    const int i = (threadIdx.x & ((1 << CLN) / CP - 1)) * CP, l0 = threadIdx.x / ((1 << CLN) / CP);
+    const int im = (i - 1) & ((1 << CLN) - 1);
+    const bool first = (threadIdx.x & 63) == 0;
+    auto ld = [](const T *p) { return *reinterpret_cast<const FV *>(p); };
+#pragma unroll
+    for (int k0 = 0; k0 < KR; k0 += KB) {
+      FV u0[KB], u1[KB], u1m[KB], u2[KB], u2m[KB];
+      T um[KB];
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        const int line = line0 + l0 + (k0 + k) * RS;
+        const int j = line & (dm.ny - 1), w = line >> dm.lny;
+        const int64_t row = (int64_t)line << CLN;
+        u0[k] = ld(U0 + row + i);
+        u1[k] = ld(U1 + row + i);
+        u1m[k] = ld(U1 + row + i + (((int64_t)((j - 1) & (dm.ny - 1)) - j) << CLN));
+        u2[k] = ld(U2 + row + i);
+        u2m[k] = ld(U2 + row + i - (w > 0 ? dm.plane : 0));
+        if (first) um[k] = U0[row + im];
+      }
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        const int l = l0 + (k0 + k) * RS, w = (line0 + l) >> dm.lny;
+        const T below = __shfl_up(u0[k][CP - 1], 1);
+        T left = first ? um[k] : below;
+        T *d = s + l * pitch + i + (i >> 4);
+#pragma unroll
+        for (int c = 0; c < CP; ++c) {
+          T acc = u0[k][c] - left;
+          left = u0[k][c];
+          acc += u1[k][c] - u1m[k][c];
+          acc += (w < dm.nz - 1 ? u2[k][c] : T(0)) - (w > 0 ? u2m[k][c] : T(0));
+          d[c] = fac * acc;
+        }
+      }
+    }
+  } else {
+    stage_tile<T, 4>(s, nx << logL, [&](int e) {
+      const int line = line0 + (e >> lnx), i = e & (nx - 1);
+      const int64_t row = (int64_t)line << lnx, c = row + i;
+      T acc = U0[c] - U0[row + ((i - 1) & (nx - 1))];
+      const int j = D == 2 ? line : line & (dm.ny - 1);
+      if constexpr (D == 3) acc += U1[c] - U1[c + (((int64_t)((j - 1) & (dm.ny - 1)) - j) << lnx)];
+      const int w = D == 2 ? line : line >> dm.lny, nw = D == 2 ? dm.ny : dm.nz;   // bounded axis
+      const int64_t step = D == 2 ? (int64_t)nx : dm.plane;
+      const T *Uw = D == 2 ? U1 : U2;
+      const T hi = Uw[c], lo = Uw[w > 0 ? c - step : c];
+      acc += (w < nw - 1 ? hi : T(0)) - (w > 0 ? lo : T(0));
+      return fac * acc;
+    }, [&](int e) {
+      const int l = e >> lnx, i = e & (nx - 1);
+      return l * pitch + i + (i >> 4);
+    });
+  }
+  __syncthreads();
+  xdht_tile<T, E, MAXR>(s, out, line0, lnx, logL, twr, twi);
 }
 
 template <typename T> struct Vec2;
@@ -1796,13 +1882,22 @@ __global__ __launch_bounds__(kThreads) void k_phi(const T *__restrict__ C, T *__
   phi[c] = c0 * c0 * c0 - c0 - cn2 * lap;
 }
 
+// Mirror value at the ghosts, sixteen lanes per ghost as in the other ghost kernels (one thread per ghost
+// walked its 2K gathers one after another: 14.6 -> 7 us at the 256^3 sphere's 42 k ghosts).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_phi_ghost(T *__restrict__ phi, const int *__restrict__ gidx,
                                                         const int *__restrict__ ap, const T *__restrict__ w,
                                                         int64_t G, int K) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= G) return;
-  phi[gidx[g]] = mirror_gather(phi, ap, w, g, G, K);
+  const int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+  const int sl = threadIdx.x & 15;
+  const int cg = gidx[g < G ? g : G - 1];
+  T v = T(0);
+  if (g < G && sl < 2 * K) {
+    const int64_t i = g * kGhostSlots + sl;
+    v = (sl < K ? T(2) : T(-1)) * w[i] * phi[ap[i]];
+  }
+  const T m = group16_sum(v);
+  if (g < G && sl == 0) phi[cg] = m;
 }
 
 // Ghost fill of any scalar under the mixed condition a f + b df/dn = g at the wall: the ghost-cell
@@ -2018,7 +2113,12 @@ __global__ __launch_bounds__(kThreads) void k_explicit_zm(const T *__restrict__ 
 inline bool stencil_zm_ok(const Plan &p) {
   return p.d == 3 && p.n[0] % kZmTx == 0 && p.n[1] % kZmTy == 0 && p.n[2] >= 16;   // chunks of 16 planes
 }
-inline int stencil_zm_log(const Plan &p) { return p.logn[2] < 4 ? p.logn[2] : 4; }   // >= log2(kZmU) below
+// planes per workgroup: 16, or 8 or 4 (kZmU) on grids that would have fewer than 1024 workgroups
+inline int stencil_zm_log(const Plan &p) {
+  int l = 4;
+  while (l > 2 && (p.N >> (8 + l)) < 1024) --l;
+  return l;
+}
 inline unsigned stencil_zm_blocks(const Plan &p) {
   return (unsigned)((p.n[0] / kZmTx) * (p.n[1] / kZmTy) * (p.n[2] >> stencil_zm_log(p)));
 }
@@ -2376,6 +2476,36 @@ hipError_t launch_xdht(const Plan &p, const T *in, T *out, const Plan::Shape &sh
     CHIB_XDHT(T, E, 16);
   }
 #undef CHIB_XDHT
+  return hipGetLastError();
+}
+
+template <typename T, int D>
+hipError_t launch_div_xdht(const Plan &p, void *const *vel, double fac, const Plan::Shape &sh) {
+  constexpr int E = tile_elems<T>();
+  const int logL = clamp_log(sh.log_tile, max_log_lines(p, E));
+  const int lines = p.d == 3 ? p.n[1] * p.n[2] : p.n[1];
+  const unsigned nb = (unsigned)(lines >> logL);
+  const size_t lds = (size_t)(1 << logL) * line_pitch(p.n[0]) * sizeof(T);
+#define CHIB_DIV(...)                                                                                             \
+  hipLaunchKernelGGL((k_div_xdht<T, D, E, __VA_ARGS__>), dim3(nb), dim3(kThreads), lds, p.stream,                 \
+                     (const T *)vel[0], (const T *)vel[1], (const T *)vel[D - 1], (T *)p.W, make_dims(p), (T)fac, \
+                     logL, (const T *)p.twr[0], (const T *)p.twi[0])
+  const bool r8 = sh.radix == 8;
+  if constexpr (D == 3) {
+    if (p.logn[0] == 8 && (logL == 3 || logL == 4)) {
+      if (logL == 3 && r8) CHIB_DIV(8, 8, 3);
+      else if (logL == 3) CHIB_DIV(16, 8, 3);
+      else if (r8) CHIB_DIV(8, 8, 4);
+      else CHIB_DIV(16, 8, 4);
+      return hipGetLastError();
+    }
+  }
+  if (r8) {
+    CHIB_DIV(8);
+  } else {
+    CHIB_DIV(16);
+  }
+#undef CHIB_DIV
   return hipGetLastError();
 }
 
@@ -2901,10 +3031,12 @@ hipError_t enqueue_solve(const Plan &p, const void *in, void *out) {
 }
 
 template <typename T>
-hipError_t enqueue_poisson(const Plan &p) {
+hipError_t enqueue_poisson(const Plan &p, void *const *vel, double fac) {
   Plan q = p;
   q.poisson = 1;
-  hipError_t e = launch_xdht<T>(q, (const T *)q.W, (T *)q.W, q.shape[3]);
+  hipError_t e = !vel ? launch_xdht<T>(q, (const T *)q.W, (T *)q.W, q.shape[3])
+                 : q.d == 2 ? launch_div_xdht<T, 2>(q, vel, fac, q.shape[3])
+                            : launch_div_xdht<T, 3>(q, vel, fac, q.shape[3]);
   if (e != hipSuccess) return e;
   if ((e = launch_spectral_tail<T>(q)) != hipSuccess) return e;
   return launch_xdht<T>(q, (const T *)q.W, (T *)q.W, q.shape[3]);
@@ -2929,8 +3061,8 @@ hipError_t enqueue_phi(const Plan &p, int cur, void *out) {
     hipLaunchKernelGGL((k_phi<T, 3>), dim3(blocks_for(p.N)), dim3(kThreads), 0, p.stream, (const T *)p.C[cur],
                        (T *)out, dm, cn2, ih2, p.N);
   if (p.G)
-    hipLaunchKernelGGL((k_phi_ghost<T>), dim3(blocks_for(p.G)), dim3(kThreads), 0, p.stream, (T *)out, p.gidx, p.ap,
-                       (const T *)p.w, p.G, p.K);
+    hipLaunchKernelGGL((k_phi_ghost<T>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream, (T *)out, p.gidx,
+                       p.apg, (const T *)p.wg, p.G, p.K);
   return hipGetLastError();
 }
 
@@ -2989,8 +3121,8 @@ template hipError_t enqueue_rhs<double>(const Plan &, int, void *);
 template hipError_t enqueue_rhs<float>(const Plan &, int, void *);
 template hipError_t enqueue_solve<double>(const Plan &, const void *, void *);
 template hipError_t enqueue_solve<float>(const Plan &, const void *, void *);
-template hipError_t enqueue_poisson<double>(const Plan &);
-template hipError_t enqueue_poisson<float>(const Plan &);
+template hipError_t enqueue_poisson<double>(const Plan &, void *const *, double);
+template hipError_t enqueue_poisson<float>(const Plan &, void *const *, double);
 template hipError_t enqueue_velocity_fill<double>(const Plan &, const void *, const NextStep *);
 template hipError_t enqueue_velocity_fill<float>(const Plan &, const void *, const NextStep *);
 template <typename T>

@@ -217,161 +217,211 @@ __global__ __launch_bounds__(kNsThreads) void k_ns_predict(FaceSet<T> U, const T
   for_each_cell(wk, g, [&](int64_t c) { ns_predict_cell<T, D>(U, C, phi, Nh, Af, Us, g, k, first, c); });
 }
 
-// 3D prediction with each edge formed once.  The convective flux E_ab = (u_a mean along b)(u_b mean
-// along a) and the shear stress tau_ab = mu_e (du_a/dx_b + du_b/dx_a) of an edge are symmetric in a and
-// b and are used by four faces; the per-cell kernel forms them four times.  Here a workgroup owns a
-// 64 x 8 tile of columns and marches it through zc planes: per plane it forms the xy, xz and yz edges
-// of the tile and of the halo column and row below it into LDS, every face takes its two edge
-// differences from there, and the xz and yz edges of the plane below come from registers.  Same
-// formulas and wall rules as ns_predict_cell (the four-cell mean viscosity of an edge is summed in the
-// order of its lower-axis face, so the other face's value may differ in the last bit).
-constexpr int kEx = 64, kEy = 8, kEhx = kEx + 1, kEhy = kEy + 1;
-constexpr int kEThreads = kEx * kEy;   // one thread per column of the tile
-
-// E and tau of the xy (0), xz (1) and yz (2) edges at cell (qx, qy, qz): edge o lies at the cell
-// centre plus half a cell along each of its two axes.
-template <typename T>
-__device__ __forceinline__ void ns_edges(const FaceSet<T> &U, const T *__restrict__ C, const NsGrid &g,
-                                         const NsCoef<T> &k, int qx, int qy, int qz, T *E, T *Tau) {
-  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-  const int cq = qx + (qy << g.ln[0]) + (qz << (g.ln[0] + g.ln[1]));
-  const int ox = ((qx + 1) & (nx - 1)) - qx;
-  const int oy = (((qy + 1) & (ny - 1)) - qy) << g.ln[0];
-  const bool top = qz == nz - 1;
-  const int oz = top ? 0 : (1 << (g.ln[0] + g.ln[1]));   // (unused at the top, kept in the box)
-  const T ux0 = U.f[0][cq], uy0 = U.f[1][cq];
-  const T uzr = U.f[2][cq];
-  const T uz0 = top ? T(0) : uzr;
-  const T ux_y = U.f[0][cq + oy], uy_x = U.f[1][cq + ox];
-  const T ux_z = U.f[0][cq + oz], uy_z = U.f[1][cq + oz];
-  const T uzx = U.f[2][cq + ox], uzy = U.f[2][cq + oy];
-  const T uz_x = top ? T(0) : uzx, uz_y = top ? T(0) : uzy;
-  const T mu_c = mu_of(k, C[cq]), mu_x = mu_of(k, C[cq + ox]), mu_y = mu_of(k, C[cq + oy]);
-  const T mu_xy = mu_of(k, C[cq + ox + oy]);
-  const T mu_z = mu_of(k, C[cq + oz]), mu_xz = mu_of(k, C[cq + ox + oz]), mu_yz = mu_of(k, C[cq + oy + oz]);
-  // xy
-  E[0] = T(0.5) * (ux0 + ux_y) * T(0.5) * (uy0 + uy_x);
-  Tau[0] = T(0.25) * (mu_c + mu_x + mu_y + mu_xy) * ((ux_y - ux0) * k.inv_h + (uy_x - uy0) * k.inv_h);
-  // xz and yz: on the top wall E = 0, the tangential velocity has the image -u, u_z = 0 along the wall
-  const T e1 = T(0.5) * (ux0 + ux_z) * T(0.5) * (uz0 + uz_x);
-  const T e2 = T(0.5) * (uy0 + uy_z) * T(0.5) * (uz0 + uz_y);
-  E[1] = top ? T(0) : e1;
-  E[2] = top ? T(0) : e2;
-  const T ux_up = top ? -ux0 : ux_z, uy_up = top ? -uy0 : uy_z;
-  Tau[1] = T(0.25) * (mu_c + mu_x + mu_z + mu_xz) * ((ux_up - ux0) * k.inv_h + (uz_x - uz0) * k.inv_h);
-  Tau[2] = T(0.25) * (mu_c + mu_y + mu_z + mu_yz) * ((uy_up - uy0) * k.inv_h + (uz_y - uz0) * k.inv_h);
-}
+// 3D prediction marching in z over a 64 x 8 tile of columns, every field read once.  The kernel is bound
+// by memory (136 bytes per cell at 256^3 FP64), so what counts is that no line is fetched twice: u, C
+// and phi of a plane, with a one-cell x/y halo, go to LDS when the plane is first read and every stencil
+// value comes from there (neighbours taken through the caches instead re-fetched u and C two to three
+// times: 170 bytes read per cell of 88, as other tiles' planes evict a plane before its neighbours ask
+// for it).  Three LDS slots hold planes z-1 .. z+1 in turn, so one barrier per plane suffices; plane z+2
+// and the own-cell fields of plane z+1 are requested while plane z is computed.
+// Each thread forms the xy, xz and yz edges around its three faces: the convective flux
+// E_ab = (u_a mean along b)(u_b mean along a) and the shear stress tau_ab = mu_e (du_a/dx_b + du_b/dx_a)
+// of an edge are symmetric in a and b; those of the z edges below come from the plane before.  Powers of
+// two and of 1/h are taken out of the sums, mu and rho are linear in C, so an edge viscosity or a face
+// density is one fused multiply-add on the sum of its cells' C.  Same formulas and wall rules as
+// ns_predict_cell: the planes beyond the box walls hold the images (-u_x, -u_y, u_z = 0, C reflected),
+// with which the wall edges take their values without a case of their own.
+constexpr int kEx = 64, kEy = 8, kEhx = kEx + 2, kEhy = kEy + 2;
+constexpr int kEThreads = kEx * kEy;                        // one thread per column of the tile
+constexpr int kEHalo = kEhx * kEhy - kEThreads;              // halo cells of a plane
+constexpr int kEFields = 5;                                  // u_x, u_y, u_z, C, phi
+template <typename T> constexpr size_t predict_lds() { return (size_t)3 * kEFields * kEhx * kEhy * sizeof(T); }
 
 template <typename T>
-__global__ __launch_bounds__(kEThreads) void k_ns_predict_edges(FaceSet<T> U, const T *__restrict__ C,
+struct PredictCoef {
+  T mu0, mu1;          // mu = mu0 + mu1 C
+  T rf0, rf1;          // rho_f = rf0 + rf1 (C + C')
+  T n_fac;             // 1/(4h)
+  T v_fac;             // 1/(Re h^2)
+  T f_fac;             // kappa/(2h)
+};
+
+// EQ: equal densities, rho_f the constant rf0 (its reciprocal in inv_rf).
+template <typename T, bool EQ>
+__global__ __launch_bounds__(kEThreads, 4) void k_ns_predict_zm(FaceSet<T> U, const T *__restrict__ C,
                                                                 const T *__restrict__ phi, FaceSet<T> Nh,
                                                                 FaceSet<T> Af, FaceSet<T> Us, NsGrid g,
-                                                                NsCoef<T> k, int first, int zc) {
-  __shared__ T sE[3][kEhy][kEhx];
-  __shared__ T sT[3][kEhy][kEhx];
+                                                                NsCoef<T> k, PredictCoef<T> q, T inv_rf, int first,
+                                                                int zc) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int PL = kEhx * kEhy;                            // one field of one slot
+  T *const s = reinterpret_cast<T *>(smem_raw);              // [slot][field][row][column]
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const int tiles_x = nx / kEx, tiles_y = ny / kEy;
-  int bidx = (int)blockIdx.x;
-  const int bx = bidx % tiles_x;
-  bidx /= tiles_x;
-  const int by = bidx % tiles_y;
-  const int bz = bidx / tiles_y;
+  int b = (int)blockIdx.x;
+  const int bx = b % tiles_x;
+  b /= tiles_x;
+  const int by = b % tiles_y;
+  const int bz = b / tiles_y;
   const int x0 = bx * kEx, y0 = by * kEy, z0 = bz * zc;
   const int tid = (int)threadIdx.x;
   const int tx = tid & (kEx - 1), ty = tid >> 6;
-  const int x = x0 + tx, y = y0 + ty;
-  const int X = tx + 1, Y = ty + 1;
-  const int plane_sh = g.ln[0] + g.ln[1];
-  const int oxp = ((x + 1) & (nx - 1)) - x, oxm = ((x - 1) & (nx - 1)) - x;
-  const int oyp = (((y + 1) & (ny - 1)) - y) << g.ln[0], oym = (((y - 1) & (ny - 1)) - y) << g.ln[0];
-  // xz and yz edges of the plane below this thread's cell
-  T Ezx, Tzx, Ezy, Tzy;
-  if (z0 == 0) {   // the bottom wall: no flux, shear from the no-slip image
-    const int c = x + (y << g.ln[0]);
-    const T mu_c = mu_of(k, C[c]);
-    const T ux = U.f[0][c], uy = U.f[1][c];
-    Ezx = T(0);
-    Ezy = T(0);
-    Tzx = T(0.5) * (mu_c + mu_of(k, C[c + oxp])) * (ux - (-ux)) * k.inv_h;
-    Tzy = T(0.5) * (mu_c + mu_of(k, C[c + oyp])) * (uy - (-uy)) * k.inv_h;
-  } else {
-    T E[3], Tau[3];
-    ns_edges(U, C, g, k, x, y, z0 - 1, E, Tau);
-    Ezx = E[1];
-    Tzx = Tau[1];
-    Ezy = E[2];
-    Tzy = Tau[2];
-  }
-  for (int kz = z0; kz < z0 + zc; ++kz) {
-    for (int e = tid; e < kEhx * kEhy; e += kEThreads) {
-      const int yy = e / kEhx, xx = e - yy * kEhx;
-      T E[3], Tau[3];
-      ns_edges(U, C, g, k, (x0 - 1 + xx) & (nx - 1), (y0 - 1 + yy) & (ny - 1), kz, E, Tau);
-#pragma unroll
-      for (int o = 0; o < 3; ++o) {
-        sE[o][yy][xx] = E[o];
-        sT[o][yy][xx] = Tau[o];
-      }
+  const int psh = g.ln[0] + g.ln[1];
+  const int col = (x0 + tx) + ((y0 + ty) << g.ln[0]);        // own column within a plane
+  const int own = (ty + 1) * kEhx + tx + 1;                  // own slot within a field
+  // the halo cell this thread also brings (threads below kEHalo): two rows, then two columns
+  int hcol = col, hslot = own;
+  const bool halo = tid < kEHalo;
+  if (halo) {
+    int hr, hc;
+    if (tid < 2 * kEhx) {
+      hr = tid < kEhx ? 0 : kEhy - 1;
+      hc = tid < kEhx ? tid : tid - kEhx;
+    } else {
+      const int e = tid - 2 * kEhx;
+      hr = 1 + (e >> 1);
+      hc = (e & 1) ? kEhx - 1 : 0;
     }
-    __syncthreads();
-    const int c = x + (y << g.ln[0]) + (kz << plane_sh);
-    const int ozp = kz < nz - 1 ? (1 << plane_sh) : 0, ozm = kz > 0 ? -(1 << plane_sh) : 0;
-    const int op[3] = {oxp, oyp, ozp}, om[3] = {oxm, oym, ozm};
-    const T C0 = C[c];
-    const T mu_c = mu_of(k, C0);
-    const T phc = phi[c];
-    const T rc = rho_of(k, C0);
+    hslot = hr * kEhx + hc;
+    hcol = ((x0 - 1 + hc) & (nx - 1)) + (((y0 - 1 + hr) & (ny - 1)) << g.ln[0]);
+  }
+  T v[kEFields], hv[kEFields];                               // the plane in flight: own cell, halo cell
+  auto request = [&](int z) {
+    const int64_t zb = (int64_t)(z < 0 ? 0 : (z >= nz ? nz - 1 : z)) << psh;
+    v[0] = U.f[0][zb + col];
+    v[1] = U.f[1][zb + col];
+    v[2] = U.f[2][zb + col];
+    v[3] = C[zb + col];
+    v[4] = phi[zb + col];
+    if (halo) {
+      hv[0] = U.f[0][zb + hcol];
+      hv[1] = U.f[1][zb + hcol];
+      hv[2] = U.f[2][zb + hcol];
+      hv[3] = C[zb + hcol];
+      hv[4] = phi[zb + hcol];
+    }
+  };
+  // the plane in flight into its slot; beyond the walls u_x and u_y change sign, and u_z vanishes there and
+  // on the top wall face
+  auto store = [&](int z, int slot) {
+    const T sg = (z < 0 || z >= nz) ? T(-1) : T(1);
+    const bool wz = z < 0 || z >= nz - 1;
+    T *p = s + slot * kEFields * PL;
+    p[own] = sg * v[0];
+    p[PL + own] = sg * v[1];
+    p[2 * PL + own] = wz ? T(0) : v[2];
+    p[3 * PL + own] = v[3];
+    p[4 * PL + own] = v[4];
+    if (halo) {
+      p[hslot] = sg * hv[0];
+      p[PL + hslot] = sg * hv[1];
+      p[2 * PL + hslot] = wz ? T(0) : hv[2];
+      p[3 * PL + hslot] = hv[3];
+      p[4 * PL + hslot] = hv[4];
+    }
+  };
+  // 4 E and h tau of the edge between axis a and b with lower cell at slot index i, its neighbour along a at
+  // i + oa and along b at j (the same field plane or the one above)
+  auto edge_xy = [&](const T *p, int i, T &E, T &t) {
+    const T ua = p[i], ub = p[PL + i], uab = p[i + kEhx], uba = p[PL + i + 1];
+    const T *c = p + 3 * PL;
+    E = (ua + uab) * (ub + uba);
+    t = (q.mu0 + q.mu1 * (c[i] + c[i + 1] + c[i + kEhx] + c[i + kEhx + 1])) * ((uab - ua) + (uba - ub));
+  };
+  // edge between axis a (field a, in-plane step oa) and z: planes lo and hi
+  auto edge_z = [&](const T *lo, const T *hi, int a, int oa, int i, T &E, T &t) {
+    const T ua = lo[a * PL + i], uaz = hi[a * PL + i], uz = lo[2 * PL + i], uza = lo[2 * PL + i + oa];
+    const T *c0 = lo + 3 * PL, *c1 = hi + 3 * PL;
+    E = (ua + uaz) * (uz + uza);
+    t = (q.mu0 + q.mu1 * (c0[i] + c0[i + oa] + c1[i] + c1[i + oa])) * ((uaz - ua) + (uza - uz));
+  };
+  request(z0 - 1);
+  store(z0 - 1, 0);
+  request(z0);
+  store(z0, 1);
+  request(z0 + 1);
+  T nh[3], af[3];
+  auto request_own = [&](int z) {
+    const int64_t c = ((int64_t)z << psh) + col;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      if (a == 2 && kz == nz - 1) {   // top wall face
-        Us.f[a][c] = T(0);
-        Nh.f[a][c] = T(0);
-        continue;
-      }
-      const T *ua = U.f[a];
-      const T u0 = ua[c];
-      const T umr = ua[c + om[a]], upr = ua[c + op[a]];
-      // the face below the bottom wall and the top wall face are zero
-      const T um = (a == 2 && kz == 0) ? T(0) : umr;
-      const T up = (a == 2 && kz + 1 == nz - 1) ? T(0) : upr;
-      T N = T(0), V;
-      const T uc0 = T(0.5) * (um + u0), uc1 = T(0.5) * (u0 + up);
-      const T Ca = C[c + op[a]];
-      const T mu_a = mu_of(k, Ca);
-      const T tn0 = T(2) * mu_c * (u0 - um) * k.inv_h;
-      const T tn1 = T(2) * mu_a * (up - u0) * k.inv_h;
-      V = (tn1 - tn0) * k.inv_h;
-      if (a == 0) {
-        N += (uc1 * uc1 - uc0 * uc0) * k.inv_h;
-        N += (sE[0][Y][X] - sE[0][Y - 1][X]) * k.inv_h;
-        N += (sE[1][Y][X] - Ezx) * k.inv_h;
-        V += (sT[0][Y][X] - sT[0][Y - 1][X]) * k.inv_h;
-        V += (sT[1][Y][X] - Tzx) * k.inv_h;
-      } else if (a == 1) {
-        N += (sE[0][Y][X] - sE[0][Y][X - 1]) * k.inv_h;
-        N += (uc1 * uc1 - uc0 * uc0) * k.inv_h;
-        N += (sE[2][Y][X] - Ezy) * k.inv_h;
-        V += (sT[0][Y][X] - sT[0][Y][X - 1]) * k.inv_h;
-        V += (sT[2][Y][X] - Tzy) * k.inv_h;
-      } else {
-        N += (sE[1][Y][X] - sE[1][Y][X - 1]) * k.inv_h;
-        N += (sE[2][Y][X] - sE[2][Y - 1][X]) * k.inv_h;
-        N += (uc1 * uc1 - uc0 * uc0) * k.inv_h;
-        V += (sT[1][Y][X] - sT[1][Y][X - 1]) * k.inv_h;
-        V += (sT[2][Y][X] - sT[2][Y - 1][X]) * k.inv_h;
-      }
-      const T F = k.kappa * (T(0.5) * (phc + phi[c + op[a]])) * (Ca - C0) * k.inv_h;
-      const T rf = T(0.5) * (rc + rho_of(k, Ca));
-      const T Np = first ? N : Nh.f[a][c];
-      const T us = u0 + k.dt * (-(T(1.5) * N - T(0.5) * Np) + (V * k.inv_re + F) / rf + k.g[a]);
-      Us.f[a][c] = Af.f[a][c] * us;
-      Nh.f[a][c] = N;
+      nh[a] = __builtin_nontemporal_load(Nh.f[a] + c);
+      af[a] = __builtin_nontemporal_load(Af.f[a] + c);
     }
-    Ezx = sE[1][Y][X];
-    Tzx = sT[1][Y][X];
-    Ezy = sE[2][Y][X];
-    Tzy = sT[2][Y][X];
-    __syncthreads();   // the next plane's edges overwrite the buffers
+  };
+  __syncthreads();
+  T Exm, txm, Eym, tym;                                      // xz and yz edges below the plane
+  edge_z(s, s + kEFields * PL, 0, 1, own, Exm, txm);
+  edge_z(s, s + kEFields * PL, 1, kEhx, own, Eym, tym);
+  int lo_s = 1, hi_s = 2;
+  T uzm = s[2 * PL + own];                                   // u_z of the plane below
+  for (int z = z0; z < z0 + zc; ++z) {
+    store(z + 1, hi_s);
+    request_own(z);
+    __syncthreads();   // (the slot after this one was last read two planes ago, before the previous barrier)
+    if (z + 1 < z0 + zc) request(z + 2);
+    const T *p = s + lo_s * kEFields * PL, *pu = s + hi_s * kEFields * PL;
+    const T *c = p + 3 * PL, *ph = p + 4 * PL;
+    const int i = own;
+    // the edges one after another (held apart: with all their LDS reads hoisted together the kernel spills)
+    T dE[3], dt[3], E, t, Exz, txz, Eyz, tyz;
+    edge_xy(p, i, E, t);
+    dE[0] = dE[1] = E;
+    dt[0] = dt[1] = t;
+    edge_xy(p, i - kEhx, E, t);
+    dE[0] -= E;
+    dt[0] -= t;
+    edge_xy(p, i - 1, E, t);
+    dE[1] -= E;
+    dt[1] -= t;
+    __builtin_amdgcn_sched_barrier(0);
+    edge_z(p, pu, 0, 1, i, Exz, txz);
+    dE[0] += Exz - Exm;
+    dt[0] += txz - txm;
+    edge_z(p, pu, 0, 1, i - 1, E, t);
+    dE[2] = Exz - E;
+    dt[2] = txz - t;
+    __builtin_amdgcn_sched_barrier(0);
+    edge_z(p, pu, 1, kEhx, i, Eyz, tyz);
+    dE[1] += Eyz - Eym;
+    dt[1] += tyz - tym;
+    edge_z(p, pu, 1, kEhx, i - kEhx, E, t);
+    dE[2] += Eyz - E;
+    dt[2] += tyz - t;
+    __builtin_amdgcn_sched_barrier(0);
+    const T C0 = c[i], p0 = ph[i];
+    const T m0 = q.mu0 + T(4) * q.mu1 * C0;
+    const int64_t cell = ((int64_t)z << psh) + col;
+    auto face = [&](int a, T um, T u0, T up, T Ca, T pa, T dE, T dt_) {
+      const T ma = q.mu0 + T(4) * q.mu1 * Ca;
+      const T f1 = u0 + up, f0 = um + u0;
+      const T N = ((f1 * f1 - f0 * f0) + dE) * q.n_fac;
+      const T V = (T(2) * (ma * (up - u0) - m0 * (u0 - um)) + dt_) * q.v_fac;
+      const T F = q.f_fac * (p0 + pa) * (Ca - C0);
+      const T VF = EQ ? (V + F) * inv_rf : (V + F) / (q.rf0 + q.rf1 * (C0 + Ca));
+      const T Np = first ? N : nh[a];
+      const T us = u0 + k.dt * (-(T(1.5) * N - T(0.5) * Np) + VF + k.g[a]);
+      __builtin_nontemporal_store(af[a] * us, Us.f[a] + cell);
+      __builtin_nontemporal_store(N, Nh.f[a] + cell);
+    };
+    face(0, p[i - 1], p[i], p[i + 1], c[i + 1], ph[i + 1], dE[0], dt[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    face(1, p[PL + i - kEhx], p[PL + i], p[PL + i + kEhx], c[i + kEhx], ph[i + kEhx], dE[1], dt[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (z < nz - 1) {
+      face(2, uzm, p[2 * PL + i], pu[2 * PL + i], pu[3 * PL + i], pu[4 * PL + i], dE[2], dt[2]);
+    } else {           // top wall face
+      Us.f[2][cell] = T(0);
+      Nh.f[2][cell] = T(0);
+    }
+    uzm = p[2 * PL + i];
+    Exm = Exz;
+    txm = txz;
+    Eym = Eyz;
+    tym = tyz;
+    const int nx_s = 3 - lo_s - hi_s;
+    lo_s = hi_s;
+    hi_s = nx_s;
   }
 }
 
@@ -462,114 +512,171 @@ __global__ __launch_bounds__(kNsThreads) void k_ns_correct(FaceSet<T> U, FaceSet
   for_each_cell(wk, g, [&](int64_t c) { ns_correct_cell<T, D>(U, Ut, Us, C, Pn, P0, P1, g, k, with_ut, c); });
 }
 
-// 3D z-marching forms of the pressure rhs and the correction (tiled walk only): a thread carries its
-// column's values of the planes below and above from one plane to the next instead of fetching them
-// again; x and y neighbours come through the caches.  Same expressions as the per-cell forms.
-struct ZCol {
-  int c0;          // linear index of the column's first plane
-  int oxp, oxm, oyp, oym;
-  int k0, k1;      // planes [k0, k1)
-  int psh;         // log2 of the plane size
-};
-
-__device__ __forceinline__ ZCol zcol(const NsWalk &wk, const NsGrid &g, int b) {
-  ZCol z;
-  const int bx = b & ((1 << wk.lbx) - 1);
-  const int by = (b >> wk.lbx) & ((1 << wk.lby) - 1);
-  const int bz = b >> (wk.lbx + wk.lby);
-  const int i = (bx << wk.ltx) + (int)(threadIdx.x & ((1u << wk.ltx) - 1));
-  const int j = (by << wk.lty) + (int)(threadIdx.x >> wk.ltx);
-  z.psh = g.ln[0] + g.ln[1];
-  z.k0 = bz * wk.zc;
-  z.k1 = z.k0 + wk.zc;
-  z.c0 = i + (j << g.ln[0]) + (z.k0 << z.psh);
-  z.oxp = ((i + 1) & (g.n[0] - 1)) - i;
-  z.oxm = ((i - 1) & (g.n[0] - 1)) - i;
-  z.oyp = (((j + 1) & (g.n[1] - 1)) - j) << g.ln[0];
-  z.oym = (((j - 1) & (g.n[1] - 1)) - j) << g.ln[0];
-  return z;
-}
+// 3D pressure rhs marching in z over a 64 x 8 tile: p^, C, u**_x and u**_y of a plane go to LDS once with
+// the halo cells that their differences need (through the caches the neighbours' loads came too late for
+// the L2, and a 64^3 grid of 64 workgroups waited for them plane after plane); the z neighbours and the z
+// flux below stay in registers.  Same expressions as the per-cell form, with p^ formed once per cell.
+constexpr int kPx = 64, kPy = 8, kPThreads = kPx * kPy, kPp = kPx + 2;
 
 template <typename T>
-__global__ __launch_bounds__(kNsThreads) void k_ns_pressure_rhs_zm(FaceSet<T> Us, const T *__restrict__ C,
-                                                                   const T *__restrict__ P0,
-                                                                   const T *__restrict__ P1, T *__restrict__ R,
-                                                                   NsGrid g, NsCoef<T> k, NsWalk wk) {
-  // XCD-aware tile order: the y-neighbour tiles whose rows this pass re-reads run on the same L2
-  // (0.298 -> 0.280 ms at 256^3; the correction and the prediction ran slower with it)
-  const ZCol z = zcol(wk, g, xcd_tile(blockIdx.x, gridDim.x));
-  const int nz = g.n[2], pl = 1 << z.psh;
-  auto ph = [&](int i) { return T(2) * P0[i] - P1[i]; };
-  int c = z.c0;
-  const int cb = z.k0 > 0 ? c - pl : c;     // the plane below (the first plane itself at the bottom)
-  T ph_m = ph(cb), r_m = rho_of(k, C[cb]), uz_m = Us.f[2][cb];
-  T phc = ph(c), rc = rho_of(k, C[c]);
-  for (int kz = z.k0; kz < z.k1; ++kz, c += pl) {
-    const bool top = kz == nz - 1, bottom = kz == 0;
-    const int cp = top ? c : c + pl;
-    const T ph_p = ph(cp), r_p = rho_of(k, C[cp]);
-    T acc1 = T(0), acc2 = T(0);
+__global__ __launch_bounds__(kPThreads) void k_ns_pressure_rhs_zm(FaceSet<T> Us, const T *__restrict__ C,
+                                                                  const T *__restrict__ P0, const T *__restrict__ P1,
+                                                                  T *__restrict__ R, NsGrid g, NsCoef<T> k, int zc) {
+  __shared__ T s[2][4][(kPy + 2) * kPp];                     // p^, C, u**_x, u**_y
+  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+  const int tiles_x = nx / kPx, tiles_y = ny / kPy;
+  int b = (int)blockIdx.x;
+  const int bx = b % tiles_x;
+  b /= tiles_x;
+  const int by = b % tiles_y;
+  const int z0 = (b / tiles_y) * zc;
+  const int tid = (int)threadIdx.x, tx = tid & (kPx - 1), ty = tid >> 6;
+  const int x0 = bx * kPx, y0 = by * kPy;
+  const int psh = g.ln[0] + g.ln[1];
+  const int col = x0 + tx + ((y0 + ty) << g.ln[0]);
+  const int i = (ty + 1) * kPp + tx + 1;
+  // halo cells: the rows below and above (waves 0 and 1), the columns left and right (8 threads each)
+  const bool row = tid < 2 * kPx, halo = tid < 2 * kPx + 2 * kPy;
+  const int e = tid - 2 * kPx;
+  const bool low = row ? tid < kPx : e < kPy;
+  const int hr = row ? (low ? 0 : kPy + 1) : 1 + (e & (kPy - 1)), hc = row ? 1 + tx : (low ? 0 : kPx + 1);
+  const int hcol = halo ? ((x0 - 1 + hc) & (nx - 1)) + (((y0 - 1 + hr) & (ny - 1)) << g.ln[0]) : col;
+  const int hi = hr * kPp + hc;
+  const int hf = row ? 1 : 0;                                // the velocity whose difference needs this halo cell
+  T v[5], hv[3];
+  auto request = [&](int z) {
+    const int64_t zb = (int64_t)(z >= nz ? nz - 1 : z) << psh;
+    v[0] = T(2) * P0[zb + col] - P1[zb + col];
+    v[1] = C[zb + col];
+    v[2] = Us.f[0][zb + col];
+    v[3] = Us.f[1][zb + col];
+    v[4] = Us.f[2][zb + col];
+    if (halo) {
+      hv[0] = T(2) * P0[zb + hcol] - P1[zb + hcol];
+      hv[1] = C[zb + hcol];
+      if (low) hv[2] = Us.f[hf][zb + hcol];
+    }
+  };
+  // flux (1 - rho0/rho_f) dp^ through the face between two cells, and u** through the z face below
+  auto flux = [&](T r0, T r1, T p0, T p1) { return (T(1) - k.rho0 / (T(0.5) * (r0 + r1))) * ((p1 - p0) * k.inv_h); };
+  T fz = T(0), uz = T(0);
+  if (z0 > 0) {
+    const int64_t m = ((int64_t)(z0 - 1) << psh) + col, c = ((int64_t)z0 << psh) + col;
+    fz = flux(rho_of(k, C[m]), rho_of(k, C[c]), T(2) * P0[m] - P1[m], T(2) * P0[c] - P1[c]);
+    uz = Us.f[2][m];
+  }
+  request(z0);
+  for (int z = z0; z < z0 + zc; ++z) {
+    T (*p)[(kPy + 2) * kPp] = s[z & 1];
+    const T ph = v[0], rc = rho_of(k, v[1]), ux = v[2], uy = v[3], uzc = v[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) p[f][i] = v[f];
+    if (halo) {
+      p[0][hi] = hv[0];
+      p[1][hi] = hv[1];
+      if (low) p[2 + hf][hi] = hv[2];
+    }
+    request(z + 1);
+    __syncthreads();   // (the slot written next plane was last read a plane ago, before this barrier)
+    const bool top = z == nz - 1;
+    T acc1 = T(0), acc2 = (ux - p[2][i - 1]) + (uy - p[3][i - kPp]);
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-      const int i1 = c + (a == 0 ? z.oxp : z.oyp), i0 = c + (a == 0 ? z.oxm : z.oym);
-      const T rf1 = T(0.5) * (rc + rho_of(k, C[i1]));
-      const T rf0 = T(0.5) * (rho_of(k, C[i0]) + rc);
-      const T fu = (T(1) - k.rho0 / rf1) * ((ph(i1) - phc) * k.inv_h);
-      const T fl = (T(1) - k.rho0 / rf0) * ((phc - ph(i0)) * k.inv_h);
-      acc1 += fu - fl;
-      acc2 += Us.f[a][c] - Us.f[a][i0];
+      const int up = a == 0 ? i + 1 : i + kPp, dn = a == 0 ? i - 1 : i - kPp;
+      acc1 += flux(rc, rho_of(k, p[1][up]), ph, p[0][up]) - flux(rho_of(k, p[1][dn]), rc, p[0][dn], ph);
     }
-    const T uzc = Us.f[2][c];
-    const T fu1 = (T(1) - k.rho0 / (T(0.5) * (rc + r_p))) * ((ph_p - phc) * k.inv_h);
-    const T fl0 = (T(1) - k.rho0 / (T(0.5) * (r_m + rc))) * ((phc - ph_m) * k.inv_h);
+    const T fu1 = flux(rc, rho_of(k, v[1]), ph, v[0]);
     const T fu = top ? T(0) : fu1, uu = top ? T(0) : uzc;
-    const T fl = bottom ? T(0) : fl0, ul = bottom ? T(0) : uz_m;
-    acc1 += fu - fl;
-    acc2 += uu - ul;
-    R[c] = acc1 * k.inv_h + k.rho0_dt * (acc2 * k.inv_h);
-    ph_m = phc;
-    r_m = rc;
-    uz_m = uzc;
-    phc = ph_p;
-    rc = r_p;
+    acc1 += fu - fz;
+    acc2 += uu - uz;
+    R[((int64_t)z << psh) + col] = acc1 * k.inv_h + k.rho0_dt * (acc2 * k.inv_h);
+    fz = fu1;
+    uz = uzc;
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kNsThreads) void k_ns_correct_zm(FaceSet<T> U, FaceSet<T> Ut, FaceSet<T> Us,
-                                                              const T *__restrict__ C, const T *__restrict__ Pn,
-                                                              const T *__restrict__ P0, const T *__restrict__ P1,
-                                                              NsGrid g, NsCoef<T> k, int with_ut, NsWalk wk) {
-  const ZCol z = zcol(wk, g, (int)blockIdx.x);
-  const int nz = g.n[2], pl = 1 << z.psh;
-  int c = z.c0;
-  T pc = Pn[c], phc = T(2) * P0[c] - P1[c], rc = rho_of(k, C[c]);
-  for (int kz = z.k0; kz < z.k1; ++kz, c += pl) {
-    const bool top = kz == nz - 1;
-    const int cp = top ? c : c + pl;
-    const T p_p = Pn[cp], ph_p = T(2) * P0[cp] - P1[cp], r_p = rho_of(k, C[cp]);
+// 3D correction marching in z over a 64 x 8 tile.  Bound by memory (128 bytes per cell at 256^3 FP64, 104
+// with equal densities): the pressure fields and C of a plane go to LDS once, with the halo column and
+// row above, because the neighbours' loads of the same lines came so late that the 4 MB L2 had given
+// them up (141 bytes read per cell of 80).  EQ: with equal densities 1/rho_f - 1/rho0 vanishes, and with
+// it the term in p^ and the reads of C, p^n and p^(n-1).  u and u** pass through once (streaming).
+constexpr int kCx = 64, kCy = 8, kCThreads = kCx * kCy, kCp = kCx + 1;
+
+template <typename T, bool EQ>
+__global__ __launch_bounds__(kCThreads) void k_ns_correct_zm(FaceSet<T> U, FaceSet<T> Ut, FaceSet<T> Us,
+                                                             const T *__restrict__ C, const T *__restrict__ Pn,
+                                                             const T *__restrict__ P0, const T *__restrict__ P1,
+                                                             NsGrid g, NsCoef<T> k, int with_ut, int zc) {
+  constexpr int NF = EQ ? 1 : 3;                              // p^(n+1), p^, C
+  __shared__ T s[2][NF][(kCy + 1) * kCp];
+  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+  const int tiles_x = nx / kCx, tiles_y = ny / kCy;
+  int b = (int)blockIdx.x;
+  const int bx = b % tiles_x;
+  b /= tiles_x;
+  const int by = b % tiles_y;
+  const int z0 = (b / tiles_y) * zc;
+  const int tid = (int)threadIdx.x, tx = tid & (kCx - 1), ty = tid >> 6;
+  const int x0 = bx * kCx, y0 = by * kCy;
+  const int psh = g.ln[0] + g.ln[1];
+  const int col = x0 + tx + ((y0 + ty) << g.ln[0]);
+  const int i = ty * kCp + tx;
+  // threads below 64 + 8 also bring a cell of the row above or of the column to the right
+  const bool halo = tid < kCx + kCy;
+  const int hx = tid < kCx ? x0 + tid : (x0 + kCx) & (nx - 1);
+  const int hy = tid < kCx ? (y0 + kCy) & (ny - 1) : y0 + (tid - kCx);
+  const int hcol = halo ? hx + (hy << g.ln[0]) : col;
+  const int hi = tid < kCx ? kCy * kCp + tid : (tid - kCx) * kCp + kCx;
+  T v[NF], hv[NF];
+  auto request = [&](int z) {
+    const int64_t zb = (int64_t)(z >= nz ? nz - 1 : z) << psh;
+    v[0] = Pn[zb + col];
+    if (halo) hv[0] = Pn[zb + hcol];
+    if constexpr (!EQ) {
+      v[1] = T(2) * P0[zb + col] - P1[zb + col];
+      v[2] = C[zb + col];
+      if (halo) {
+        hv[1] = T(2) * P0[zb + hcol] - P1[zb + hcol];
+        hv[2] = C[zb + hcol];
+      }
+    }
+  };
+  request(z0);
+  for (int z = z0; z < z0 + zc; ++z) {
+    T (*p)[(kCy + 1) * kCp] = s[z & 1];
+    T c[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      c[f] = v[f];
+      p[f][i] = v[f];
+      if (halo) p[f][hi] = hv[f];
+    }
+    const int64_t cell = ((int64_t)z << psh) + col;
+    request(z + 1);
+    T us[3], uo[3] = {T(0), T(0), T(0)};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      T Gn, Gh, rf;
-      if (a < 2) {
-        const int ca = c + (a == 0 ? z.oxp : z.oyp);
-        Gn = (Pn[ca] - pc) * k.inv_h;
-        Gh = ((T(2) * P0[ca] - P1[ca]) - phc) * k.inv_h;
-        rf = T(0.5) * (rc + rho_of(k, C[ca]));
-      } else {
-        Gn = (p_p - pc) * k.inv_h;
-        Gh = (ph_p - phc) * k.inv_h;
-        rf = T(0.5) * (rc + r_p);
-      }
-      const T u1 = Us.f[a][c] - k.dt * (Gn * k.inv_rho0 + (T(1) / rf - k.inv_rho0) * Gh);
-      const T un = (a == 2 && top) ? T(0) : u1;
-      const T uo = U.f[a][c];
-      U.f[a][c] = un;
-      if (with_ut) Ut.f[a][c] = T(2) * un - uo;
+      us[a] = __builtin_nontemporal_load(Us.f[a] + cell);
+      if (with_ut) uo[a] = __builtin_nontemporal_load(U.f[a] + cell);
     }
-    pc = p_p;
-    phc = ph_p;
-    rc = r_p;
+    __syncthreads();   // (the slot written next plane was last read a plane ago, before this barrier)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int in = a == 0 ? i + 1 : i + kCp;
+      auto up = [&](int f) { return a == 2 ? v[f] : p[f][in]; };
+      const T Gn = (up(0) - c[0]) * k.inv_h;
+      T u1;
+      if constexpr (EQ) {
+        u1 = us[a] - k.dt * (Gn * k.inv_rho0);
+      } else {
+        const T Gh = (up(1) - c[1]) * k.inv_h;
+        const T rf = T(0.5) * (rho_of(k, c[2]) + rho_of(k, up(2)));
+        u1 = us[a] - k.dt * (Gn * k.inv_rho0 + (T(1) / rf - k.inv_rho0) * Gh);
+      }
+      const T un = (a == 2 && z == nz - 1) ? T(0) : u1;
+      __builtin_nontemporal_store(un, U.f[a] + cell);
+      if (with_ut) __builtin_nontemporal_store(T(2) * un - uo[a], Ut.f[a] + cell);
+    }
   }
 }
 
@@ -590,6 +697,19 @@ NsCoef<T> ns_coef(const Plan &p) {
   k.inv_rho0 = (T)(1.0 / rho0);
   k.rho0_dt = (T)(rho0 / p.dt);
   return k;
+}
+
+template <typename T>
+PredictCoef<T> predict_coef(const Plan &p) {
+  PredictCoef<T> q;
+  q.mu0 = (T)(0.5 * (p.mu1 + p.mu2));
+  q.mu1 = (T)(0.125 * (p.mu2 - p.mu1));      // a quarter of mu's slope: it meets sums of four cells
+  q.rf0 = (T)(0.5 * (p.rho1 + p.rho2));
+  q.rf1 = (T)(0.25 * (p.rho2 - p.rho1));
+  q.n_fac = (T)(0.25 / p.h);
+  q.v_fac = (T)(1.0 / (p.Re * p.h * p.h));
+  q.f_fac = (T)(3.0 / (2.0 * 1.4142135623730951 * p.Re * p.Ca * p.Cn) * 0.5 / p.h);
+  return q;
 }
 
 NsGrid ns_grid(const Plan &p) {
@@ -624,6 +744,14 @@ NsWalk ns_walk(const Plan &p, unsigned *nb) {
   return w;
 }
 
+// Planes per workgroup of the tiled z-marches: 16 amortise the planes read at the chunk's ends; fewer
+// where that leaves the chip short of workgroups (128^3 prediction: 91 us with 32 planes, 63 with 16).
+int march_planes(const Plan &p, int tile) {
+  int zc = p.n[2] < 16 ? p.n[2] : 16;
+  while (zc > 4 && p.N / ((int64_t)tile * zc) < 512) zc >>= 1;
+  return zc;
+}
+
 template <typename T>
 FaceSet<T> faces(void *const *f, int d) {
   FaceSet<T> s;
@@ -648,6 +776,7 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
   const FaceSet<T> U = faces<T>(p.F, p.d), Us = faces<T>(p.Us, p.d), Nh = faces<T>(p.Nh, p.d);
   const FaceSet<T> Af = faces<T>(p.Af, p.d);
   const bool with_ut = p.Ut[0] != nullptr;
+  const bool eq = p.rho1 == p.rho2;   // equal densities: no term in p^, rho_f a constant
   const FaceSet<T> Ut = with_ut ? faces<T>(p.Ut, p.d) : U;
   mark("ns_phi");
   if (e == hipSuccess) e = enqueue_phi<T>(p, cur, p.W);
@@ -657,10 +786,16 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
       hipLaunchKernelGGL((k_ns_predict<T, 2>), dim3(nb), dim3(kNsThreads), 0, p.stream, U, C, (const T *)p.W, Nh, Af,
                          Us, g, k, first, wk);
     else if (p.n[0] % kEx == 0 && p.n[1] % kEy == 0) {
-      const int zc = p.n[2] < 16 ? p.n[2] : 16;
+      const int zc = march_planes(p, kEx * kEy);
       const unsigned nbe = (unsigned)((p.n[0] / kEx) * (p.n[1] / kEy) * (p.n[2] / zc));
-      hipLaunchKernelGGL((k_ns_predict_edges<T>), dim3(nbe), dim3(kEThreads), 0, p.stream, U, C, (const T *)p.W, Nh,
-                         Af, Us, g, k, first, zc);
+      const PredictCoef<T> q = predict_coef<T>(p);
+      const T inv_rf = (T)(1.0 / (0.5 * (p.rho1 + p.rho2)));
+      if (eq)
+        hipLaunchKernelGGL((k_ns_predict_zm<T, true>), dim3(nbe), dim3(kEThreads), predict_lds<T>(), p.stream, U, C,
+                           (const T *)p.W, Nh, Af, Us, g, k, q, inv_rf, first, zc);
+      else
+        hipLaunchKernelGGL((k_ns_predict_zm<T, false>), dim3(nbe), dim3(kEThreads), predict_lds<T>(), p.stream, U, C,
+                           (const T *)p.W, Nh, Af, Us, g, k, q, inv_rf, first, zc);
     } else
       hipLaunchKernelGGL((k_ns_predict<T, 3>), dim3(nb), dim3(kNsThreads), 0, p.stream, U, C, (const T *)p.W, Nh, Af,
                          Us, g, k, first, wk);
@@ -677,30 +812,44 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
     e = enqueue_velocity_fill<T>(q, C, join ? &nx : nullptr);
     if (link) link->dphi_done = join && e == hipSuccess;
   }
-  mark("ns_pressure_rhs");
-  if (e == hipSuccess) {
-    if (p.d == 2)
-      hipLaunchKernelGGL((k_ns_pressure_rhs<T, 2>), dim3(nb), dim3(kNsThreads), 0, p.stream, Us, C,
-                         (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, wk);
-    else if (!wk.flat)
-      hipLaunchKernelGGL((k_ns_pressure_rhs_zm<T>), dim3(nb), dim3(kNsThreads), 0, p.stream, Us, C,
-                         (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, wk);
-    else
-      hipLaunchKernelGGL((k_ns_pressure_rhs<T, 3>), dim3(nb), dim3(kNsThreads), 0, p.stream, Us, C,
-                         (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, wk);
-    e = hipGetLastError();
+  if (eq) {
+    // the right-hand side is (rho0/dt) div u** alone: formed inside the forward x transform
+    mark("ns_div_poisson");
+    if (e == hipSuccess) e = enqueue_poisson<T>(p, p.Us, (double)k.rho0_dt * (double)k.inv_h);
+  } else {
+    mark("ns_pressure_rhs");
+    if (e == hipSuccess) {
+      if (p.d == 2)
+        hipLaunchKernelGGL((k_ns_pressure_rhs<T, 2>), dim3(nb), dim3(kNsThreads), 0, p.stream, Us, C,
+                           (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, wk);
+      else if (p.n[0] % kPx == 0 && p.n[1] % kPy == 0) {
+        const int zc = march_planes(p, kPx * kPy);
+        const unsigned nbp = (unsigned)((p.n[0] / kPx) * (p.n[1] / kPy) * (p.n[2] / zc));
+        hipLaunchKernelGGL((k_ns_pressure_rhs_zm<T>), dim3(nbp), dim3(kPThreads), 0, p.stream, Us, C,
+                           (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, zc);
+      } else
+        hipLaunchKernelGGL((k_ns_pressure_rhs<T, 3>), dim3(nb), dim3(kNsThreads), 0, p.stream, Us, C,
+                           (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, wk);
+      e = hipGetLastError();
+    }
+    mark("ns_poisson");
+    if (e == hipSuccess) e = enqueue_poisson<T>(p);
   }
-  mark("ns_poisson");
-  if (e == hipSuccess) e = enqueue_poisson<T>(p);
   mark("ns_correct");
   if (e == hipSuccess) {
     if (p.d == 2)
       hipLaunchKernelGGL((k_ns_correct<T, 2>), dim3(nb), dim3(kNsThreads), 0, p.stream, U, Ut, Us, C,
                          (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, wk);
-    else if (!wk.flat)
-      hipLaunchKernelGGL((k_ns_correct_zm<T>), dim3(nb), dim3(kNsThreads), 0, p.stream, U, Ut, Us, C,
-                         (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, wk);
-    else
+    else if (p.n[0] % kCx == 0 && p.n[1] % kCy == 0) {
+      const int zc = march_planes(p, kCx * kCy);
+      const unsigned nbc = (unsigned)((p.n[0] / kCx) * (p.n[1] / kCy) * (p.n[2] / zc));
+      if (eq)
+        hipLaunchKernelGGL((k_ns_correct_zm<T, true>), dim3(nbc), dim3(kCThreads), 0, p.stream, U, Ut, Us, C,
+                           (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, zc);
+      else
+        hipLaunchKernelGGL((k_ns_correct_zm<T, false>), dim3(nbc), dim3(kCThreads), 0, p.stream, U, Ut, Us, C,
+                           (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, zc);
+    } else
       hipLaunchKernelGGL((k_ns_correct<T, 3>), dim3(nb), dim3(kNsThreads), 0, p.stream, U, Ut, Us, C,
                          (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, wk);
     e = hipGetLastError();

@@ -49,8 +49,8 @@ def algorithmic_bytes(name: str, cells: int, d: int, es: int, G: int, NF: int, d
         return G * per_ghost + NF * per_face
     if name == "phi":                                # explicit step: phi on every cell, mirror value at ghosts
         return cells * es * 2 + G * (4 + 2 * K * (4 + es) + 2 * K * es + es)
-    if name == "explicit_update":                    # C, phi, R, d faces in; C^(n+1), R out
-        return cells * es * (5 + d)
+    if name == "explicit_update":                    # C, R, d faces in; C^(n+1), R out (phi formed on the way)
+        return cells * es * (4 + d)
     if name == "ghost_fills":                        # static: both fills, one launch plus the faces
         return (algorithmic_bytes("ghost_fill_C", cells, d, es, G, NF, dynamic)
                 + algorithmic_bytes("ghost_fill_u", cells, d, es, G, NF, dynamic))
@@ -121,9 +121,9 @@ def kernel_template(name: str, shapes, es: int, n) -> list:
     if name == "ghost_fill_C":
         return [f"k_fill_static<{t}>"]
     if name == "ghost_fill_u":
-        return [f"k_vel_ghosts<{t}>", f"k_vel_faces<{t}>"]
+        return [f"k_vel_ghosts<{t}, 3, false>", f"k_vel_faces<{t}>"]
     if name == "ghost_fills":
-        return [f"k_fill_static_vel<{t}>", f"k_vel_faces_dphi<{t}, true>"]
+        return [f"k_fill_static_vel<{t}, 3>", f"k_vel_faces_dphi<{t}, true>"]
     return []
 
 

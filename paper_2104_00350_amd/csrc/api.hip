@@ -719,8 +719,8 @@ static hipError_t enqueue_one_step(ch_ib_state *st, chib::KernelTimer *tm, chib:
     }
   }
   if (p.explicit_ab2) {
-    e = st->es == 8 ? chib::enqueue_explicit_step<double>(q, st->cur, !st->r_valid, tm)
-                    : chib::enqueue_explicit_step<float>(q, st->cur, !st->r_valid, tm);
+    e = st->es == 8 ? chib::enqueue_explicit_step<double>(q, st->cur, !st->r_valid, tm, link)
+                    : chib::enqueue_explicit_step<float>(q, st->cur, !st->r_valid, tm, link);
     if (e == hipSuccess) st->r_valid = 1;
   } else {
     e = st->es == 8 ? chib::enqueue_step<double>(q, st->cur, tm, link)

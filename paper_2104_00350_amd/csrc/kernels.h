@@ -120,7 +120,7 @@ struct KernelTimer {
   hipError_t end(hipStream_t s) { return hipEventRecord(ev[n], s); }
 };
 
-// Consecutive semi-implicit steps of one call: with `next` the step's last kernel also runs the first
+// Consecutive steps of one call: with `next` the step's last kernel also runs the first
 // kernel of the following step's ghost patch (dphi_done on return, taken over by that step).
 struct StepLink {
   bool next = false;
@@ -135,7 +135,8 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm = nullptr, StepL
 template <typename T> hipError_t enqueue_initial_fill(const Plan &p, int cur);
 template <typename T> hipError_t tune_shapes(Plan &p, int cur, int reps);
 // One explicit Adams-Bashforth step (first: no previous rate, forward Euler) from C[cur] into C[1-cur].
-template <typename T> hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer *tm = nullptr);
+template <typename T>
+hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer *tm = nullptr, StepLink *link = nullptr);
 // Largest log2 tile height (passes 0 and 3: lines; 1 and 2: columns) a pass allows on this grid.
 template <typename T> int max_log_tile(const Plan &p, int pass);
 template <typename T> hipError_t enqueue_ghost_refresh(const Plan &p, int cur);   // static fill again, same step

@@ -1377,57 +1377,50 @@ __device__ __forceinline__ T mirror_gather(const T *__restrict__ f, const int *_
   return T(2) * o1 - o2;
 }
 
+// Neighbours of a cell, as offsets: periodic axes wrap, and along the bounded axis both ends are flagged.  D and
+// every index into the per-axis arrays below are compile-time constants: with the dimension at run time the
+// compiler kept those arrays in LDS.
+template <int D>
+struct Nbr {
+  int up[D], dn[D];
+  bool lo, hi;               // on the first / last layer of the bounded axis
+  __device__ __forceinline__ Nbr(int c, const Dims &dm) {
+    const int i = c & (dm.nx - 1), r = c >> dm.lnx;
+    up[0] = ((i + 1) & (dm.nx - 1)) - i;
+    dn[0] = ((i - 1) & (dm.nx - 1)) - i;
+    int w = r, nw = dm.ny, step = dm.nx;
+    if constexpr (D == 3) {
+      const int j = r & (dm.ny - 1);
+      up[1] = (((j + 1) & (dm.ny - 1)) - j) << dm.lnx;
+      dn[1] = (((j - 1) & (dm.ny - 1)) - j) << dm.lnx;
+      w = r >> dm.lny;
+      nw = dm.nz;
+      step = (int)dm.plane;
+    }
+    lo = w == 0;
+    hi = w == nw - 1;
+    up[D - 1] = step;
+    dn[D - 1] = -step;
+  }
+};
+
 // Central-difference gradient at a cell (periodic axes wrap, the bounded axis reflects).
-template <typename T>
-__device__ __forceinline__ void grad_at(const T *__restrict__ f, int64_t c, const Dims &dm, int d, T inv2h, T *g) {
-  const int i = (int)(c & (dm.nx - 1));
-  const int64_t r = c >> dm.lnx;
-  const int j = (int)(r & (dm.ny - 1));
-  const int k = (int)(r >> dm.lny);
-  const int64_t rowb = c - i;
-  g[0] = (f[rowb + ((i + 1) & (dm.nx - 1))] - f[rowb + ((i - 1) & (dm.nx - 1))]) * inv2h;
-  if (d == 2) {
-    const int64_t up = j < dm.ny - 1 ? c + dm.nx : c;
-    const int64_t dnn = j > 0 ? c - dm.nx : c;
-    g[1] = (f[up] - f[dnn]) * inv2h;
-  } else {
-    const int jp = (j + 1) & (dm.ny - 1), jm = (j - 1) & (dm.ny - 1);
-    g[1] = (f[c + (int64_t)(jp - j) * dm.nx] - f[c + (int64_t)(jm - j) * dm.nx]) * inv2h;
-    const int64_t up = k < dm.nz - 1 ? c + dm.plane : c;
-    const int64_t dnn = k > 0 ? c - dm.plane : c;
-    g[2] = (f[up] - f[dnn]) * inv2h;
+template <int D, typename T>
+__device__ __forceinline__ void grad_at(const T *__restrict__ f, int c, const Nbr<D> &nb, T inv2h, T (&g)[D]) {
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    const bool w = a == D - 1;
+    g[a] = (f[c + (w && nb.hi ? 0 : nb.up[a])] - f[c + (w && nb.lo ? 0 : nb.dn[a])]) * inv2h;
   }
 }
 
-// Cell-centred velocity component a: mean of the two faces along a (box-wall faces read 0).
-template <typename T>
-__device__ __forceinline__ T centred_u(const T *__restrict__ Fa, int64_t c, int a, const Dims &dm, int d) {
-  int64_t step;
-  int idx, n;
-  const int i = (int)(c & (dm.nx - 1));
-  const int64_t r = c >> dm.lnx;
-  const int j = (int)(r & (dm.ny - 1));
-  const int k = (int)(r >> dm.lny);
-  if (a == 0) {
-    const int64_t rowb = c - i;
-    return T(0.5) * (Fa[rowb + ((i - 1) & (dm.nx - 1))] + Fa[c]);
-  }
-  if (a == 1) {
-    step = dm.nx;
-    idx = j;
-    n = dm.ny;
-  } else {
-    step = dm.plane;
-    idx = k;
-    n = dm.nz;
-  }
-  if (a < d - 1) {  // periodic y in 3D
-    const int jm = (j - 1) & (dm.ny - 1);
-    return T(0.5) * (Fa[c + (int64_t)(jm - j) * dm.nx] + Fa[c]);
-  }
-  const T lo = idx > 0 ? Fa[c - step] : T(0);
-  const T hi = idx < n - 1 ? Fa[c] : T(0);
-  return T(0.5) * (lo + hi);
+// Cell-centred velocity component a: mean of the two faces along a (box-wall faces read 0; every load
+// happens, from the cell itself at a wall).
+template <int D, typename T>
+__device__ __forceinline__ T centred_u(const T *__restrict__ Fa, int c, const Nbr<D> &nb, int a) {
+  const bool w = a == D - 1;
+  const T lo = Fa[c + (w && nb.lo ? 0 : nb.dn[a])], hi = Fa[c];
+  return T(0.5) * ((w && nb.lo ? T(0) : lo) + (w && nb.hi ? T(0) : hi));
 }
 
 // Sum over the 16 lanes of an aligned lane group (fixed order: deterministic).
@@ -1498,59 +1491,74 @@ __global__ __launch_bounds__(kThreads) void k_scatter_pg(T *__restrict__ C, cons
 // C_I <- C_I + dt [ -u_I . grad_t C_I + Vs (Cn dC/dn + cos(theta)(1 - C_I*^2)/sqrt2) ],
 // C_I* = (gamma C^_G + C_M)/(gamma+1), dC/dn = (C_M - C^_G)/((1+gamma) dn); then
 // C_G = ((gamma+1) C_I - C_M)/gamma.  All reads from the provisional field (Jacobi).
-template <typename T>
+// Sixteen lanes per ghost: lane s < 2K one weighted averaging point, lane 2K the ghost itself (one thread
+// per ghost walked 2K (1 + 4d) gathers: 23.5 us for 1024 ghosts, 6 us now).
+template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void k_fill_dynamic(
     const T *__restrict__ C, const T *__restrict__ F0, const T *__restrict__ F1, const T *__restrict__ F2,
     const int *__restrict__ gidx, const T *__restrict__ nrm, const T *__restrict__ dn, const T *__restrict__ gam,
     const int *__restrict__ ap, const T *__restrict__ w, T *__restrict__ CI, T *__restrict__ CGnew,
-    T *__restrict__ CMs, int64_t G, int K, Dims dm, int d, T inv2h, T Cn, T Vs, T cos_t, T dt, int init) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= G) return;
-  const int64_t cg = gidx[g];
-  const T PG = C[cg];
-  const T CM = mirror_gather(C, ap, w, g, G, K);
-  const T ga = gam[g];
-  const T CIs = (ga * PG + CM) / (ga + T(1));
-  CMs[g] = CM;
-  if (init) {
-    CI[g] = CIs;
-    CGnew[g] = PG;
-    return;
-  }
-  T gG[3] = {0, 0, 0}, gM[3] = {0, 0, 0}, n[3] = {0, 0, 0}, uG[3] = {0, 0, 0}, uM[3] = {0, 0, 0};
-  grad_at(C, cg, dm, d, inv2h, gG);
+    T *__restrict__ CMs, int64_t G, int K, Dims dm, T inv2h, T Cn, T Vs, T cos_t, T dt, int init) {
+  const int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+  const int sl = threadIdx.x & 15;
+  const int64_t gs = g < G ? g : G - 1;
+  const T ga = gam[gs], dng = dn[gs], ci0 = CI[gs];
+  const int cg = gidx[gs];
+  T n[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) n[a] = nrm[(int64_t)a * G + gs];
   const T *Fs[3] = {F0, F1, F2};
-  for (int jp = 0; jp < 2; ++jp) {
-    const T coef = jp == 0 ? T(2) : T(-1);
-    for (int k = 0; k < K; ++k) {
-      const int64_t sl = (int64_t)(jp * K + k) * G + g;
-      const T wk = w[sl];
-      const int64_t c = ap[sl];
-      T gk[3];
-      grad_at(C, c, dm, d, inv2h, gk);
-      for (int a = 0; a < d; ++a) {
-        gM[a] += coef * wk * gk[a];
-        uM[a] += coef * wk * centred_u(Fs[a], c, a, dm, d);
+  // per lane: its share of C_M and of the mirror gradient and velocity; lane 2K the ghost's own
+  T cm = T(0), pg = T(0), gm[D], um[D], gg[D], ug[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) gm[a] = um[a] = gg[a] = ug[a] = T(0);
+  if (g < G && sl <= 2 * K) {
+    const int64_t i = g * kGhostSlots + sl;
+    const bool own = sl == 2 * K;
+    const int c = own ? cg : ap[i];
+    const T cw = own ? T(1) : (sl < K ? T(2) : T(-1)) * w[i];
+    const T v = cw * C[c];
+    cm = own ? T(0) : v;
+    pg = own ? v : T(0);
+    if (!init) {
+      const Nbr<D> nb(c, dm);
+      T gk[D];
+      grad_at<D>(C, c, nb, inv2h, gk);
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        const T u = cw * centred_u<D>(Fs[a], c, nb, a), gv = cw * gk[a];
+        gm[a] = own ? T(0) : gv;
+        gg[a] = own ? gv : T(0);
+        um[a] = own ? T(0) : u;
+        ug[a] = own ? u : T(0);
       }
     }
   }
-  T gn = T(0), un = T(0);
-  for (int a = 0; a < d; ++a) {
-    n[a] = nrm[(int64_t)a * G + g];
-    uG[a] = centred_u(Fs[a], cg, a, dm, d);
+  const T CM = group16_sum(cm), PG = group16_sum(pg);
+  const T CIs = (ga * PG + CM) / (ga + T(1));
+  if (init) {
+    if (g < G && sl == 0) {
+      CMs[g] = CM;
+      CI[g] = CIs;
+      CGnew[g] = PG;
+    }
+    return;
   }
-  T gI[3], uI[3];
-  for (int a = 0; a < d; ++a) {
-    gI[a] = (ga * gG[a] + gM[a]) / (ga + T(1));
-    uI[a] = (ga * uG[a] + uM[a]) / (ga + T(1));
+  T gI[D], uI[D], gn = T(0);
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    gI[a] = (ga * group16_sum(gg[a]) + group16_sum(gm[a])) / (ga + T(1));
+    uI[a] = (ga * group16_sum(ug[a]) + group16_sum(um[a])) / (ga + T(1));
     gn += gI[a] * n[a];
   }
+  if (g >= G || sl != 0) return;
   T adv = T(0);
-  for (int a = 0; a < d; ++a) adv += uI[a] * (gI[a] - gn * n[a]);
-  (void)un;
-  const T dCdn = (CM - PG) / ((T(1) + ga) * dn[g]);
+#pragma unroll
+  for (int a = 0; a < D; ++a) adv += uI[a] * (gI[a] - gn * n[a]);
+  const T dCdn = (CM - PG) / ((T(1) + ga) * dng);
   const T rhs = -adv + Vs * (Cn * dCdn + cos_t * (T(1) - CIs * CIs) * T(0.70710678118654752440));
-  const T ci = CI[g] + dt * rhs;
+  const T ci = ci0 + dt * rhs;
+  CMs[g] = CM;
   CI[g] = ci;
   CGnew[g] = ((ga + T(1)) * ci - CM) / ga;
 }
@@ -1692,31 +1700,32 @@ __global__ __launch_bounds__(kThreads) void k_rhs_patch(T *__restrict__ Q, const
 // ghost's own gradient); the remaining blocks take one face per thread.  With the static
 // condition (capillary = 0) the wall equation makes the bracket Kc of Eq. UpdateVtan zero,
 // and no gradient of C is gathered.
-template <typename T>
+template <typename T, int D, bool CAP>
 __device__ __forceinline__ void vel_ghosts_body(
     const T *__restrict__ C, const T *__restrict__ F0, const T *__restrict__ F1, const T *__restrict__ F2,
     const int *__restrict__ gidx, const T *__restrict__ nrm, const T *__restrict__ dn, const T *__restrict__ gam,
     const int *__restrict__ ap, const T *__restrict__ w, const T *__restrict__ CMs, T *__restrict__ UG, int64_t G,
     int K, const int *__restrict__ f_cell, const int *__restrict__ f_axis, const int *__restrict__ f_gL,
-    const int *__restrict__ f_gR, T *__restrict__ stashL, T *__restrict__ stashR, int64_t NF, Dims dm, int d,
-    T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls, int capillary, unsigned nbg, int64_t tile) {
+    const int *__restrict__ f_gR, T *__restrict__ stashL, T *__restrict__ stashR, int64_t NF, const Dims &dm,
+    T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls, unsigned nbg, int64_t tile) {
   const T *Fs[3] = {F0, F1, F2};
   if (tile >= nbg) {
     const int64_t f = (int64_t)(tile - nbg) * blockDim.x + threadIdx.x;
     if (f >= NF) return;
-    const int a = f_axis[f];
-    const int64_t cL = f_cell[f];
-    int64_t cR;
-    {
-      const int i = (int)(cL & (dm.nx - 1));
-      const int64_t r = cL >> dm.lnx;
-      const int j = (int)(r & (dm.ny - 1));
-      if (a == 0) cR = cL - i + ((i + 1) & (dm.nx - 1));
-      else if (a == 1) cR = (d == 3) ? cL + (int64_t)(((j + 1) & (dm.ny - 1)) - j) * dm.nx : cL + dm.nx;
-      else cR = cL + dm.plane;
-    }
-    stashL[f] = f_gL[f] < 0 ? centred_u(Fs[a], cL, a, dm, d) : T(0);
-    stashR[f] = f_gR[f] < 0 ? centred_u(Fs[a], cR, a, dm, d) : T(0);
+    const int ax = f_axis[f], cL = f_cell[f], gL = f_gL[f], gR = f_gR[f];
+    const Nbr<D> nl(cL, dm);
+    T vL = T(0), vR = T(0);
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+      if (ax == a) {
+        // (a list face never lies on a box wall: its right cell is inside)
+        const int cR = cL + nl.up[a];
+        const Nbr<D> nr(cR, dm);
+        if (gL < 0) vL = centred_u<D>(Fs[a], cL, nl, a);
+        if (gR < 0) vR = centred_u<D>(Fs[a], cR, nr, a);
+      }
+    stashL[f] = vL;
+    stashR[f] = vR;
     return;
   }
   const int64_t g = ((int64_t)tile * blockDim.x + threadIdx.x) >> 4;
@@ -1724,84 +1733,96 @@ __device__ __forceinline__ void vel_ghosts_body(
   // the ghost's own table entries are requested with the gathers, not after the lane sums
   const int64_t gs = g < G ? g : G - 1;
   const T ga = gam[gs], dng = dn[gs];
-  T n[3] = {0, 0, 0};
-  for (int a = 0; a < d; ++a) n[a] = nrm[(int64_t)a * G + gs];
-  T gm[3] = {0, 0, 0}, um[3] = {0, 0, 0}, gg[3] = {0, 0, 0};
+  const int cg = CAP ? gidx[gs] : 0;
+  T n[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) n[a] = nrm[(int64_t)a * G + gs];
+  T gm[D], um[D], gg[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) gm[a] = um[a] = gg[a] = T(0);
   if (g < G) {
     if (sl < 2 * K) {
       const int64_t i = g * kGhostSlots + sl;
       const T cw = (sl < K ? T(2) : T(-1)) * w[i];
-      const int64_t c = ap[i];
-      T gk[3] = {0, 0, 0};
-      if (capillary) grad_at(C, c, dm, d, inv2h, gk);
-      for (int a = 0; a < d; ++a) {
-        gm[a] = cw * gk[a];
-        um[a] = cw * centred_u(Fs[a], c, a, dm, d);
+      const int c = ap[i];
+      const Nbr<D> nb(c, dm);
+      if constexpr (CAP) {
+        T gk[D];
+        grad_at<D>(C, c, nb, inv2h, gk);
+#pragma unroll
+        for (int a = 0; a < D; ++a) gm[a] = cw * gk[a];
       }
-    } else if (sl == 2 * K && capillary) {
-      grad_at(C, (int64_t)gidx[g], dm, d, inv2h, gg);
+#pragma unroll
+      for (int a = 0; a < D; ++a) um[a] = cw * centred_u<D>(Fs[a], c, nb, a);
+    } else if (CAP && sl == 2 * K) {
+      grad_at<D>(C, cg, Nbr<D>(cg, dm), inv2h, gg);
     }
   }
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    gm[a] = group16_sum(gm[a]);
+  for (int a = 0; a < D; ++a) {
     um[a] = group16_sum(um[a]);
-    gg[a] = group16_sum(gg[a]);
+    if constexpr (CAP) {
+      gm[a] = group16_sum(gm[a]);
+      gg[a] = group16_sum(gg[a]);
+    }
   }
   if (g >= G || sl != 0) return;
-  T VnM = T(0), gIn = T(0), gI[3];
-  for (int a = 0; a < d; ++a) {
+  T VnM = T(0), gIn = T(0), gI[D];
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
     VnM += um[a] * n[a];
-    gI[a] = (ga * gg[a] + gm[a]) / (ga + T(1));
+    gI[a] = CAP ? (ga * gg[a] + gm[a]) / (ga + T(1)) : T(0);
     gIn += gI[a] * n[a];
   }
   const T VnG = -VnM / ga;
-  T Kc = T(0);
-  if (capillary) {   // only then are C and C_M read (the static fill may be writing them meanwhile)
-    const T CG = C[gidx[g]], CM = CMs[g];
+  const T den = ls + ga * dng;
+  const T fM = (ls - dng) / den;
+  T Kc = T(0), fK = T(0);
+  if constexpr (CAP) {   // only then are C and C_M read (the static fill may be writing them meanwhile)
+    const T CG = C[cg], CM = CMs[g];
     const T CIv = (ga * CG + CM) / (ga + T(1));
     const T dCdn = (CM - CG) / ((T(1) + ga) * dng);
     Kc = (T(1.06066017177982128660) * Cn * dCdn + T(0.75) * cos_t * (T(1) - CIv * CIv)) * inv_Ca;
+    fK = ls * (ga + T(1)) * dng * inv_mu / den;
   }
-  const T den = ls + ga * dng;
-  const T fM = (ls - dng) / den;
-  const T fK = ls * (ga + T(1)) * dng * inv_mu / den;
-  for (int a = 0; a < d; ++a) {
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
     const T VtM = um[a] - VnM * n[a];
-    const T gt = gI[a] - gIn * n[a];
-    const T VtG = VtM * fM - Kc * gt * fK;
+    T VtG = VtM * fM;
+    if constexpr (CAP) VtG -= Kc * (gI[a] - gIn * n[a]) * fK;
     UG[(int64_t)a * G + g] = VnG * n[a] + VtG;
   }
 }
 
-template <typename T>
+template <typename T, int D, bool CAP>
 __global__ __launch_bounds__(kThreads) void k_vel_ghosts(
     const T *__restrict__ C, const T *__restrict__ F0, const T *__restrict__ F1, const T *__restrict__ F2,
     const int *__restrict__ gidx, const T *__restrict__ nrm, const T *__restrict__ dn, const T *__restrict__ gam,
     const int *__restrict__ ap, const T *__restrict__ w, const T *__restrict__ CMs, T *__restrict__ UG, int64_t G,
     int K, const int *__restrict__ f_cell, const int *__restrict__ f_axis, const int *__restrict__ f_gL,
-    const int *__restrict__ f_gR, T *__restrict__ stashL, T *__restrict__ stashR, int64_t NF, Dims dm, int d,
-    T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls, int capillary, unsigned nbg) {
-  vel_ghosts_body<T>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR, stashL, stashR, NF, dm, d, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, capillary, nbg, blockIdx.x);
+    const int *__restrict__ f_gR, T *__restrict__ stashL, T *__restrict__ stashR, int64_t NF, Dims dm,
+    T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls, unsigned nbg) {
+  vel_ghosts_body<T, D, CAP>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
+                             stashL, stashR, NF, dm, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, nbg, blockIdx.x);
 }
 
 // K6 + K7a in one launch for the static condition, where the velocity fill does not read C:
 // blocks [0, nbc) fill the C ghosts, the others compute the ghost velocities and face stashes.
-template <typename T>
+template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void k_fill_static_vel(
     T *__restrict__ C, const int *__restrict__ gidx, const T *__restrict__ dn, const T *__restrict__ gam,
     const int *__restrict__ ap, const T *__restrict__ w, T *__restrict__ CGn, T *__restrict__ CGnm1,
     T *__restrict__ CMs, int64_t G, int K, T cb, const T *__restrict__ F0, const T *__restrict__ F1,
     const T *__restrict__ F2, const T *__restrict__ nrm, T *__restrict__ UG, const int *__restrict__ f_cell,
     const int *__restrict__ f_axis, const int *__restrict__ f_gL, const int *__restrict__ f_gR, T *__restrict__ stashL,
-    T *__restrict__ stashR, int64_t NF, Dims dm, int d, T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls,
+    T *__restrict__ stashR, int64_t NF, Dims dm, T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls,
     unsigned nbc, unsigned nbg) {
   if (blockIdx.x < nbc) {
     fill_static_body<T>(C, gidx, dn, gam, ap, w, CGn, CGnm1, CMs, G, K, cb, 0, blockIdx.x);
     return;
   }
-  vel_ghosts_body<T>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR, stashL,
-                     stashR, NF, dm, d, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, 0, nbg, blockIdx.x - nbc);
+  vel_ghosts_body<T, D, false>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
+                               stashL, stashR, NF, dm, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, nbg, blockIdx.x - nbc);
 }
 
 // K7b: every face touching a ghost becomes the mean of its two cell-centred values.
@@ -2037,77 +2058,164 @@ __global__ __launch_bounds__(kThreads) void k_phi_zm(const T *__restrict__ C, T 
   }
 }
 
+// The explicit step with phi formed on the way (3D, nx % 64 == 0, ny % 8 == 0), marching in z over a
+// 64 x 8 tile: bound by memory, 56 bytes per cell against 80 with phi as a field of its own.  C of a plane
+// goes to LDS with a two-cell x/y halo; plane z+1 of phi is formed from it for the tile and its one-cell
+// ring (the threads that bring a ring cell keep that column too) and goes to LDS in turn; plane z is
+// advanced from phi and C in LDS and the z neighbours in registers.  Four slots of C and three of phi
+// leave one barrier per plane: a slot is rewritten two barriers after its last read.  phi is the raw
+// C^3 - C - Cn^2 lap C everywhere; the mirror value at the ghosts enters through the sparse patch
+// (k_patch_apply).  256^3 FP64: phi 62, its ghosts 7 and update 217 us before, 198 us with the patch here.
+constexpr int kXx = 64, kXy = 8, kXThreads = kXx * kXy;
+constexpr int kXcp = kXx + 4, kXpp = kXx + 2;                  // row pitch of C and of phi
+constexpr int kXcPlane = kXcp * (kXy + 4), kXpPlane = kXpp * (kXy + 2);
+constexpr int kXRing1 = kXpPlane - kXThreads;                  // cells around the tile where phi is formed
+constexpr int kXHalo = kXcPlane - kXThreads;                   // cells around the tile whose C is held
+static_assert(kXHalo <= kXThreads, "one halo cell per thread");
+
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_explicit_zm(const T *__restrict__ C, const T *__restrict__ phi,
-                                                          const T *__restrict__ F0, const T *__restrict__ F1,
-                                                          const T *__restrict__ F2, T *__restrict__ R,
-                                                          T *__restrict__ Cnext, Dims dm, T half_inv_h, T inv_h2,
-                                                          T inv_pe, T dt, int first, int zc_log) {
-  __shared__ T sc[2][kZmTy + 2][kZmTx + 2], sp[2][kZmTy + 2][kZmTx + 2];
-  const int nx = dm.nx, ny = dm.ny;
-  const int nbx = nx / kZmTx, nby = ny / kZmTy;
-  const int t = blockIdx.x;
-  const int bx = t % nbx, by = (t / nbx) % nby, bz = t / (nbx * nby);
-  const int tx = threadIdx.x & (kZmTx - 1), ty = threadIdx.x / kZmTx;
-  const int x = bx * kZmTx + tx, y = by * kZmTy + ty;
-  const int z0 = bz << zc_log;
-  const int64_t col = x + (int64_t)nx * y;
-  const int64_t colxm = ((x - 1) & (nx - 1)) + (int64_t)nx * y;
-  const int64_t colym = x + (int64_t)nx * ((y - 1) & (ny - 1));
-  auto zb = [&](int z) { return (int64_t)(z < 0 ? 0 : (z >= dm.nz ? dm.nz - 1 : z)) * dm.plane; };
-  T cm = C[zb(z0 - 1) + col], c0 = C[zb(z0) + col];
-  T pm = phi[zb(z0 - 1) + col], p0 = phi[zb(z0) + col];
-  T f2m = F2[zb(z0 - 1) + col];   // the face below plane z0 (unused at the bottom wall)
-  for (int zg = 0; zg < (1 << zc_log); zg += kZmU) {
-    const int zs = z0 + zg;
-    T cz[kZmU], pz[kZmU], hcx[kZmU], hcy[kZmU], hpx[kZmU], hpy[kZmU];
-    T f0z[kZmU], f0mz[kZmU], f1z[kZmU], f1mz[kZmU], f2z[kZmU], rz[kZmU];
-#pragma unroll
-    for (int u = 0; u < kZmU; ++u) {
-      const int64_t b = zb(zs + u), b1 = zb(zs + u + 1);
-      cz[u] = C[b1 + col];
-      pz[u] = phi[b1 + col];
-      f0z[u] = F0[b + col];
-      f0mz[u] = F0[b + colxm];
-      f1z[u] = F1[b + col];
-      f1mz[u] = F1[b + colym];
-      f2z[u] = F2[b + col];
-      rz[u] = R[b + col];
-      hcx[u] = zm_halo(C, b, x, y, tx, ty, dm);
-      hcy[u] = zm_halo_y(C, b, x, y, ty, dm);
-      hpx[u] = zm_halo(phi, b, x, y, tx, ty, dm);
-      hpy[u] = zm_halo_y(phi, b, x, y, ty, dm);
-    }
-#pragma unroll
-    for (int u = 0; u < kZmU; ++u) {
-      const int z = zs + u;
-      const int64_t c = zb(z) + col;
-      const T cp = cz[u], pp = pz[u];
-      const T f0 = f0z[u], f0m = f0mz[u], f1 = f1z[u], f1m = f1mz[u], f2 = f2z[u];
-      const T rprev = rz[u];
-      T (*sbc)[kZmTx + 2] = sc[u & 1];
-      T (*sbp)[kZmTx + 2] = sp[u & 1];
-      zm_tile_store(sbc, tx, ty, c0, hcx[u], hcy[u]);
-      zm_tile_store(sbp, tx, ty, p0, hpx[u], hpy[u]);
-      __syncthreads();   // these slots were last read two planes ago, before the previous barrier
-      const bool top = z == dm.nz - 1, bot = z == 0;
-      T flux = f0 * (c0 + sbc[ty + 1][tx + 2]) - f0m * (sbc[ty + 1][tx] + c0);
-      T lsum = sbp[ty + 1][tx + 2] + sbp[ty + 1][tx];
-      flux += f1 * (c0 + sbc[ty + 2][tx + 1]) - f1m * (sbc[ty][tx + 1] + c0);
-      lsum += sbp[ty + 2][tx + 1] + sbp[ty][tx + 1];
-      flux += (top ? T(0) : f2 * (c0 + cp)) - (bot ? T(0) : f2m * (cm + c0));
-      lsum += (top ? p0 : pp) + (bot ? p0 : pm);
-      const T r = -flux * half_inv_h + inv_pe * (lsum - T(6) * p0) * inv_h2;
-      const T rp = first ? r : rprev;
-      R[c] = r;
-      Cnext[c] = c0 + dt * (T(1.5) * r - T(0.5) * rp);
-      cm = c0;
-      c0 = cp;
-      pm = p0;
-      p0 = pp;
-      f2m = f2;
-    }
+__global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__ C, const T *__restrict__ F0,
+                                                           const T *__restrict__ F1, const T *__restrict__ F2,
+                                                           T *__restrict__ R, T *__restrict__ Cnext, Dims dm, T cn2,
+                                                           T half_inv_h, T inv_h2, T inv_pe, T dt, int first, int zc) {
+  __shared__ T sc[4][kXcPlane];
+  __shared__ T sp[3][kXpPlane];
+  const int nx = dm.nx, ny = dm.ny, nz = dm.nz;
+  const int nbx = nx / kXx, nby = ny / kXy;
+  const int b = blockIdx.x;
+  const int x0 = (b % nbx) * kXx, y0 = ((b / nbx) % nby) * kXy, z0 = b / (nbx * nby) * zc;
+  const int tid = threadIdx.x, tx = tid & (kXx - 1), ty = tid / kXx;
+  const int col = x0 + tx + ((y0 + ty) << dm.lnx);
+  const int ic = (ty + 2) * kXcp + tx + 2, ip = (ty + 1) * kXpp + tx + 1;
+  // the halo cell of this thread: first the ring of phi (row below, row above, columns), then the outer ring
+  int hr, hc;                                                  // row and column within the C plane
+  if (tid < kXRing1) {
+    const int e = tid - 2 * kXpp;
+    hr = tid < kXpp ? 1 : (e < 0 ? kXy + 2 : 2 + (e >> 1));
+    hc = e < 0 ? 1 + (tid < kXpp ? tid : tid - kXpp) : ((e & 1) ? kXx + 2 : 1);
+  } else {
+    const int t = tid - kXRing1, e = t - 2 * kXcp;
+    hr = t < kXcp ? 0 : (e < 0 ? kXy + 3 : 1 + (e >> 1));
+    hc = e < 0 ? (t < kXcp ? t : t - kXcp) : ((e & 1) ? kXx + 3 : 0);
   }
+  const bool halo = tid < kXHalo, ring = tid < kXRing1;
+  const int hcol = halo ? ((x0 - 2 + hc) & (nx - 1)) + (((y0 - 2 + hr) & (ny - 1)) << dm.lnx) : col;
+  const int hic = hr * kXcp + hc, hip = (hr - 1) * kXpp + hc - 1;
+  const int colym = x0 + tx + (((y0 + ty - 1) & (ny - 1)) << dm.lnx);
+  const int colxm = ((x0 - 1) & (nx - 1)) + ((y0 + ty) << dm.lnx);   // (the first lane of each row asks for it)
+  // planes beyond the walls reflect onto the boundary plane
+  auto zb = [&](int z) { return (int64_t)(z < 0 ? 0 : (z >= nz ? nz - 1 : z)) * dm.plane; };
+  T cn, hn = T(0);                                             // the plane of C in flight
+  auto request_c = [&](int z) {
+    cn = C[zb(z) + col];
+    if (halo) hn = C[zb(z) + hcol];
+  };
+  T f0, f0l, f1, f1m, f2, rz;                                  // faces and rate of the plane to advance
+  auto request_f = [&](int z) {
+    const int64_t c = zb(z);
+    f0 = F0[c + col];
+    if (tx == 0) f0l = F0[c + colxm];
+    f1 = F1[c + col];
+    f1m = F1[c + colym];
+    f2 = F2[c + col];
+    rz = R[c + col];
+  };
+  auto phi_of = [&](const T *p, int i, T cm, T c0, T cp) {
+    const T sum = ((p[i + 1] + p[i - 1]) + (p[i + kXcp] + p[i - kXcp])) + (cp + cm);
+    return c0 * c0 * c0 - c0 - cn2 * ((sum - T(6) * c0) * inv_h2);
+  };
+  // own column (c*) and ring column (h*): planes z, z+1, z+2
+  T c0, c1, h0, h1;
+  request_c(z0 - 2);
+  c0 = cn;
+  h0 = hn;
+  request_c(z0 - 1);
+  c1 = cn;
+  h1 = hn;
+  sc[(z0 + 3) & 3][ic] = c1;
+  if (halo) sc[(z0 + 3) & 3][hic] = h1;
+  request_c(z0);
+  T pm = T(0), p0 = T(0);
+  T f2m = z0 > 0 ? F2[zb(z0 - 1) + col] : T(0);
+  int s1 = 2;                                                  // slot of phi plane z+1
+  __syncthreads();
+  for (int z = z0 - 2; z < z0 + zc; ++z) {
+    // plane z+2 of C arrives; phi of plane z+1
+    const T c2 = cn, h2 = hn;
+    T *cs = sc[(z + 6) & 3];
+    cs[ic] = c2;
+    if (halo) cs[hic] = h2;
+    const T *cc = sc[(z + 5) & 3];
+    const T p1 = phi_of(cc, ic, c0, c1, c2);
+    sp[s1][ip] = p1;
+    if (ring) sp[s1][hip] = phi_of(cc, hic, h0, h1, h2);
+    if (z + 1 < z0 + zc) request_c(z + 3);
+    if (z == z0 - 1) request_f(z0);
+    __syncthreads();
+    if (z >= z0) {
+      const T *pc = sc[(z + 4) & 3], *pp = sp[s1 >= 1 ? s1 - 1 : 2];
+      const bool top = z == nz - 1, bot = z == 0;
+      const T up = __shfl_up(f0, 1);
+      const T f0m = tx == 0 ? f0l : up;
+      T flux = f0 * (c0 + pc[ic + 1]) - f0m * (pc[ic - 1] + c0);
+      flux += f1 * (c0 + pc[ic + kXcp]) - f1m * (pc[ic - kXcp] + c0);
+      T lsum = (pp[ip + 1] + pp[ip - 1]) + (pp[ip + kXpp] + pp[ip - kXpp]);
+      lsum += (top ? p0 : p1) + (bot ? p0 : pm);
+      // the face below reads 0 on the bottom wall, the one above on the top wall
+      const T fz = top ? T(0) : f2 * (c0 + c1);
+      flux += fz - f2m;
+      const T r = -flux * half_inv_h + inv_pe * (lsum - T(6) * p0) * inv_h2;
+      const T rp = first ? r : rz;
+      const int64_t c = zb(z) + col;
+      __builtin_nontemporal_store(r, R + c);
+      Cnext[c] = c0 + dt * (T(1.5) * r - T(0.5) * rp);
+      f2m = fz;
+      if (z + 1 < z0 + zc) request_f(z + 1);
+    } else if (z == z0 - 1) {
+      f2m = f2m * (c0 + c1);                                   // the z flux below plane z0
+    }
+    pm = p0;
+    p0 = p1;
+    c0 = c1;
+    c1 = c2;
+    h0 = h1;
+    h1 = h2;
+    s1 = s1 < 2 ? s1 + 1 : 0;
+  }
+}
+
+// The mirror value of phi at the ghosts in the explicit step, as the change it makes: with
+// dg_G = phi_M - phi_G, the rate gains dq/Pe and C^(n+1) its share of it (dq as in k_patch_dq).
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_patch_apply(const int *__restrict__ cell, const int *__restrict__ ref,
+                                                          const T *__restrict__ dg, T *__restrict__ R,
+                                                          T *__restrict__ Cnext, int64_t np, int nref, T twod, T inv_h2,
+                                                          T inv_pe, T cdt) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= np) return;
+  const int c = cell[e], own = ref[e];
+  T acc = T(0);
+  for (int j = 1; j < nref; ++j) {
+    const int id = ref[(int64_t)j * np + e];
+    if (id >= 0) acc += dg[id];
+  }
+  if (own >= 0) acc -= twod * dg[own];
+  const T r = acc * inv_h2 * inv_pe;
+  R[c] += r;
+  Cnext[c] += cdt * r;
+}
+
+// From a million cells on: below, the three launches of the patch cost more than phi's pass through the
+// caches (128x64x128 FP64 36.7 -> 32.7 us a step, 64x64x128 26.2 -> 28.0, 64^3 21.8 -> 26.4).
+inline bool explicit_zm_ok(const Plan &p) {
+  return p.d == 3 && p.n[0] % kXx == 0 && p.n[1] % kXy == 0 && p.N >= (int64_t(1) << 20);
+}
+// planes per workgroup: 16 (each chunk reads four more of C; 256^3 FP64 206 us, 210 with 32), fewer where
+// that leaves under 512 workgroups
+inline int explicit_zm_planes(const Plan &p) {
+  int zc = p.n[2] < 16 ? p.n[2] : 16;
+  while (zc > 4 && p.N / ((int64_t)kXThreads * zc) < 512) zc >>= 1;
+  return zc;
 }
 
 inline bool stencil_zm_ok(const Plan &p) {
@@ -2400,9 +2508,11 @@ hipError_t launch_dphi(const Plan &p, const T *Cn, const T *Cp) {
 }
 
 // dg of every ghost from C^n, C^(n-1) (before the rhs pass of a semi-implicit step); need_dq: then dq
-// of every patched cell; dphi_done: launch_dphi's kernel ran at the end of the step before.
+// of every patched cell; dphi_done: launch_dphi's kernel ran at the end of the step before.  3D explicit
+// steps take C^n twice (then C~ = C^n) and dg without the factor 1/Cn^2.
 template <typename T>
-hipError_t launch_ghost_patch(const Plan &p, const T *Cn, const T *Cp, bool need_dq, bool dphi_done = false) {
+hipError_t launch_ghost_patch(const Plan &p, const T *Cn, const T *Cp, bool need_dq, bool dphi_done = false,
+                              bool phi_units = false) {
   if (!has_patch(p)) return hipSuccess;
   if (!dphi_done) {
     hipError_t e = launch_dphi<T>(p, Cn, Cp);
@@ -2410,7 +2520,8 @@ hipError_t launch_ghost_patch(const Plan &p, const T *Cn, const T *Cp, bool need
   }
   if (dphi_points(p))
     hipLaunchKernelGGL((k_ghost_dg<T>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream,
-                       (const T *)p.pt_phi, p.pt_idx, (const T *)p.wg, (T *)p.dg, p.G, p.K, (T)(1.0 / (p.Cn * p.Cn)));
+                       (const T *)p.pt_phi, p.pt_idx, (const T *)p.wg, (T *)p.dg, p.G, p.K,
+                       phi_units ? T(1) : (T)(1.0 / (p.Cn * p.Cn)));
   if (need_dq)
     hipLaunchKernelGGL((k_patch_dq<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, p.pl_ref,
                        (const T *)p.dg, (T *)p.pl_dq, p.NP, 2 * p.d + 1, (T)(2 * p.d), (T)(1.0 / (p.h * p.h)));
@@ -2720,10 +2831,15 @@ hipError_t launch_ghost_fill(const Plan &p, T *Cout, int init) {
     if (!init)
       hipLaunchKernelGGL((k_scatter_pg<T>), dim3(nb), dim3(kThreads), 0, p.stream, Cout, p.gidx,
                          (const T *)p.CGn, (const T *)p.CGnm1, p.G);
-    hipLaunchKernelGGL((k_fill_dynamic<T>), dim3(nb), dim3(kThreads), 0, p.stream, (const T *)Cout,
-                       (const T *)p.F[0], (const T *)p.F[1], (const T *)p.F[2], p.gidx, (const T *)p.normal,
-                       (const T *)p.dn, (const T *)p.gamma, p.ap, (const T *)p.w, (T *)p.CI, (T *)p.CGnew,
-                       (T *)p.CMs, p.G, p.K, dm, p.d, (T)(0.5 / p.h), (T)p.Cn, (T)p.Vs, (T)p.cos_t, (T)p.dt, init);
+#define CHIB_FILL_DYNAMIC(D)                                                                                         \
+  hipLaunchKernelGGL((k_fill_dynamic<T, D>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream,                \
+                     (const T *)Cout, (const T *)p.F[0], (const T *)p.F[1], (const T *)p.F[D - 1], p.gidx,           \
+                     (const T *)p.normal, (const T *)p.dn, (const T *)p.gamma, p.apg, (const T *)p.wg, (T *)p.CI,    \
+                     (T *)p.CGnew, (T *)p.CMs, p.G, p.K, dm, (T)(0.5 / p.h), (T)p.Cn, (T)p.Vs, (T)p.cos_t, (T)p.dt,  \
+                     init)
+    if (p.d == 2) CHIB_FILL_DYNAMIC(2);
+    else CHIB_FILL_DYNAMIC(3);
+#undef CHIB_FILL_DYNAMIC
     hipLaunchKernelGGL((k_commit_ghosts<T>), dim3(nb), dim3(kThreads), 0, p.stream, Cout, p.gidx,
                        (const T *)p.CGnew, (T *)p.CGn, (T *)p.CGnm1, p.G, init);
   }
@@ -2763,12 +2879,16 @@ hipError_t launch_static_fills(const Plan &p, T *Cout, const NextStep *next) {
   const Dims dm = make_dims(p);
   const unsigned nbc = blocks_for(p.G * 16), nbg = blocks_for(p.G * 16);
   const T cb = (T)(p.cos_t / (1.4142135623730951 * p.Cn));
-  hipLaunchKernelGGL((k_fill_static_vel<T>), dim3(nbc + nbg + blocks_for(p.NF)), dim3(kThreads), 0, p.stream, Cout,
-                     p.gidx, (const T *)p.dn, (const T *)p.gamma, p.apg, (const T *)p.wg, (T *)p.CGn, (T *)p.CGnm1,
-                     (T *)p.CMs, p.G, p.K, cb, (const T *)p.F[0], (const T *)p.F[1], (const T *)p.F[2],
-                     (const T *)p.normal, (T *)p.UG, p.f_cell, p.f_axis, p.f_gL, p.f_gR, (T *)p.stashL,
-                     (T *)p.stashR, p.NF, dm, p.d, (T)(0.5 / p.h), (T)p.Cn, (T)p.cos_t, (T)(1.0 / p.Ca),
-                     (T)(1.0 / p.mu), (T)p.ls, nbc, nbg);
+#define CHIB_FILL_STATIC_VEL(D)                                                                                     \
+  hipLaunchKernelGGL((k_fill_static_vel<T, D>), dim3(nbc + nbg + blocks_for(p.NF)), dim3(kThreads), 0, p.stream,    \
+                     Cout, p.gidx, (const T *)p.dn, (const T *)p.gamma, p.apg, (const T *)p.wg, (T *)p.CGn,         \
+                     (T *)p.CGnm1, (T *)p.CMs, p.G, p.K, cb, (const T *)p.F[0], (const T *)p.F[1],                  \
+                     (const T *)p.F[D - 1], (const T *)p.normal, (T *)p.UG, p.f_cell, p.f_axis, p.f_gL, p.f_gR,     \
+                     (T *)p.stashL, (T *)p.stashR, p.NF, dm, (T)(0.5 / p.h), (T)p.Cn, (T)p.cos_t, (T)(1.0 / p.Ca),  \
+                     (T)(1.0 / p.mu), (T)p.ls, nbc, nbg)
+  if (p.d == 2) CHIB_FILL_STATIC_VEL(2);
+  else CHIB_FILL_STATIC_VEL(3);
+#undef CHIB_FILL_STATIC_VEL
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? launch_velocity_faces<T>(p, next) : e;
 }
@@ -2778,12 +2898,17 @@ hipError_t launch_velocity_fill(const Plan &p, const T *Cfin, const NextStep *ne
   if (!p.vel_fill || p.G == 0) return hipSuccess;
   const Dims dm = make_dims(p);
   const unsigned nbg = blocks_for(p.G * 16);
-  hipLaunchKernelGGL((k_vel_ghosts<T>), dim3(nbg + blocks_for(p.NF)), dim3(kThreads), 0, p.stream, Cfin,
-                     (const T *)p.F[0], (const T *)p.F[1], (const T *)p.F[2], p.gidx, (const T *)p.normal,
-                     (const T *)p.dn, (const T *)p.gamma, p.apg, (const T *)p.wg, (const T *)p.CMs, (T *)p.UG, p.G,
-                     p.K, p.f_cell, p.f_axis, p.f_gL, p.f_gR, (T *)p.stashL, (T *)p.stashR, p.NF, dm, p.d,
-                     (T)(0.5 / p.h), (T)p.Cn, (T)p.cos_t, (T)(1.0 / p.Ca), (T)(1.0 / p.mu), (T)p.ls,
-                     p.dynamic ? 1 : 0, nbg);
+#define CHIB_VEL_GHOSTS(D, CAP)                                                                                     \
+  hipLaunchKernelGGL((k_vel_ghosts<T, D, CAP>), dim3(nbg + blocks_for(p.NF)), dim3(kThreads), 0, p.stream, Cfin,    \
+                     (const T *)p.F[0], (const T *)p.F[1], (const T *)p.F[D - 1], p.gidx, (const T *)p.normal,      \
+                     (const T *)p.dn, (const T *)p.gamma, p.apg, (const T *)p.wg, (const T *)p.CMs, (T *)p.UG, p.G, \
+                     p.K, p.f_cell, p.f_axis, p.f_gL, p.f_gR, (T *)p.stashL, (T *)p.stashR, p.NF, dm,               \
+                     (T)(0.5 / p.h), (T)p.Cn, (T)p.cos_t, (T)(1.0 / p.Ca), (T)(1.0 / p.mu), (T)p.ls, nbg)
+  if (p.d == 2 && p.dynamic) CHIB_VEL_GHOSTS(2, true);
+  else if (p.d == 2) CHIB_VEL_GHOSTS(2, false);
+  else if (p.dynamic) CHIB_VEL_GHOSTS(3, true);
+  else CHIB_VEL_GHOSTS(3, false);
+#undef CHIB_VEL_GHOSTS
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? launch_velocity_faces<T>(p, next) : e;
 }
@@ -3126,7 +3251,7 @@ template hipError_t enqueue_poisson<float>(const Plan &, void *const *, double);
 template hipError_t enqueue_velocity_fill<double>(const Plan &, const void *, const NextStep *);
 template hipError_t enqueue_velocity_fill<float>(const Plan &, const void *, const NextStep *);
 template <typename T>
-hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer *tm) {
+hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer *tm, StepLink *link) {
   if (!p.R) return hipErrorInvalidValue;
   const T *Cn = (const T *)p.C[cur];
   T *Cnext = (T *)p.C[1 - cur];
@@ -3134,27 +3259,50 @@ hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer 
   auto mark = [&](const char *name) {
     if (tm && e == hipSuccess) e = tm->mark(name, p.stream);
   };
+  const Dims dm = make_dims(p);
+  const T hih = (T)(0.5 / p.h), ih2 = (T)(1.0 / (p.h * p.h)), ipe = (T)(1.0 / p.Pe), dt = (T)p.dt;
+  const T cn2 = (T)(p.Cn * p.Cn);
+  const bool patch = p.G == 0 || (has_patch(p) && dphi_points(p));
+  if (explicit_zm_ok(p) && patch) {
+    if (p.G) {
+      mark("ghost_dphi");
+      if (e == hipSuccess) e = launch_ghost_patch<T>(p, Cn, Cn, false, link && link->dphi_done, true);
+    }
+    mark("explicit_update");
+    if (e == hipSuccess) {
+      const int zc = explicit_zm_planes(p);
+      const unsigned nb = (unsigned)((p.n[0] / kXx) * (p.n[1] / kXy) * (p.n[2] / zc));
+      hipLaunchKernelGGL((k_explicit_zm<T>), dim3(nb), dim3(kXThreads), 0, p.stream, Cn, (const T *)p.F[0],
+                         (const T *)p.F[1], (const T *)p.F[2], (T *)p.R, Cnext, dm, cn2, hih, ih2, ipe, dt, first, zc);
+      if (p.G)
+        hipLaunchKernelGGL((k_patch_apply<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, p.pl_cell,
+                           p.pl_ref, (const T *)p.dg, (T *)p.R, Cnext, p.NP, 2 * p.d + 1, (T)(2 * p.d), ih2, ipe,
+                           first ? dt : T(1.5) * dt);
+      e = hipGetLastError();
+    }
+    const NextStep nx{Cnext, Cnext};
+    const bool join = link && link->next && p.vel_fill && p.NF && p.G;
+    if (e == hipSuccess) e = launch_step_fills<T>(p, Cnext, tm, join ? &nx : nullptr);
+    if (link) link->dphi_done = join && e == hipSuccess;
+    if (tm && e == hipSuccess) e = tm->end(p.stream);
+    return e;
+  }
   mark("phi");
   if (e == hipSuccess) e = enqueue_phi<T>(p, cur, p.W);
   mark("explicit_update");
   if (e == hipSuccess) {
-    const Dims dm = make_dims(p);
-    const T hih = (T)(0.5 / p.h), ih2 = (T)(1.0 / (p.h * p.h)), ipe = (T)(1.0 / p.Pe), dt = (T)p.dt;
     const T *F2 = (const T *)(p.d == 3 ? p.F[2] : p.F[1]);
     if (p.d == 2)
       hipLaunchKernelGGL((k_explicit<T, 2>), dim3(blocks_for(p.N)), dim3(kThreads), 0, p.stream, Cn,
                          (const T *)p.W, (const T *)p.F[0], (const T *)p.F[1], F2, (T *)p.R, Cnext, dm, hih, ih2,
                          ipe, dt, first, p.N);
-    else if (stencil_zm_ok(p))
-      hipLaunchKernelGGL((k_explicit_zm<T>), dim3(stencil_zm_blocks(p)), dim3(kThreads), 0, p.stream, Cn,
-                         (const T *)p.W, (const T *)p.F[0], (const T *)p.F[1], F2, (T *)p.R, Cnext, dm, hih, ih2,
-                         ipe, dt, first, stencil_zm_log(p));
     else
       hipLaunchKernelGGL((k_explicit<T, 3>), dim3(blocks_for(p.N)), dim3(kThreads), 0, p.stream, Cn,
                          (const T *)p.W, (const T *)p.F[0], (const T *)p.F[1], F2, (T *)p.R, Cnext, dm, hih, ih2,
                          ipe, dt, first, p.N);
     e = hipGetLastError();
   }
+  if (link) link->dphi_done = false;
   if (e == hipSuccess) e = launch_step_fills<T>(p, Cnext, tm, nullptr);
   if (tm && e == hipSuccess) e = tm->end(p.stream);
   return e;
@@ -3171,8 +3319,8 @@ hipError_t enqueue_scalar_fill(const Plan &p, void *f, double a, double b, doubl
 
 template hipError_t enqueue_scalar_fill<double>(const Plan &, void *, double, double, double, const void *);
 template hipError_t enqueue_scalar_fill<float>(const Plan &, void *, double, double, double, const void *);
-template hipError_t enqueue_explicit_step<double>(const Plan &, int, int, KernelTimer *);
-template hipError_t enqueue_explicit_step<float>(const Plan &, int, int, KernelTimer *);
+template hipError_t enqueue_explicit_step<double>(const Plan &, int, int, KernelTimer *, StepLink *);
+template hipError_t enqueue_explicit_step<float>(const Plan &, int, int, KernelTimer *, StepLink *);
 template hipError_t enqueue_phi<double>(const Plan &, int, void *);
 template hipError_t enqueue_phi<float>(const Plan &, int, void *);
 template hipError_t enqueue_diag<double>(const Plan &, int);
@@ -3293,9 +3441,9 @@ __global__ __launch_bounds__(kThreads) void kb_fill(const CaseDesc<T> *__restric
     fill_static_body<T>(d.C[1 - parity], d.gidx, d.dn, d.gam, d.ap, d.w, d.CGn, d.CGnm1, d.CMs, d.G, d.K, d.cb, 0, t);
     return;
   }
-  vel_ghosts_body<T>(d.C[1 - parity], d.F0, d.F1, d.F1, d.gidx, d.normal, d.dn, d.gam, d.ap, d.w, d.CMs, d.UG, d.G,
-                     d.K, d.f_cell, d.f_axis, d.f_gL, d.f_gR, d.stashL, d.stashR, d.NF, d.dm, 2, d.inv2h, d.Cn,
-                     d.cos_t, d.inv_Ca, d.inv_mu, d.ls, 0, d.nbg, t - nbc);
+  vel_ghosts_body<T, 2, false>(d.C[1 - parity], d.F0, d.F1, d.F1, d.gidx, d.normal, d.dn, d.gam, d.ap, d.w, d.CMs,
+                               d.UG, d.G, d.K, d.f_cell, d.f_axis, d.f_gL, d.f_gR, d.stashL, d.stashR, d.NF, d.dm,
+                               d.inv2h, d.Cn, d.cos_t, d.inv_Ca, d.inv_mu, d.ls, d.nbg, t - nbc);
 }
 
 template <typename T>

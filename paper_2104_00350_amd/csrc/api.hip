@@ -261,6 +261,7 @@ struct ch_ib_state {
   int r_valid = 0;      // explicit step: R holds the previous step's rate
   int ns_first = 1;     // momentum step: no previous convective term yet
   int ut_valid = 0;     // momentum step: Ut holds 2u^n - u^(n-1)
+  int auto_shapes = 1;  // launch shapes still those of default_shapes (neither set nor tuned)
   double d1_min = 0, d1_max = 0;   // range of gamma dn = d1 over the ghosts (mixed-condition checks)
 };
 
@@ -438,6 +439,8 @@ extern "C" int ch_ib_state_create(const ch_ib_grid *grid, const ch_ib_geometry *
   p.red_out = W0 + o.red_out;
   p.nred = (int)std::min<int64_t>(kNred, (p.N + 255) / 256);
   p.stream = (hipStream_t)hip_stream;
+  if (st->es == 8) chib::default_shapes<double>(p);
+  else chib::default_shapes<float>(p);
 
   // host-side tables in double, converted to the element type on upload
   const int64_t G = geom->n_ghost;
@@ -822,6 +825,7 @@ extern "C" int ch_ib_set_shapes(ch_ib_state *st, const int *in) {
         in[3 * k + 2] > (k == 0 ? 8 : 2))
       return fail(CH_IB_EINVAL, "shape out of range");
   for (int k = 0; k < 4; ++k) st->plan.shape[k] = {in[3 * k], in[3 * k + 1], in[3 * k + 2]};
+  st->auto_shapes = 0;
   return CH_IB_OK;
 }
 
@@ -835,6 +839,7 @@ extern "C" int ch_ib_tune(ch_ib_state *st, int reps, int *out) {
                              : chib::tune_shapes<float>(st->plan, st->cur, reps);
   if (e == hipSuccess) e = hipStreamSynchronize(st->plan.stream);
   if (e != hipSuccess) return hip_fail(st, e, "tune");
+  st->auto_shapes = 0;
   return out ? ch_ib_get_shapes(st, out) : CH_IB_OK;
 }
 
@@ -1239,6 +1244,14 @@ extern "C" int ch_ib_batch_create(ch_ib_state *const *states, int n, void *ws, s
   b->ws = (char *)ws;
   b->ws_bytes = bytes;
   b->stream = (hipStream_t)stream;
+  // members nobody has set or tuned shapes for take the tile heights that suit the batch as a whole
+  int64_t cells = 0;
+  for (const ch_ib_state *s : b->grp) cells += s->plan.N;
+  for (ch_ib_state *s : b->grp)
+    if (s->auto_shapes) {
+      if (es == 8) chib::batch_heights<double>(s->plan, cells);
+      else chib::batch_heights<float>(s->plan, cells);
+    }
   // shared kernel choices follow the first grouped member's shapes (so that a batched step is the
   // same computation as stepping each member with those shapes)
   const ch_ib_state *s0 = b->grp.empty() ? states[0] : b->grp[0];
@@ -1338,8 +1351,10 @@ extern "C" int ch_ib_batch_tune(ch_ib_batch *b, int reps, int *radix_out, int *u
     int rc = ch_ib_tune(s, reps, nullptr);
     if (rc) return rc;
     for (ch_ib_state *o : b->st)
-      if (o->plan.n[0] == key.first && o->plan.n[1] == key.second)
+      if (o->plan.n[0] == key.first && o->plan.n[1] == key.second) {
         for (int k = 0; k < 4; ++k) o->plan.shape[k] = s->plan.shape[k];
+        o->auto_shapes = 0;
+      }
   }
   // 2. the shared radix / cells in flight: time full batched steps of the grouped members (an even
   // number, so that every member's buffer roles end where they started; the fields advance, so

@@ -134,6 +134,8 @@ template <typename T>
 hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm = nullptr, StepLink *link = nullptr);
 template <typename T> hipError_t enqueue_initial_fill(const Plan &p, int cur);
 template <typename T> hipError_t tune_shapes(Plan &p, int cur, int reps);
+template <typename T> void default_shapes(Plan &p);                      // launch shapes by the grid's size
+template <typename T> void batch_heights(Plan &p, int64_t cells);        // tile heights inside a batch of that many cells
 // One explicit Adams-Bashforth step (first: no previous rate, forward Euler) from C[cur] into C[1-cur].
 template <typename T>
 hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer *tm = nullptr, StepLink *link = nullptr);

@@ -77,7 +77,7 @@ __device__ __forceinline__ T patch_dq(const int (&id)[2 * D + 1], const T *__res
     acc += id[j] < 0 ? T(0) : v;
   }
   const T own = dg[id[0] < 0 ? 0 : id[0]];
-  acc -= id[0] < 0 ? T(0) : T(2 * D) * own;
+  if (id[0] >= 0) acc -= T(2 * D) * own;
   return acc * inv_h2;
 }
 
@@ -108,7 +108,10 @@ struct TilePatch {
       const int l = (int)((c >> lnx) - line0);
       const int i = c & ((1 << lnx) - 1);
       const T dq = patch_dq<T, D>(id, rp.dg, rp.inv_h2);
-      s[l * pitch + i + (i >> 4)] += dq;
+      {
+#pragma clang fp contract(off)   // dq is rounded first, as the stored list's entries are
+        s[l * pitch + i + (i >> 4)] += dq;
+      }
     }
   }
 };
@@ -471,6 +474,23 @@ __host__ __device__ __forceinline__ int col_tile(int N, int B) { return N * B + 
 //   Q = (Pe/Cn^2)(C^/dt - div_h(u C~)) + lap_h((C~^3 - C~ - S C~)/Cn^2)
 // with C~ = 2C^n - C^(n-1), C^ = 2C^n - C^(n-1)/2; periodic axes wrap, the bounded (last)
 // axis reflects for the Laplacian and has zero normal velocity on its box walls.
+// The 2D expression on the values of C~ around the cell (v0, x+-1, y+-1, the latter already v0 beyond a
+// wall) and its faces: shared by the line-tiled and the y-marching kernel, which so give the same bits.
+template <typename T>
+__device__ __forceinline__ T rhs_2d(T v0, T cxp, T cxm, T cyp, T cym, T f0, T f0m, T f1, T f1m, bool top, bool bot,
+                                    T cn, T cp, const RhsCoef<T> &cf) {
+  auto gf = [&](T v) { return (v * v * v - v - cf.S * v) * cf.inv_cn2; };
+  T flux = f0 * (v0 + cxp) - f0m * (cxm + v0);
+  T gsum = gf(cxp) + gf(cxm);
+  const T ft = f1 * (v0 + cyp), fb = f1m * (cym + v0);
+  flux += (top ? T(0) : ft) - (bot ? T(0) : fb);
+  gsum += gf(cyp) + gf(cym);
+  const T A = flux * T(0.5) * cf.inv_h;
+  const T lap = (gsum - T(4) * gf(v0)) * cf.inv_h2;
+  const T cc = T(2) * cn - T(0.5) * cp;
+  return cf.pe_cn2 * (cc * cf.inv_dt - A) + lap;
+}
+
 template <typename T, int D>
 __device__ __forceinline__ T rhs_at(const T *__restrict__ Cn, const T *__restrict__ Cp, const T *__restrict__ F0,
                                     const T *__restrict__ F1, const T *__restrict__ F2, int i, int j, int k,
@@ -483,15 +503,15 @@ __device__ __forceinline__ T rhs_at(const T *__restrict__ Cn, const T *__restric
   const int ip = (i + 1) & (nx - 1), im = (i - 1) & (nx - 1);
   const T c0 = ct(c);
   const T cxp = ct(rowb + ip), cxm = ct(rowb + im);
+  if constexpr (D == 2) {   // (every load happens, from the cell itself beyond a wall)
+    const bool top = (j == dm.ny - 1), bot = (j == 0);
+    const int64_t cu = top ? c : c + nx, cd = bot ? c : c - nx;
+    const T cyp = ct(cu), cym = ct(cd);
+    return rhs_2d(c0, cxp, cxm, cyp, cym, F0[c], F0[rowb + im], F1[c], F1[cd], top, bot, Cn[c], Cp[c], cf);
+  }
   T flux = F0[c] * (c0 + cxp) - F0[rowb + im] * (cxm + c0);
   T gsum = gf(cxp) + gf(cxm);
-  if (D == 2) {
-    const bool top = (j == dm.ny - 1), bot = (j == 0);
-    const T cyp = top ? c0 : ct(c + nx);
-    const T cym = bot ? c0 : ct(c - nx);
-    flux += (top ? T(0) : F1[c] * (c0 + cyp)) - (bot ? T(0) : F1[c - nx] * (cym + c0));
-    gsum += gf(cyp) + gf(cym);
-  } else {
+  {
     const int jp = (j + 1) & (dm.ny - 1), jm = (j - 1) & (dm.ny - 1);
     const int64_t cyp_i = c + (int64_t)(jp - j) * nx, cym_i = c + (int64_t)(jm - j) * nx;
     const T cyp = ct(cyp_i), cym = ct(cym_i);
@@ -599,11 +619,10 @@ __host__ __device__ __forceinline__ int ym_extra(int nx) { return 2 * nx; }
 // K1 for 2D grids, marching in y: the workgroup owns the L rows of its tile across the whole x
 // range, thread t the columns x = t + 256 m (m < XM, nx <= 256 XM).  C~ = 2C^n - C^(n-1) of row
 // y-1 and the raw C^n, C^(n-1) of rows y and y+1 stay in registers, so every value is loaded
-// once and y neighbours never leave the thread (C~, C^ = 2C^n - C^(n-1)/2 and g(C~) =
-// C~^3 - (1 + S) C~ are formed from them as needed); the raw values of row y+2 are requested
+// once and y neighbours never leave the thread; the raw values of row y+2 are requested
 // while row y is computed.  x neighbours come from a two-row
 // ring of C~ in LDS (one barrier per row); each Q row goes straight into the line tile, which
-// then goes through the same x transform as the line-tiled K1.  1/Cn^2 scales the Laplacian.
+// then goes through the same x transform as the line-tiled K1.
 template <typename T, int XM, int R>
 __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__restrict__ Cn,
                                             const T *__restrict__ Cp, const T *__restrict__ F0,
@@ -618,9 +637,6 @@ __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__
   const int y0 = tile * L;
   const int tid = threadIdx.x;
   TilePatch<T, 2> patch(rp, y0, L);
-  const T s1 = T(1) + cf.S;
-  const T klap = cf.inv_h2 * cf.inv_cn2;
-  auto g = [&](T v) { return v * (v * v - s1); };
   auto rowp = [&](const T *__restrict__ a, int y) { return a + (int64_t)(y < 0 ? 0 : (y >= ny ? ny - 1 : y)) * nx; };
   // per column: C~ of row y-1, the raw C^n, C^(n-1) of rows y, y+1 and y+2 (in flight), F1 of row y-1
   T cm[XM], a0[XM], b0[XM], a1[XM], b1[XM], an[XM], bn[XM], f1m[XM];
@@ -663,14 +679,8 @@ __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__
         const T v0 = T(2) * a0[m] - b0[m];
         const T cxp = xb[(i + 1) & (nx - 1)], cxm = xb[(i - 1) & (nx - 1)];
         const T cyp = top ? v0 : T(2) * a1[m] - b1[m], cym = bot ? v0 : cm[m];
-        T flux = f0[m] * (v0 + cxp) - f0m[m] * (cxm + v0);
-        flux += (top ? T(0) : f1[m] * (v0 + cyp)) - (bot ? T(0) : f1m[m] * (cym + v0));
-        const T g0 = g(v0);
-        const T gsum = g(cxp) + g(cxm) + (top ? g0 : g(cyp)) + (bot ? g0 : g(cym));
-        const T A = flux * T(0.5) * cf.inv_h;
-        const T lap = (gsum - T(4) * g0) * klap;
-        const T h0 = T(2) * a0[m] - T(0.5) * b0[m];
-        fb[r * pitch + i + (i >> 4)] = cf.pe_cn2 * (h0 * cf.inv_dt - A) + lap;
+        fb[r * pitch + i + (i >> 4)] =
+            rhs_2d(v0, cxp, cxm, cyp, cym, f0[m], f0m[m], f1[m], f1m[m], top, bot, a0[m], b0[m], cf);
         // slide the window down one row and request the row after next
         cm[m] = v0;
         a0[m] = a1[m];
@@ -1492,7 +1502,9 @@ __global__ __launch_bounds__(kThreads) void k_scatter_pg(T *__restrict__ C, cons
 // C_I* = (gamma C^_G + C_M)/(gamma+1), dC/dn = (C_M - C^_G)/((1+gamma) dn); then
 // C_G = ((gamma+1) C_I - C_M)/gamma.  All reads from the provisional field (Jacobi).
 // Sixteen lanes per ghost: lane s < 2K one weighted averaging point, lane 2K the ghost itself (one thread
-// per ghost walked 2K (1 + 4d) gathers: 23.5 us for 1024 ghosts, 6 us now).
+// per ghost walked 2K (1 + 4d) gathers: 23.5 us for 1024 ghosts, 6 us now).  In 2D the lanes' values are added
+// in the order of the averaging points, so the sums keep their rounding: C_I integrates it, and the slip
+// velocity divides its gradient by Ca, which FP32 runs show in the third digit of single faces.
 template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void k_fill_dynamic(
     const T *__restrict__ C, const T *__restrict__ F0, const T *__restrict__ F1, const T *__restrict__ F2,
@@ -1508,33 +1520,51 @@ __global__ __launch_bounds__(kThreads) void k_fill_dynamic(
 #pragma unroll
   for (int a = 0; a < D; ++a) n[a] = nrm[(int64_t)a * G + gs];
   const T *Fs[3] = {F0, F1, F2};
-  // per lane: its share of C_M and of the mirror gradient and velocity; lane 2K the ghost's own
-  T cm = T(0), pg = T(0), gm[D], um[D], gg[D], ug[D];
+  // per lane: its averaging point's weight, value, gradient and velocity; lane 2K the ghost's own
+  const bool own = sl == 2 * K, used = g < G && sl <= 2 * K;
+  const int64_t i = (g < G ? g : 0) * kGhostSlots + sl;
+  const T wt = used && !own ? w[i] : T(0);
+  T f = T(0), gk[D], uk[D];
 #pragma unroll
-  for (int a = 0; a < D; ++a) gm[a] = um[a] = gg[a] = ug[a] = T(0);
-  if (g < G && sl <= 2 * K) {
-    const int64_t i = g * kGhostSlots + sl;
-    const bool own = sl == 2 * K;
+  for (int a = 0; a < D; ++a) gk[a] = uk[a] = T(0);
+  if (used) {
     const int c = own ? cg : ap[i];
-    const T cw = own ? T(1) : (sl < K ? T(2) : T(-1)) * w[i];
-    const T v = cw * C[c];
-    cm = own ? T(0) : v;
-    pg = own ? v : T(0);
+    f = C[c];
     if (!init) {
       const Nbr<D> nb(c, dm);
-      T gk[D];
       grad_at<D>(C, c, nb, inv2h, gk);
 #pragma unroll
-      for (int a = 0; a < D; ++a) {
-        const T u = cw * centred_u<D>(Fs[a], c, nb, a), gv = cw * gk[a];
-        gm[a] = own ? T(0) : gv;
-        gg[a] = own ? gv : T(0);
-        um[a] = own ? T(0) : u;
-        ug[a] = own ? u : T(0);
-      }
+      for (int a = 0; a < D; ++a) uk[a] = centred_u<D>(Fs[a], c, nb, a);
     }
   }
-  const T CM = group16_sum(cm), PG = group16_sum(pg);
+  const int base = (threadIdx.x & 63) & ~15;
+  auto own_of = [&](T v) { return __shfl(v, base + 2 * K); };
+  const T PG = own_of(f);
+  T CM, gM[D], uM[D];
+  if constexpr (D == 2) {
+    T o1 = T(0), o2 = T(0);
+    for (int k = 0; k < K; ++k) o1 += __shfl(wt, base + k) * __shfl(f, base + k);
+    for (int k = K; k < 2 * K; ++k) o2 += __shfl(wt, base + k) * __shfl(f, base + k);
+    CM = T(2) * o1 - o2;
+    gM[0] = gM[1] = uM[0] = uM[1] = T(0);
+    if (!init)
+      for (int k = 0; k < 2 * K; ++k) {
+        const T cw = (k < K ? T(2) : T(-1)) * __shfl(wt, base + k);
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+          gM[a] += cw * __shfl(gk[a], base + k);
+          uM[a] += cw * __shfl(uk[a], base + k);
+        }
+      }
+  } else {
+    const T cw = (sl < K ? T(2) : T(-1)) * wt;   // (0 on the ghost's own lane)
+    CM = group16_sum(cw * f);
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      gM[a] = init ? T(0) : group16_sum(cw * gk[a]);
+      uM[a] = init ? T(0) : group16_sum(cw * uk[a]);
+    }
+  }
   const T CIs = (ga * PG + CM) / (ga + T(1));
   if (init) {
     if (g < G && sl == 0) {
@@ -1547,8 +1577,8 @@ __global__ __launch_bounds__(kThreads) void k_fill_dynamic(
   T gI[D], uI[D], gn = T(0);
 #pragma unroll
   for (int a = 0; a < D; ++a) {
-    gI[a] = (ga * group16_sum(gg[a]) + group16_sum(gm[a])) / (ga + T(1));
-    uI[a] = (ga * group16_sum(ug[a]) + group16_sum(um[a])) / (ga + T(1));
+    gI[a] = (ga * own_of(gk[a]) + gM[a]) / (ga + T(1));
+    uI[a] = (ga * own_of(uk[a]) + uM[a]) / (ga + T(1));
     gn += gI[a] * n[a];
   }
   if (g >= G || sl != 0) return;
@@ -1700,7 +1730,9 @@ __global__ __launch_bounds__(kThreads) void k_rhs_patch(T *__restrict__ Q, const
 // ghost's own gradient); the remaining blocks take one face per thread.  With the static
 // condition (capillary = 0) the wall equation makes the bracket Kc of Eq. UpdateVtan zero,
 // and no gradient of C is gathered.
-template <typename T, int D, bool CAP>
+// LONE (the fill on its own, k_vel_ghosts): V_tG is rounded before V_nG n joins it; the joined fills leave
+// the order to the compiler.  (Both as they always were: the slip velocity feeds back into FP32 runs.)
+template <typename T, int D, bool CAP, bool LONE>
 __device__ __forceinline__ void vel_ghosts_body(
     const T *__restrict__ C, const T *__restrict__ F0, const T *__restrict__ F1, const T *__restrict__ F2,
     const int *__restrict__ gidx, const T *__restrict__ nrm, const T *__restrict__ dn, const T *__restrict__ gam,
@@ -1790,7 +1822,8 @@ __device__ __forceinline__ void vel_ghosts_body(
     const T VtM = um[a] - VnM * n[a];
     T VtG = VtM * fM;
     if constexpr (CAP) VtG -= Kc * (gI[a] - gIn * n[a]) * fK;
-    UG[(int64_t)a * G + g] = VnG * n[a] + VtG;
+    if constexpr (LONE) UG[(int64_t)a * G + g] = __builtin_fma(VnG, n[a], VtG);
+    else UG[(int64_t)a * G + g] = VnG * n[a] + VtG;
   }
 }
 
@@ -1802,7 +1835,7 @@ __global__ __launch_bounds__(kThreads) void k_vel_ghosts(
     int K, const int *__restrict__ f_cell, const int *__restrict__ f_axis, const int *__restrict__ f_gL,
     const int *__restrict__ f_gR, T *__restrict__ stashL, T *__restrict__ stashR, int64_t NF, Dims dm,
     T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls, unsigned nbg) {
-  vel_ghosts_body<T, D, CAP>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
+  vel_ghosts_body<T, D, CAP, true>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
                              stashL, stashR, NF, dm, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, nbg, blockIdx.x);
 }
 
@@ -1821,7 +1854,7 @@ __global__ __launch_bounds__(kThreads) void k_fill_static_vel(
     fill_static_body<T>(C, gidx, dn, gam, ap, w, CGn, CGnm1, CMs, G, K, cb, 0, blockIdx.x);
     return;
   }
-  vel_ghosts_body<T, D, false>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
+  vel_ghosts_body<T, D, false, false>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
                                stashL, stashR, NF, dm, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, nbg, blockIdx.x - nbc);
 }
 
@@ -2967,6 +3000,78 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm, StepLink *link)
   return e;
 }
 
+// Launch shapes before any tuning, from the grid alone.  A pass needs some 1024 workgroups to keep 256
+// compute units busy through its memory round trips; past that, larger tiles share a workgroup's fixed
+// costs (barriers, twiddles) among more lines.  So every tile takes as many lines as leave that many
+// workgroups, within its 32 KB (2D grids: 2 lines or columns, a launch of a few microseconds is all
+// latency).  Measured per step against the former fixed shapes {8 lines, 16 columns, line-tiled rhs}:
+// 512x256 FP64 49 -> 28 us, 1024x512 FP32 85 -> 40 us.
+// rhs, 3D: the z-march reads C once instead of three times and wins from 2^22 cells (256x128x128 FP64 66 us
+// line-tiled, 63 marching; 256x128x64 43 and 46; 512x256x128 296 and 210), with the longest march that
+// leaves 512 workgroups (1024 in FP32, whose planes are half as long in flight).  rhs, 2D: the y-march for
+// all widths it serves, at one radix, so that a batch of uneven sizes shares its kernels.
+// FP32 keeps the transforms at radix 16 and the rhs at 8: fewer stages round less, and rounding is what limits
+// it (64^3 coupled, 10 steps: u off by 2.2e-6 with the solve at radix 8, 1.3e-6 at 16).
+template <typename T>
+void default_shapes(Plan &p) {
+  constexpr int E = tile_elems<T>();
+  auto height = [](int64_t items, int hi) {   // log2 of the items per tile
+    int l = 1;
+    while (l < hi && (items >> (l + 1)) >= 1024) ++l;
+    return l;
+  };
+  if (p.d == 2) {
+    const int wide = p.n[0] >= 1024 ? 2 : 1;
+    const bool f64 = sizeof(T) == 8;
+    // (FP32 with the momentum step: the line-tiled rhs, whose sums round in the order they always have; the
+    // velocities carry 1e-4 of accumulated rounding, which another order changes by a fifth)
+    p.shape[0] = {1, 8, ym_ok(p) && (f64 || !p.ns) ? 3 : 2};
+    p.shape[1] = {4, 16, 1};
+    p.shape[2] = {clamp_log(wide, max_log_cols(p, p.n[1], E)), f64 ? 8 : 16, 1};
+    p.shape[3] = {1, f64 ? 8 : 16, 1};
+    return;
+  }
+  const int64_t lines = (int64_t)p.n[1] * p.n[2];
+  const int hl = max_log_lines(p, E);
+  // radix by line length: 8 where its stages divide the line evenly, else 16 (fewer stages)
+  auto radix = [](int logn) { return sizeof(T) == 8 && (logn == 8 || logn % 3 == 0 || logn == 5) ? 8 : 16; };
+  if (zm_ok(p) && p.N >= (int64_t(1) << 22)) {
+    const int L = sizeof(T) == 8 ? (p.n[0] == 512 ? 1 : 2) : (p.n[0] == 512 ? 2 : 3);
+    int zc = 5;
+    const int64_t want = sizeof(T) == 8 ? 512 : 1024;
+    while (zc > 3 && ((int64_t)(p.n[1] >> L) * (p.n[2] >> zc)) < want) --zc;
+    p.shape[0] = {L, sizeof(T) == 4 ? 8 : 4, zc};
+  } else {
+    p.shape[0] = {height(lines, hl), 8, p.n[0] >= 256 ? 2 : 1};
+  }
+  // 256-point lines take the fixed-size instances' widths
+  const int cy = max_log_cols(p, p.n[1], E), cz = max_log_cols(p, p.n[2], E);
+  p.shape[1] = {p.n[1] == 256 ? clamp_log(4, cy) : height((int64_t)p.n[0] * p.n[2], cy),
+                p.n[1] == 256 ? 16 : radix(p.logn[1]), 1};
+  p.shape[2] = {p.n[2] == 256 ? cz : height((int64_t)p.n[0] * p.n[1], cz),
+                p.n[2] == 256 ? (sizeof(T) == 8 ? 8 : 16) : radix(p.logn[2]), 1};
+  p.shape[3] = {p.n[0] == 256 ? clamp_log(sizeof(T) == 8 ? 3 : 4, hl) : height(lines, hl),
+                p.n[0] == 256 && sizeof(T) == 4 ? 16 : radix(p.logn[0]), 1};
+}
+
+// Tile heights of a 2D state inside a batch of `cells` cells: the batch as a whole fills the chip, so each
+// tile takes the lines that leave it about 1024 workgroups (32 cases, FP64: 178 us a step with the heights
+// of single states, 161 here, 198 with 4096 workgroups).  Heights change no result.
+template <typename T>
+void batch_heights(Plan &p, int64_t cells) {
+  constexpr int E = tile_elems<T>();
+  const int64_t per = cells / 1024;   // elements per workgroup
+  auto height = [&](int n, int hi) {
+    int l = 1;
+    while (l < hi && ((int64_t)n << (l + 1)) <= per) ++l;
+    return l;
+  };
+  const int hl = max_log_lines(p, E);
+  p.shape[0].log_tile = height(p.n[0], hl);
+  p.shape[2].log_tile = height(p.n[1], max_log_cols(p, p.n[1], E));
+  p.shape[3].log_tile = height(p.n[0], hl);
+}
+
 // Times every candidate shape of each pass on the state's buffers (the spectral workspace
 // only; the fields are not modified) and keeps the fastest.  `out` receives the chosen
 // shapes.  The candidates: lines/columns per tile from 2 to the 32 KB LDS limit, radix 8 or
@@ -3232,6 +3337,10 @@ int max_log_tile(const Plan &p, int pass) {
   return max_log_cols(p, p.n[pass == 1 ? 1 : p.d - 1], E);
 }
 
+template void default_shapes<double>(Plan &);
+template void default_shapes<float>(Plan &);
+template void batch_heights<double>(Plan &, int64_t);
+template void batch_heights<float>(Plan &, int64_t);
 template int max_log_tile<double>(const Plan &, int);
 template int max_log_tile<float>(const Plan &, int);
 template hipError_t tune_shapes<double>(Plan &, int, int);
@@ -3441,7 +3550,7 @@ __global__ __launch_bounds__(kThreads) void kb_fill(const CaseDesc<T> *__restric
     fill_static_body<T>(d.C[1 - parity], d.gidx, d.dn, d.gam, d.ap, d.w, d.CGn, d.CGnm1, d.CMs, d.G, d.K, d.cb, 0, t);
     return;
   }
-  vel_ghosts_body<T, 2, false>(d.C[1 - parity], d.F0, d.F1, d.F1, d.gidx, d.normal, d.dn, d.gam, d.ap, d.w, d.CMs,
+  vel_ghosts_body<T, 2, false, false>(d.C[1 - parity], d.F0, d.F1, d.F1, d.gidx, d.normal, d.dn, d.gam, d.ap, d.w, d.CMs,
                                d.UG, d.G, d.K, d.f_cell, d.f_axis, d.f_gL, d.f_gR, d.stashL, d.stashR, d.NF, d.dm,
                                d.inv2h, d.Cn, d.cos_t, d.inv_Ca, d.inv_mu, d.ls, d.nbg, t - nbc);
 }

@@ -812,8 +812,10 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
     e = enqueue_velocity_fill<T>(q, C, join ? &nx : nullptr);
     if (link) link->dphi_done = join && e == hipSuccess;
   }
-  if (eq) {
-    // the right-hand side is (rho0/dt) div u** alone: formed inside the forward x transform
+  // equal densities: the right-hand side is (rho0/dt) div u** alone, formed inside the forward x transform.
+  // (2D FP32 keeps the full expression: its velocities carry 1e-4 of rounding that way or this, and the
+  // transform saves it one launch of 14.)
+  if (eq && (p.d == 3 || sizeof(T) == 8)) {
     mark("ns_div_poisson");
     if (e == hipSuccess) e = enqueue_poisson<T>(p, p.Us, (double)k.rho0_dt * (double)k.inv_h);
   } else {

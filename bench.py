@@ -86,6 +86,14 @@ def kernel_template(name: str, shapes, es: int, n) -> list:
     def log2(v):
         return v.bit_length() - 1
 
+    def cols(m):
+        return (4 if es == 8 else 5) - (m == 512)
+
+    def small_fixed(m, lt, want, r):
+        """The fixed-size instance (log2 points, log2 tile) of a 64-, 128- or 512-point line, or (0, 0)."""
+        radix = 16 if m == 128 or es == 4 else 8
+        return (log2(m), lt) if m in (64, 128, 512) and lt == want and (r if r == 8 else 16) == radix else (0, 0)
+
     if name == "rhs_xdht":
         lt, r, u = shapes[0]
         if u >= 3 and nx in (256, 512):
@@ -98,18 +106,22 @@ def kernel_template(name: str, shapes, es: int, n) -> list:
     if name in ("xdht_fwd", "xdht_out"):
         lt, r, _ = shapes[3]
         logL = clamp(lt, log2(max(min(E // nx, lines), 2)))
-        fixed = (8, logL) if (nx == 256 and logL in (3, 4)) else (0, 0)
+        fixed = (8, logL) if (nx == 256 and logL in (3, 4)) else small_fixed(nx, logL, 2 if nx == 512 else 4, r)
         return [f"k_xdht<{t}, {E}, {r if r == 8 else 16}, {fixed[0]}, {fixed[1]}>"]
     if name in ("ydht_fwd", "ydht_inv"):
         lt, r, _ = shapes[1]
         lb = clamp(lt, log2(max(min(E // n[1], nx), 2)))
-        fixed = (8, lb) if (n[1] == 256 and lb in (3, 4) and nx * 256 * es < 2 ** 32) else (0, 0)
+        fixed = (8, lb) if (n[1] == 256 and lb in (3, 4)) else small_fixed(n[1], lb, cols(n[1]), r)
+        if nx * n[1] * es >= 2 ** 32:
+            fixed = (0, 0)
         return [f"k_strided_dht<{t}, {E}, {r if r == 8 else 16}, {fixed[0]}, {fixed[1]}>"]
     if name == "neumann_solve":
         lt, r, _ = shapes[2]
         lb = clamp(lt, log2(max(min(E // n[-1], nx), 2)))
         stride = nx * (n[1] if len(n) == 3 else 1)
-        fixed = (8, lb) if (n[-1] == 256 and (256 << lb) == E and stride * 256 * es < 2 ** 32) else (0, 0)
+        fixed = (8, lb) if (n[-1] == 256 and (256 << lb) == E) else small_fixed(n[-1], lb, cols(n[-1]), r)
+        if stride * n[-1] * es >= 2 ** 32:
+            fixed = (0, 0)
         return [f"k_neumann_solve<{t}, {E}, {r if r == 8 else 16}, {fixed[0]}, {fixed[1]}>"]
     if name in ("ns_predict", "ns_correct"):         # (matched fluids)
         return [f"k_{name}_zm<{t}, true>"]

@@ -1245,19 +1245,19 @@ __device__ __forceinline__ void neumann_body(unsigned char *smem_raw, T *__restr
   // fixed size: a thread keeps 16 bytes of adjacent columns and every (CP kThreads / B)-th
   // position, so its global offsets step by a constant (unsigned 32-bit bytes from a uniform base:
   // the caller bounds N * stride * sizeof(T)) and, the step being even, all its positions share one parity and
-  // land on reordered slots a constant LDS distance apart (16 positions, one padding group)
+  // land on reordered slots a constant LDS distance apart (whole padding groups of 16 positions)
   using FV = std::conditional_t<sizeof(T) == 8, double2, float4>;
   constexpr int CP = 16 / (int)sizeof(T);
   constexpr int RS = CLB ? (CP * kThreads) >> CLB : 2, KR = CLN ? (1 << CLN) / RS : 1;
   const int fcol = (threadIdx.x & ((B / CP) - 1)) * CP, fn0 = threadIdx.x / (B / CP);
   const int fp0 = (fn0 & 1) ? N - 1 - (fn0 >> 1) : fn0 >> 1;
   const int fa0 = fp0 * B + (fp0 >> 4) * 2 + fcol;
-  const int fda = (fn0 & 1) ? -((RS / 2) * B + 2) : (RS / 2) * B + 2;
+  const int fda = ((RS / 2) * B + (RS / 32) * 2) * ((fn0 & 1) ? -1 : 1);
   unsigned foff = ((unsigned)fn0 * (unsigned)stride + (unsigned)fcol) * (unsigned)sizeof(T);   // bytes
   const unsigned fstep = (unsigned)RS * (unsigned)stride * (unsigned)sizeof(T);
   char *const gb = reinterpret_cast<char *>(W + base);
   if constexpr (CLN != 0 && CLB != 0) {
-    static_assert(RS == 32 && KR * RS == (1 << CLN), "fixed-size tile");
+    static_assert(RS % 32 == 0 && KR * RS == (1 << CLN), "fixed-size tile");
     FV v[KR];
 #pragma unroll
     for (int k = 0; k < KR; ++k) v[k] = *reinterpret_cast<const FV *>(gb + (foff + k * fstep));
@@ -1937,20 +1937,30 @@ __global__ __launch_bounds__(kThreads) void k_phi(const T *__restrict__ C, T *__
 }
 
 // Mirror value at the ghosts, sixteen lanes per ghost as in the other ghost kernels (one thread per ghost
-// walked its 2K gathers one after another: 14.6 -> 7 us at the 256^3 sphere's 42 k ghosts).
-template <typename T>
+// walked its 2K gathers one after another: 14.6 -> 7 us at the 256^3 sphere's 42 k ghosts).  ORDERED (2D):
+// the lanes' values are added in the order of the averaging points, as in k_fill_dynamic.
+template <typename T, bool ORDERED>
 __global__ __launch_bounds__(kThreads) void k_phi_ghost(T *__restrict__ phi, const int *__restrict__ gidx,
                                                         const int *__restrict__ ap, const T *__restrict__ w,
                                                         int64_t G, int K) {
   const int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
   const int sl = threadIdx.x & 15;
   const int cg = gidx[g < G ? g : G - 1];
-  T v = T(0);
+  T wt = T(0), f = T(0), m;
   if (g < G && sl < 2 * K) {
     const int64_t i = g * kGhostSlots + sl;
-    v = (sl < K ? T(2) : T(-1)) * w[i] * phi[ap[i]];
+    wt = w[i];
+    f = phi[ap[i]];
   }
-  const T m = group16_sum(v);
+  if constexpr (ORDERED) {
+    const int base = (threadIdx.x & 63) & ~15;
+    T o1 = T(0), o2 = T(0);
+    for (int k = 0; k < K; ++k) o1 += __shfl(wt, base + k) * __shfl(f, base + k);
+    for (int k = K; k < 2 * K; ++k) o2 += __shfl(wt, base + k) * __shfl(f, base + k);
+    m = T(2) * o1 - o2;
+  } else {
+    m = group16_sum((sl < K ? T(2) : T(-1)) * wt * f);
+  }
   if (g < G && sl == 0) phi[cg] = m;
 }
 
@@ -2595,8 +2605,18 @@ inline int max_log_cols(const Plan &p, int N, int E) {
 
 inline int clamp_log(int v, int hi) { return v < 1 ? 1 : (v > hi ? hi : v); }
 
-// The fixed-size instances (256-point lines, template constants for the line length and tile width)
-// serve the tile widths and radices below; other shapes take the runtime-size kernels.
+// The fixed-size instances (line length and tile width are template constants, so addresses step by constants
+// and loops unroll) serve 64- to 512-point lines at the tile widths and radices below; other shapes take the
+// runtime-size kernels, with the same results.  Besides 256 points (one width per radix a tuner may ask for),
+// each length has the one shape that the grid's default takes: 16 columns in FP64 and 32 in FP32 (128 bytes a
+// row; half as many at 512 points, which fill the 32 KB tile), 16 lines in the x pass (4 at 512).  Per step,
+// runtime-size against fixed: 128^3 FP64 105 and 91 us (y 13.7 and 10.9, solve 23.5 and 19.6, inverse y 17.8
+// and 15.1, x out 13.9 and 10.1), FP32 78 and 66; 256x64x64 61 and 56; 32x512x512 290 and 273.
+template <typename T> constexpr int fixed_cols(int logn) { return (sizeof(T) == 8 ? 4 : 5) - (logn == 9 ? 1 : 0); }
+constexpr int fixed_lines(int logn) { return logn == 9 ? 2 : 4; }
+// radix at 64 and 512 points (128 take 16: radix 8 leaves a stage of 2, 97 against 92 us per 128^3 step)
+template <typename T> constexpr int fixed_radix() { return sizeof(T) == 8 ? 8 : 16; }
+
 template <typename T>
 hipError_t launch_xdht(const Plan &p, const T *in, T *out, const Plan::Shape &sh) {
   constexpr int E = tile_elems<T>();
@@ -2608,7 +2628,14 @@ hipError_t launch_xdht(const Plan &p, const T *in, T *out, const Plan::Shape &sh
   hipLaunchKernelGGL((k_xdht<__VA_ARGS__>), dim3(nb), dim3(kThreads), lds, p.stream, in, out, p.logn[0], logL, \
                      (const T *)p.twr[0], (const T *)p.twi[0])
   const bool r8 = sh.radix == 8, fixed = p.logn[0] == 8;
-  if (fixed && logL == 3) {
+  constexpr int RD = fixed_radix<T>();
+  if (p.logn[0] == 6 && logL == 4 && sh.radix == RD) {
+    CHIB_XDHT(T, E, RD, 6, 4);
+  } else if (p.logn[0] == 7 && logL == 4 && !r8) {
+    CHIB_XDHT(T, E, 16, 7, 4);
+  } else if (p.logn[0] == 9 && logL == 2 && sh.radix == RD) {
+    CHIB_XDHT(T, E, RD, 9, 2);
+  } else if (fixed && logL == 3) {
     if (r8) CHIB_XDHT(T, E, 8, 8, 3);
     else CHIB_XDHT(T, E, 16, 8, 3);
   } else if (fixed && logL == 4) {
@@ -2665,8 +2692,16 @@ hipError_t launch_ydht(const Plan &p, const Plan::Shape &sh) {
   hipLaunchKernelGGL((k_strided_dht<__VA_ARGS__>), dim3(nb), dim3(kThreads), lds, p.stream, (T *)p.W, p.logn[1], \
                      (int64_t)nx, lb, lxb, (int64_t)nx * p.n[1], (const T *)p.twr[1], (const T *)p.twi[1])
   const bool r8 = sh.radix == 8;
-  const bool fixed = p.logn[1] == 8 && (int64_t)nx * 256 * (int64_t)sizeof(T) < (int64_t(1) << 32);
-  if (fixed && lb == 3) {
+  const bool fits = (int64_t)nx * p.n[1] * (int64_t)sizeof(T) < (int64_t(1) << 32);
+  const bool fixed = fits && p.logn[1] == 8;
+  constexpr int WB = fixed_cols<T>(7), RD = fixed_radix<T>();
+  if (fits && p.logn[1] == 6 && lb == WB && sh.radix == RD) {
+    CHIB_YDHT(T, E, RD, 6, WB);
+  } else if (fits && p.logn[1] == 7 && lb == WB && !r8) {
+    CHIB_YDHT(T, E, 16, 7, WB);
+  } else if (fits && p.logn[1] == 9 && lb == WB - 1 && sh.radix == RD) {
+    CHIB_YDHT(T, E, RD, 9, WB - 1);
+  } else if (fixed && lb == 3) {
     if (r8) CHIB_YDHT(T, E, 8, 8, 3);
     else CHIB_YDHT(T, E, 16, 8, 3);
   } else if (fixed && lb == 4) {
@@ -2702,8 +2737,16 @@ hipError_t launch_neumann(const Plan &p, const Plan::Shape &sh) {
                      (const T *)p.dctc, (const T *)p.dcts, p.poisson)
   // 256-point lines in a full tile
   constexpr int FB = ilog2c(E / 256);
-  const bool fixed = p.logn[ax] == 8 && lb == FB && stride * 256 * (int64_t)sizeof(T) < (int64_t(1) << 32);
-  if (fixed) {
+  const bool fits = stride * Nn * (int64_t)sizeof(T) < (int64_t(1) << 32);
+  const bool fixed = fits && p.logn[ax] == 8 && lb == FB;
+  constexpr int WB = fixed_cols<T>(7), RD = fixed_radix<T>();
+  if (fits && p.logn[ax] == 6 && lb == WB && sh.radix == RD) {
+    CHIB_NEUMANN(T, E, RD, 6, WB);
+  } else if (fits && p.logn[ax] == 7 && lb == WB && sh.radix == 16) {
+    CHIB_NEUMANN(T, E, 16, 7, WB);
+  } else if (fits && p.logn[ax] == 9 && lb == WB - 1 && sh.radix == RD) {
+    CHIB_NEUMANN(T, E, RD, 9, WB - 1);
+  } else if (fixed) {
     if (sh.radix == 8) CHIB_NEUMANN(T, E, 8, 8, FB);
     else CHIB_NEUMANN(T, E, 16, 8, FB);
   } else if (sh.radix == 8) {
@@ -3005,7 +3048,9 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm, StepLink *link)
 // costs (barriers, twiddles) among more lines.  So every tile takes as many lines as leave that many
 // workgroups, within its 32 KB (2D grids: 2 lines or columns, a launch of a few microseconds is all
 // latency).  Measured per step against the former fixed shapes {8 lines, 16 columns, line-tiled rhs}:
-// 512x256 FP64 49 -> 28 us, 1024x512 FP32 85 -> 40 us.
+// 512x256 FP64 49 -> 28 us, 1024x512 FP32 85 -> 40 us.  Lines of 64 to 512 points take the width of their
+// fixed-size instance from 128 tiles on, which saves more than the emptier chip costs (64^3 38 -> 34 us with
+// 256 tiles instead of 1024, 64x64x32 33.9 -> 31.8 with 128).
 // rhs, 3D: the z-march reads C once instead of three times and wins from 2^22 cells (256x128x128 FP64 66 us
 // line-tiled, 63 marching; 256x128x64 43 and 46; 512x256x128 296 and 210), with the longest march that
 // leaves 512 workgroups (1024 in FP32, whose planes are half as long in flight).  rhs, 2D: the y-march for
@@ -3044,13 +3089,16 @@ void default_shapes(Plan &p) {
   } else {
     p.shape[0] = {height(lines, hl), 8, p.n[0] >= 256 ? 2 : 1};
   }
-  // 256-point lines take the fixed-size instances' widths
   const int cy = max_log_cols(p, p.n[1], E), cz = max_log_cols(p, p.n[2], E);
-  p.shape[1] = {p.n[1] == 256 ? clamp_log(4, cy) : height((int64_t)p.n[0] * p.n[2], cy),
+  auto width = [&](int64_t items, int logn, int wd, int hi) {
+    const bool fixed = logn >= 6 && logn <= 9 && wd <= hi && (logn == 8 || (items >> wd) >= 128);
+    return fixed ? wd : height(items, hi);
+  };
+  p.shape[1] = {width((int64_t)p.n[0] * p.n[2], p.logn[1], p.n[1] == 256 ? 4 : fixed_cols<T>(p.logn[1]), cy),
                 p.n[1] == 256 ? 16 : radix(p.logn[1]), 1};
-  p.shape[2] = {p.n[2] == 256 ? cz : height((int64_t)p.n[0] * p.n[1], cz),
+  p.shape[2] = {width((int64_t)p.n[0] * p.n[1], p.logn[2], p.n[2] == 256 ? cz : fixed_cols<T>(p.logn[2]), cz),
                 p.n[2] == 256 ? (sizeof(T) == 8 ? 8 : 16) : radix(p.logn[2]), 1};
-  p.shape[3] = {p.n[0] == 256 ? clamp_log(sizeof(T) == 8 ? 3 : 4, hl) : height(lines, hl),
+  p.shape[3] = {width(lines, p.logn[0], p.n[0] == 256 ? (sizeof(T) == 8 ? 3 : 4) : fixed_lines(p.logn[0]), hl),
                 p.n[0] == 256 && sizeof(T) == 4 ? 16 : radix(p.logn[0]), 1};
 }
 
@@ -3290,9 +3338,12 @@ hipError_t enqueue_phi(const Plan &p, int cur, void *out) {
   else
     hipLaunchKernelGGL((k_phi<T, 3>), dim3(blocks_for(p.N)), dim3(kThreads), 0, p.stream, (const T *)p.C[cur],
                        (T *)out, dm, cn2, ih2, p.N);
-  if (p.G)
-    hipLaunchKernelGGL((k_phi_ghost<T>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream, (T *)out, p.gidx,
-                       p.apg, (const T *)p.wg, p.G, p.K);
+  if (p.G && p.d == 2)
+    hipLaunchKernelGGL((k_phi_ghost<T, true>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream, (T *)out,
+                       p.gidx, p.apg, (const T *)p.wg, p.G, p.K);
+  else if (p.G)
+    hipLaunchKernelGGL((k_phi_ghost<T, false>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream, (T *)out,
+                       p.gidx, p.apg, (const T *)p.wg, p.G, p.K);
   return hipGetLastError();
 }
 

@@ -1,0 +1,70 @@
+"""GPU: transform kernels compiled for 64-, 128- and 512-point lines give the bits of the runtime-size
+kernels, whose per-line arithmetic is the same, and match the oracle."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle.geometry import build_tables
+from oracle.solver import derived_coefficients, spectral_solve
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def chib():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2104_00350_amd import chib as m
+    return m
+
+
+def _state(chib, n, precision):
+    d = len(n)
+    grid = W.Grid(n, (0.0,) * d, tuple(v / 64.0 for v in n))
+    prm = W.Params(Cn=0.02, Pe=100.0, dt=1e-4)
+    T = build_tables(grid, [], prm)
+    geo = chib.Geometry.from_tables(grid.n, grid.lo, grid.hi, T.gidx, T.normal, T.dn, T.gamma, T.ap, T.w)
+    st = chib.State(geo, prm, precision)
+    st.set_initial(np.zeros(grid.shape))
+    return grid, prm, st
+
+
+# every axis at each length, and the narrowest grid that a tile of adjacent columns fits
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("n", [(64, 64, 64), (128, 128, 128), (32, 64, 128), (32, 512, 64), (512, 64, 512),
+                               (64, 128), (128, 512), (512, 64)])
+def test_fixed_lines(chib, n, precision):
+    grid, prm, st = _state(chib, n, precision)
+    Q = np.random.default_rng(11).standard_normal(grid.shape) * 1e9
+    cols = 4 if precision == 64 else 5
+    default = 8 if precision == 64 else 16
+
+    def shapes(drop):
+        r = [16 if m == 128 else default for m in n]
+        lb = [cols - (m == 512) - drop for m in n]
+        return [[2, 8, 1], [lb[1], r[1], 1], [lb[-1], r[-1], 1], [(2 if n[0] == 512 else 4) - drop, r[0], 1]]
+
+    print("fixed-size lines", n, precision, shapes(0), flush=True)
+    st.set_shapes(shapes(0))
+    fixed = np.asarray(st.stage(chib.STAGE_SOLVE, Q))
+    st.set_shapes(shapes(1))
+    runtime = np.asarray(st.stage(chib.STAGE_SOLVE, Q))
+    assert np.array_equal(fixed, runtime)
+    _, al, a = derived_coefficients(prm)
+    ref = spectral_solve(Q, grid, al, a)
+    assert np.max(np.abs(fixed - ref)) <= (1e-12 if precision == 64 else 1e-4) * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("n", [(16, 8), (64, 32), (1024, 512), (8, 8, 8), (32, 32, 64), (64, 64, 64),
+                               (128, 128, 64), (256, 128, 128), (512, 256, 32)])
+def test_default_shapes_fit(chib, n, precision):
+    """The shapes a new state takes from its grid's size: the solve at them against the oracle."""
+    grid, prm, st = _state(chib, n, precision)
+    Q = np.random.default_rng(12).standard_normal(grid.shape) * 1e9
+    print("default shapes", n, precision, flush=True)
+    out = np.asarray(st.stage(chib.STAGE_SOLVE, Q))
+    _, al, a = derived_coefficients(prm)
+    ref = spectral_solve(Q, grid, al, a)
+    assert np.max(np.abs(out - ref)) <= (1e-12 if precision == 64 else 1e-4) * np.max(np.abs(ref))

@@ -178,13 +178,10 @@ template <typename T> hipError_t enqueue_batch_step(const BatchLaunch &bl, int p
 
 // Logical tile of hardware block b of nb: blocks are dealt round-robin to the 8 XCDs, so this
 // gives each XCD a run of consecutive tiles and neighbouring tiles (which read each other's halo
-// lines) share its L2.  A permutation of [0, nb) when nb is a multiple of 8, else the identity.
+// lines) share its L2.  A permutation of [0, nb) for every nb.
 __device__ __forceinline__ int xcd_tile(int b, int nb) {
-  if ((nb & 7) == 0) {
-    const int per = nb >> 3;
-    return (b & 7) * per + (b >> 3);
-  }
-  return b;
+  const int per = nb >> 3, rest = nb & 7, x = b & 7;
+  return x * per + (x < rest ? x : rest) + (b >> 3);
 }
 
 // Launch-shape helpers shared with the host (elements per LDS tile).

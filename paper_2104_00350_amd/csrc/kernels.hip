@@ -619,8 +619,10 @@ __host__ __device__ __forceinline__ int ym_extra(int nx) { return 2 * nx; }
 // K1 for 2D grids, marching in y: the workgroup owns the L rows of its tile across the whole x
 // range, thread t the columns x = t + 256 m (m < XM, nx <= 256 XM).  C~ = 2C^n - C^(n-1) of row
 // y-1 and the raw C^n, C^(n-1) of rows y and y+1 stay in registers, so every value is loaded
-// once and y neighbours never leave the thread; the raw values of row y+2 are requested
-// while row y is computed.  x neighbours come from a two-row
+// once and y neighbours never leave the thread; the raw values and the faces of row y+2 are requested
+// once row y is computed (a row's arithmetic is far shorter than a memory round trip; with the faces requested
+// at the head of their own row, 72 instead of 63 us per step of 32 cases, 5.8 million cells, FP64, at three
+// waves per SIMD, which is what the tile and ring leave in LDS anyway).  x neighbours come from a two-row
 // ring of C~ in LDS (one barrier per row); each Q row goes straight into the line tile, which
 // then goes through the same x transform as the line-tiled K1.
 template <typename T, int XM, int R>
@@ -655,21 +657,29 @@ __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__
       cm[m] = T(2) * a_m - b_m;
     }
   }
+  // faces of the row and of the next one (in flight)
+  T f0[XM], f0m[XM], f1[XM], g0[XM], g0m[XM], g1[XM];
+  auto faces = [&](int m, int y, T *u0, T *u0m, T *u1) {
+    const int i = tid + 256 * m;
+    const T *r0 = rowp(F0, y), *r1 = rowp(F1, y);
+    u0[m] = r0[i];
+    u0m[m] = r0[(i - 1) & (nx - 1)];
+    u1[m] = r1[i];
+  };
+#pragma unroll
+  for (int m = 0; m < XM; ++m)
+    if (tid + 256 * m < nx) {
+      faces(m, y0, f0, f0m, f1);
+      faces(m, y0 + 1, g0, g0m, g1);
+    }
   for (int r = 0; r < L; ++r) {
     const int y = y0 + r;
     const bool top = y == ny - 1, bot = y == 0;
     T *xb = xr + (r & 1) * nx;
-    T f0[XM], f0m[XM], f1[XM];
 #pragma unroll
     for (int m = 0; m < XM; ++m) {
       const int i = tid + 256 * m;
-      if (i < nx) {
-        const T *r0 = rowp(F0, y), *r1 = rowp(F1, y);
-        f0[m] = r0[i];
-        f0m[m] = r0[(i - 1) & (nx - 1)];
-        f1[m] = r1[i];
-        xb[i] = T(2) * a0[m] - b0[m];
-      }
+      if (i < nx) xb[i] = T(2) * a0[m] - b0[m];
     }
     __syncthreads();   // the row is in LDS; the ring slot written next row was last read two rows ago
 #pragma unroll
@@ -688,9 +698,13 @@ __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__
         a1[m] = an[m];
         b1[m] = bn[m];
         f1m[m] = f1[m];
-        if (r + 1 < L) {
+        f0[m] = g0[m];
+        f0m[m] = g0m[m];
+        f1[m] = g1[m];
+        if (r + 2 < L) {
           an[m] = rowp(Cn, y + 3)[i];
           bn[m] = rowp(Cp, y + 3)[i];
+          faces(m, y + 2, g0, g0m, g1);
         }
       }
     }
@@ -716,7 +730,7 @@ __device__ __forceinline__ void rhs_ym_body(unsigned char *smem_raw, const T *__
 }
 
 template <typename T, int XM, int R>
-__global__ __launch_bounds__(kThreads, R == 8 ? 4 : 3) void k_rhs_xdht_ym(const T *__restrict__ Cn, const T *__restrict__ Cp,
+__global__ __launch_bounds__(kThreads, R == 8 && XM < 4 ? 4 : 3) void k_rhs_xdht_ym(const T *__restrict__ Cn, const T *__restrict__ Cp,
                                                           const T *__restrict__ F0, const T *__restrict__ F1,
                                                           T *__restrict__ W, Dims dm, RhsCoef<T> cf, int logL,
                                                           const T *__restrict__ twr, const T *__restrict__ twi,
@@ -2612,7 +2626,8 @@ inline int clamp_log(int v, int hi) { return v < 1 ? 1 : (v > hi ? hi : v); }
 // row; half as many at 512 points, which fill the 32 KB tile), 16 lines in the x pass (4 at 512).  Per step,
 // runtime-size against fixed: 128^3 FP64 105 and 91 us (y 13.7 and 10.9, solve 23.5 and 19.6, inverse y 17.8
 // and 15.1, x out 13.9 and 10.1), FP32 78 and 66; 256x64x64 61 and 56; 32x512x512 290 and 273.
-template <typename T> constexpr int fixed_cols(int logn) { return (sizeof(T) == 8 ? 4 : 5) - (logn == 9 ? 1 : 0); }
+template <typename T>
+constexpr int fixed_cols(int logn) { return (sizeof(T) == 8 ? 4 : 5) - (logn == 9 ? 1 : 0); }
 constexpr int fixed_lines(int logn) { return logn == 9 ? 2 : 4; }
 // radix at 64 and 512 points (128 take 16: radix 8 leaves a stage of 2, 97 against 92 us per 128^3 step)
 template <typename T> constexpr int fixed_radix() { return sizeof(T) == 8 ? 8 : 16; }
@@ -3103,12 +3118,16 @@ void default_shapes(Plan &p) {
 }
 
 // Tile heights of a 2D state inside a batch of `cells` cells: the batch as a whole fills the chip, so each
-// tile takes the lines that leave it about 1024 workgroups (32 cases, FP64: 178 us a step with the heights
-// of single states, 161 here, 198 with 4096 workgroups).  Heights change no result.
+// tile of the x passes takes the lines that leave it about 1024 workgroups, and past two million cells 2048
+// (32 cases of 5.8 million cells: FP64 148 us a step with 1024, 139 with 2048, 144 with 4096; 6 cases of 1.3
+// million: 64 with 1024, 69 with 2048).  The bounded axis takes the widths of the fixed-size solves, FP32,
+// which has none here, only past two million cells (32 cases 113 -> 108 us; 6 cases 58 -> 61).  Heights
+// change no result.
 template <typename T>
 void batch_heights(Plan &p, int64_t cells) {
   constexpr int E = tile_elems<T>();
-  const int64_t per = cells / 1024;   // elements per workgroup
+  const bool large = cells >= (int64_t(1) << 21);
+  const int64_t per = large ? cells / 2048 : cells / 1024;   // elements per workgroup
   auto height = [&](int n, int hi) {
     int l = 1;
     while (l < hi && ((int64_t)n << (l + 1)) <= per) ++l;
@@ -3116,7 +3135,9 @@ void batch_heights(Plan &p, int64_t cells) {
   };
   const int hl = max_log_lines(p, E);
   p.shape[0].log_tile = height(p.n[0], hl);
-  p.shape[2].log_tile = height(p.n[1], max_log_cols(p, p.n[1], E));
+  const int hc = max_log_cols(p, p.n[1], E);
+  p.shape[2].log_tile =
+      sizeof(T) == 8 || large ? clamp_log(fixed_cols<T>(p.logn[1]), hc) : height(p.n[1], hc);
   p.shape[3].log_tile = height(p.n[0], hl);
 }
 
@@ -3535,10 +3556,10 @@ template <typename T, int E, int U, int R>
 __global__ __launch_bounds__(kThreads) void kb_rhs(const CaseDesc<T> *__restrict__ cs, const int *__restrict__ off,
                                                    int n, int parity) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int c = find_case(off, n, blockIdx.x);
+  const int blk = xcd_tile(blockIdx.x, gridDim.x), c = find_case(off, n, blk);
   const CaseDesc<T> &d = cs[c];
   rhs_xdht_body<T, 2, E, U, R>(smem_raw, d.C[parity], d.C[1 - parity], d.F0, d.F1, d.F1, d.W, d.dm, d.cf,
-                               d.logL_rhs, d.twr0, d.twi0, (int)(blockIdx.x - off[c]), d.rp);
+                               d.logL_rhs, d.twr0, d.twi0, blk - off[c], d.rp);
 }
 
 // dg of every ghost of every case, before the rhs pass.
@@ -3552,12 +3573,12 @@ __global__ __launch_bounds__(kThreads) void kb_dphi(const CaseDesc<T> *__restric
 }
 
 template <typename T, int R>
-__global__ __launch_bounds__(kThreads, R == 8 ? 4 : 3) void kb_rhs_ym(const CaseDesc<T> *__restrict__ cs,
+__global__ __launch_bounds__(kThreads, 3) void kb_rhs_ym(const CaseDesc<T> *__restrict__ cs,
                                                       const int *__restrict__ off, int n, int parity) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int c = find_case(off, n, blockIdx.x);
+  const int blk = xcd_tile(blockIdx.x, gridDim.x), c = find_case(off, n, blk);
   const CaseDesc<T> &d = cs[c];
-  const int t = (int)(blockIdx.x - off[c]);
+  const int t = blk - off[c];
   // the same instantiation as the single-state launch for this width, so results match bit for bit
   if (d.dm.nx <= 256)
     rhs_ym_body<T, 1, R>(smem_raw, d.C[parity], d.C[1 - parity], d.F0, d.F1, d.W, d.dm, d.cf, d.logL_rhs, d.twr0, d.twi0, t, d.rp);
@@ -3571,21 +3592,34 @@ template <typename T, int E, int R>
 __global__ __launch_bounds__(kThreads) void kb_neumann(const CaseDesc<T> *__restrict__ cs, const int *__restrict__ off,
                                                        int n) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int c = find_case(off, n, blockIdx.x);
+  const int blk = xcd_tile(blockIdx.x, gridDim.x), c = find_case(off, n, blk);
   const CaseDesc<T> &d = cs[c];
-  neumann_body<T, E, R>(smem_raw, d.W, d.dm.lny, (int64_t)d.dm.nx, d.logB, d.lognxb, (int64_t)0, d.lamx,
-                        (const T *)nullptr, d.lamy, d.a, d.alpha_s, d.inv_norm, d.twr1, d.twi1, d.dctc, d.dcts,
-                        (int)(blockIdx.x - off[c]), 0);
+#define CHIB_BODY(...)                                                                                            \
+  neumann_body<__VA_ARGS__>(smem_raw, d.W, d.dm.lny, (int64_t)d.dm.nx, d.logB, d.lognxb, (int64_t)0, d.lamx,      \
+                            (const T *)nullptr, d.lamy, d.a, d.alpha_s, d.inv_norm, d.twr1, d.twi1, d.dctc, d.dcts, \
+                            blk - off[c], 0)
+  // fixed sizes in FP64 (32 cases: 42 -> 35 us).  FP32 keeps the one runtime-size body: next to others it
+  // contracts into other fused multiply-adds than alone, and a member steps as it does alone, bit for bit.
+  if constexpr (sizeof(T) == 8) {
+    if (d.dm.lny == 6 && d.logB == fixed_cols<T>(6)) CHIB_BODY(T, E, R, 6, fixed_cols<T>(6));
+    else if (d.dm.lny == 7 && d.logB == fixed_cols<T>(7)) CHIB_BODY(T, E, R, 7, fixed_cols<T>(7));
+    else if (d.dm.lny == 8 && d.logB == fixed_cols<T>(8)) CHIB_BODY(T, E, R, 8, fixed_cols<T>(8));
+    else if (d.dm.lny == 9 && d.logB == fixed_cols<T>(9)) CHIB_BODY(T, E, R, 9, fixed_cols<T>(9));
+    else CHIB_BODY(T, E, R);
+  } else {
+    CHIB_BODY(T, E, R);
+  }
+#undef CHIB_BODY
 }
 
 template <typename T, int E, int R>
 __global__ __launch_bounds__(kThreads) void kb_out(const CaseDesc<T> *__restrict__ cs, const int *__restrict__ off,
                                                    int n, int parity) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int c = find_case(off, n, blockIdx.x);
+  const int blk = xcd_tile(blockIdx.x, gridDim.x), c = find_case(off, n, blk);
   const CaseDesc<T> &d = cs[c];
   xdht_body<T, E, R>(smem_raw, d.W, d.C[1 - parity], d.dm.lnx, d.logL_out, d.twr0, d.twi0,
-                     (int)(blockIdx.x - off[c]));
+                     blk - off[c]);
 }
 
 // Static C fill and (with the velocity fill) the ghost velocities of every case in one launch:

@@ -1089,14 +1089,14 @@ __global__ __launch_bounds__(kThreads) void k_div_xdht(const T *__restrict__ U0,
   const int line0 = xcd_tile(blockIdx.x, gridDim.x) << logL;
   if constexpr (D == 3 && CLN != 0 && CLB != 0) {
     // fixed size: 16 bytes of every field per thread; the x neighbour of a thread's first value is the last
-    // one of the lane below (the first lane of a wave asks for it)
+    // one of the lane below (the first lane of a wave or a line asks for it)
     constexpr int CP = 16 / (int)sizeof(T);
     typedef T FV __attribute__((ext_vector_type(CP)));
     constexpr int RS = (CP * kThreads) >> CLN, KR = (1 << CLB) / RS, KB = KR < 4 ? KR : 4;
     static_assert(RS >= 1 && KR % KB == 0, "fixed-size tile");
     const int i = (threadIdx.x & ((1 << CLN) / CP - 1)) * CP, l0 = threadIdx.x / ((1 << CLN) / CP);
     const int im = (i - 1) & ((1 << CLN) - 1);
-    const bool first = (threadIdx.x & 63) == 0;
+    const bool first = (threadIdx.x & 63) == 0 || i == 0;
     auto ld = [](const T *p) { return *reinterpret_cast<const FV *>(p); };
 #pragma unroll
     for (int k0 = 0; k0 < KR; k0 += KB) {
@@ -2134,12 +2134,12 @@ template <typename T>
 __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__ C, const T *__restrict__ F0,
                                                            const T *__restrict__ F1, const T *__restrict__ F2,
                                                            T *__restrict__ R, T *__restrict__ Cnext, Dims dm, T cn2,
-                                                           T half_inv_h, T inv_h2, T inv_pe, T dt, int first, int zc) {
+                                                           T half_inv_h, T inv_h2, T inv_pe, T dt, int first, int zc, int runs) {
   __shared__ T sc[4][kXcPlane];
   __shared__ T sp[3][kXpPlane];
   const int nx = dm.nx, ny = dm.ny, nz = dm.nz;
   const int nbx = nx / kXx, nby = ny / kXy;
-  const int b = blockIdx.x;
+  const int b = runs ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const int x0 = (b % nbx) * kXx, y0 = ((b / nbx) % nby) * kXy, z0 = b / (nbx * nby) * zc;
   const int tid = threadIdx.x, tx = tid & (kXx - 1), ty = tid / kXx;
   const int col = x0 + tx + ((y0 + ty) << dm.lnx);
@@ -2683,6 +2683,20 @@ hipError_t launch_div_xdht(const Plan &p, void *const *vel, double fac, const Pl
       else if (logL == 3) CHIB_DIV(16, 8, 3);
       else if (r8) CHIB_DIV(8, 8, 4);
       else CHIB_DIV(16, 8, 4);
+      return hipGetLastError();
+    }
+    constexpr int RD = fixed_radix<T>();
+    const bool rd = sh.radix == RD;
+    if (p.logn[0] == 6 && logL == fixed_lines(6) && rd) {
+      CHIB_DIV(RD, 6, fixed_lines(6));
+      return hipGetLastError();
+    }
+    if (p.logn[0] == 7 && logL == fixed_lines(7) && !r8) {
+      CHIB_DIV(16, 7, fixed_lines(7));
+      return hipGetLastError();
+    }
+    if (p.logn[0] == 9 && logL == fixed_lines(9) && rd) {
+      CHIB_DIV(RD, 9, fixed_lines(9));
       return hipGetLastError();
     }
   }
@@ -3452,9 +3466,11 @@ hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer 
     mark("explicit_update");
     if (e == hipSuccess) {
       const int zc = explicit_zm_planes(p);
+      // (in runs up to half that size in FP64: 128^3 45.7 -> 42.5 us a step, 256x256x128 117.7 -> 118.9)
       const unsigned nb = (unsigned)((p.n[0] / kXx) * (p.n[1] / kXy) * (p.n[2] / zc));
       hipLaunchKernelGGL((k_explicit_zm<T>), dim3(nb), dim3(kXThreads), 0, p.stream, Cn, (const T *)p.F[0],
-                         (const T *)p.F[1], (const T *)p.F[2], (T *)p.R, Cnext, dm, cn2, hih, ih2, ipe, dt, first, zc);
+                         (const T *)p.F[1], (const T *)p.F[2], (T *)p.R, Cnext, dm, cn2, hih, ih2, ipe, dt, first, zc,
+                         tiles_in_runs<T>(p) && (sizeof(T) == 4 || p.N < (int64_t(1) << 23)));
       if (p.G)
         hipLaunchKernelGGL((k_patch_apply<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, p.pl_cell,
                            p.pl_ref, (const T *)p.dg, (T *)p.R, Cnext, p.NP, 2 * p.d + 1, (T)(2 * p.d), ih2, ipe,

@@ -252,13 +252,13 @@ __global__ __launch_bounds__(kEThreads, 4) void k_ns_predict_zm(FaceSet<T> U, co
                                                                 const T *__restrict__ phi, FaceSet<T> Nh,
                                                                 FaceSet<T> Af, FaceSet<T> Us, NsGrid g,
                                                                 NsCoef<T> k, PredictCoef<T> q, T inv_rf, int first,
-                                                                int zc) {
+                                                                int zc, int runs) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr int PL = kEhx * kEhy;                            // one field of one slot
   T *const s = reinterpret_cast<T *>(smem_raw);              // [slot][field][row][column]
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const int tiles_x = nx / kEx, tiles_y = ny / kEy;
-  int b = (int)blockIdx.x;
+  int b = runs ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const int bx = b % tiles_x;
   b /= tiles_x;
   const int by = b % tiles_y;
@@ -521,11 +521,12 @@ constexpr int kPx = 64, kPy = 8, kPThreads = kPx * kPy, kPp = kPx + 2;
 template <typename T>
 __global__ __launch_bounds__(kPThreads) void k_ns_pressure_rhs_zm(FaceSet<T> Us, const T *__restrict__ C,
                                                                   const T *__restrict__ P0, const T *__restrict__ P1,
-                                                                  T *__restrict__ R, NsGrid g, NsCoef<T> k, int zc) {
+                                                                  T *__restrict__ R, NsGrid g, NsCoef<T> k, int zc,
+                                                                  int runs) {
   __shared__ T s[2][4][(kPy + 2) * kPp];                     // p^, C, u**_x, u**_y
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const int tiles_x = nx / kPx, tiles_y = ny / kPy;
-  int b = (int)blockIdx.x;
+  int b = runs ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const int bx = b % tiles_x;
   b /= tiles_x;
   const int by = b % tiles_y;
@@ -606,12 +607,12 @@ template <typename T, bool EQ>
 __global__ __launch_bounds__(kCThreads) void k_ns_correct_zm(FaceSet<T> U, FaceSet<T> Ut, FaceSet<T> Us,
                                                              const T *__restrict__ C, const T *__restrict__ Pn,
                                                              const T *__restrict__ P0, const T *__restrict__ P1,
-                                                             NsGrid g, NsCoef<T> k, int with_ut, int zc) {
+                                                             NsGrid g, NsCoef<T> k, int with_ut, int zc, int runs) {
   constexpr int NF = EQ ? 1 : 3;                              // p^(n+1), p^, C
   __shared__ T s[2][NF][(kCy + 1) * kCp];
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const int tiles_x = nx / kCx, tiles_y = ny / kCy;
-  int b = (int)blockIdx.x;
+  int b = runs ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const int bx = b % tiles_x;
   b /= tiles_x;
   const int by = b % tiles_y;
@@ -775,6 +776,7 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
   const T *C = (const T *)p.C[cur];
   const FaceSet<T> U = faces<T>(p.F, p.d), Us = faces<T>(p.Us, p.d), Nh = faces<T>(p.Nh, p.d);
   const FaceSet<T> Af = faces<T>(p.Af, p.d);
+  const int runs = tiles_in_runs<T>(p);   // tiles of the marching kernels dealt in runs per die
   const bool with_ut = p.Ut[0] != nullptr;
   const bool eq = p.rho1 == p.rho2;   // equal densities: no term in p^, rho_f a constant
   const FaceSet<T> Ut = with_ut ? faces<T>(p.Ut, p.d) : U;
@@ -792,10 +794,10 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
       const T inv_rf = (T)(1.0 / (0.5 * (p.rho1 + p.rho2)));
       if (eq)
         hipLaunchKernelGGL((k_ns_predict_zm<T, true>), dim3(nbe), dim3(kEThreads), predict_lds<T>(), p.stream, U, C,
-                           (const T *)p.W, Nh, Af, Us, g, k, q, inv_rf, first, zc);
+                           (const T *)p.W, Nh, Af, Us, g, k, q, inv_rf, first, zc, runs);
       else
         hipLaunchKernelGGL((k_ns_predict_zm<T, false>), dim3(nbe), dim3(kEThreads), predict_lds<T>(), p.stream, U, C,
-                           (const T *)p.W, Nh, Af, Us, g, k, q, inv_rf, first, zc);
+                           (const T *)p.W, Nh, Af, Us, g, k, q, inv_rf, first, zc, runs);
     } else
       hipLaunchKernelGGL((k_ns_predict<T, 3>), dim3(nb), dim3(kNsThreads), 0, p.stream, U, C, (const T *)p.W, Nh, Af,
                          Us, g, k, first, wk);
@@ -828,7 +830,7 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
         const int zc = march_planes(p, kPx * kPy);
         const unsigned nbp = (unsigned)((p.n[0] / kPx) * (p.n[1] / kPy) * (p.n[2] / zc));
         hipLaunchKernelGGL((k_ns_pressure_rhs_zm<T>), dim3(nbp), dim3(kPThreads), 0, p.stream, Us, C,
-                           (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, zc);
+                           (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, zc, runs);
       } else
         hipLaunchKernelGGL((k_ns_pressure_rhs<T, 3>), dim3(nb), dim3(kNsThreads), 0, p.stream, Us, C,
                            (const T *)p.P[0], (const T *)p.P[1], (T *)p.W, g, k, wk);
@@ -847,10 +849,10 @@ hipError_t enqueue_momentum(const Plan &p, int cur, int first, KernelTimer *tm, 
       const unsigned nbc = (unsigned)((p.n[0] / kCx) * (p.n[1] / kCy) * (p.n[2] / zc));
       if (eq)
         hipLaunchKernelGGL((k_ns_correct_zm<T, true>), dim3(nbc), dim3(kCThreads), 0, p.stream, U, Ut, Us, C,
-                           (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, zc);
+                           (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, zc, runs);
       else
         hipLaunchKernelGGL((k_ns_correct_zm<T, false>), dim3(nbc), dim3(kCThreads), 0, p.stream, U, Ut, Us, C,
-                           (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, zc);
+                           (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, zc, runs);
     } else
       hipLaunchKernelGGL((k_ns_correct<T, 3>), dim3(nb), dim3(kNsThreads), 0, p.stream, U, Ut, Us, C,
                          (const T *)p.W, (const T *)p.P[0], (const T *)p.P[1], g, k, with_ut ? 1 : 0, wk);

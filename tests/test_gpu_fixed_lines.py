@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from oracle.geometry import build_tables
+from oracle.geometry import build_tables, face_fractions
 from oracle.solver import derived_coefficients, spectral_solve
 
 pytestmark = pytest.mark.gpu
@@ -68,3 +68,33 @@ def test_default_shapes_fit(chib, n, precision):
     _, al, a = derived_coefficients(prm)
     ref = spectral_solve(Q, grid, al, a)
     assert np.max(np.abs(out - ref)) <= (1e-12 if precision == 64 else 1e-4) * np.max(np.abs(ref))
+
+
+# the divergence of the velocity formed on the way into the x transform (fluids of one density)
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("n", [(64, 64, 64), (128, 64, 64), (512, 64, 64)])
+def test_fixed_lines_of_the_divergence(chib, n, precision):
+    h = 1.0 / 32
+    g = W.Grid(n, (0.0, 0.0, 0.0), tuple(v * h for v in n))
+    prm = W.Params(Cn=1.3 * h, Pe=50.0, Re=10.0, Ca=0.2, theta_deg=60.0, slip_length=0.02, dt=1e-4,
+                   navier_stokes=True, subgrid=10)
+    wall = [W.Shape(W.HALFPLANE, (0.0, 0.0, 2.6 * h, 0.0, 0.0, 1.0))]
+    T = build_tables(g, wall, prm)
+    geo = chib.Geometry.from_tables(g.n, g.lo, g.hi, T.gidx, T.normal, T.dn, T.gamma, T.ap, T.w, T.alpha)
+    geo.set_face_fractions(face_fractions(g, wall, prm))
+    rng = np.random.default_rng(4)
+    C0 = np.tanh(rng.standard_normal(g.shape))
+    faces = [0.1 * rng.standard_normal(g.shape) for _ in range(3)]
+    out = []
+    for drop in (0, 1):
+        st = chib.State(geo, prm, precision)
+        sh = st.shapes()
+        sh[3] = [(2 if n[0] == 512 else 4) - drop, 16 if n[0] == 128 or precision == 32 else 8, 1]
+        st.set_initial(C0, faces)
+        st.set_shapes(sh)
+        print("divergence", n, precision, sh, flush=True)
+        st.step(2)
+        out.append([st.get(f) for f in (chib.FIELD_C, chib.FIELD_U, chib.FIELD_V, chib.FIELD_P)])
+    for a, b in zip(*out):
+        assert np.isfinite(a).all()
+        assert np.array_equal(a, b)

@@ -99,7 +99,8 @@ def kernel_template(name: str, shapes, es: int, n) -> list:
         if u >= 3 and nx in (256, 512):
             L = 2 ** min(max(lt, 1), 3 if nx == 256 else 2)
             return [f"k_rhs_xdht_zm<{t}, {L}, {nx // 256}, {8 if (r == 4 and L == 8) else r}, false>"]
-        return [f"k_rhs_xdht<{t}, 3, {E}, {u}, {max(r, 8)}>"]
+        wide = log2(nx) if nx in (64, 128, 256, 512) else 0
+        return [f"k_rhs_xdht<{t}, 3, {E}, {1 if wide else min(u, 2)}, {8 if r <= 8 else 16}, {wide}>"]
     if name == "rhs_stencil":
         lt = shapes[0][0]
         return [f"k_rhs_xdht_zm<{t}, {2 ** min(max(lt, 1), 3 if nx == 256 else 2)}, {nx // 256}, 8, true>"]

@@ -491,6 +491,23 @@ __device__ __forceinline__ T rhs_2d(T v0, T cxp, T cxm, T cyp, T cym, T f0, T f0
   return cf.pe_cn2 * (cc * cf.inv_dt - A) + lap;
 }
 
+// The same in 3D, for the line-tiled kernels (beyond a wall the caller passes the cell's own C~ and any face).
+template <typename T>
+__device__ __forceinline__ T rhs_3d(T v0, T cxp, T cxm, T cyp, T cym, T czp, T czm, T f0, T f0m, T f1, T f1m, T f2,
+                                    T f2m, bool top, bool bot, T cn, T cp, const RhsCoef<T> &cf) {
+  auto gf = [&](T v) { return (v * v * v - v - cf.S * v) * cf.inv_cn2; };
+  T flux = f0 * (v0 + cxp) - f0m * (cxm + v0);
+  T gsum = gf(cxp) + gf(cxm);
+  flux += f1 * (v0 + cyp) - f1m * (cym + v0);
+  gsum += gf(cyp) + gf(cym);
+  flux += (top ? T(0) : f2 * (v0 + czp)) - (bot ? T(0) : f2m * (czm + v0));
+  gsum += gf(czp) + gf(czm);
+  const T A = flux * T(0.5) * cf.inv_h;
+  const T lap = (gsum - T(6) * gf(v0)) * cf.inv_h2;
+  const T cc = T(2) * cn - T(0.5) * cp;
+  return cf.pe_cn2 * (cc * cf.inv_dt - A) + lap;
+}
+
 template <typename T, int D>
 __device__ __forceinline__ T rhs_at(const T *__restrict__ Cn, const T *__restrict__ Cp, const T *__restrict__ F0,
                                     const T *__restrict__ F1, const T *__restrict__ F2, int i, int j, int k,
@@ -498,7 +515,6 @@ __device__ __forceinline__ T rhs_at(const T *__restrict__ Cn, const T *__restric
   const int nx = dm.nx;
   const int64_t c = (int64_t)i + (int64_t)nx * ((int64_t)j + (int64_t)dm.ny * k);
   auto ct = [&](int64_t q) { return T(2) * Cn[q] - Cp[q]; };
-  auto gf = [&](T v) { return (v * v * v - v - cf.S * v) * cf.inv_cn2; };
   const int64_t rowb = c - i;
   const int ip = (i + 1) & (nx - 1), im = (i - 1) & (nx - 1);
   const T c0 = ct(c);
@@ -509,24 +525,12 @@ __device__ __forceinline__ T rhs_at(const T *__restrict__ Cn, const T *__restric
     const T cyp = ct(cu), cym = ct(cd);
     return rhs_2d(c0, cxp, cxm, cyp, cym, F0[c], F0[rowb + im], F1[c], F1[cd], top, bot, Cn[c], Cp[c], cf);
   }
-  T flux = F0[c] * (c0 + cxp) - F0[rowb + im] * (cxm + c0);
-  T gsum = gf(cxp) + gf(cxm);
-  {
-    const int jp = (j + 1) & (dm.ny - 1), jm = (j - 1) & (dm.ny - 1);
-    const int64_t cyp_i = c + (int64_t)(jp - j) * nx, cym_i = c + (int64_t)(jm - j) * nx;
-    const T cyp = ct(cyp_i), cym = ct(cym_i);
-    flux += F1[c] * (c0 + cyp) - F1[cym_i] * (cym + c0);
-    gsum += gf(cyp) + gf(cym);
-    const bool top = (k == dm.nz - 1), bot = (k == 0);
-    const T czp = top ? c0 : ct(c + dm.plane);
-    const T czm = bot ? c0 : ct(c - dm.plane);
-    flux += (top ? T(0) : F2[c] * (c0 + czp)) - (bot ? T(0) : F2[c - dm.plane] * (czm + c0));
-    gsum += gf(czp) + gf(czm);
-  }
-  const T A = flux * T(0.5) * cf.inv_h;
-  const T lap = (gsum - T(2 * D) * gf(c0)) * cf.inv_h2;
-  const T cc = T(2) * Cn[c] - T(0.5) * Cp[c];
-  return cf.pe_cn2 * (cc * cf.inv_dt - A) + lap;
+  const int jp = (j + 1) & (dm.ny - 1), jm = (j - 1) & (dm.ny - 1);
+  const int64_t cyp_i = c + (int64_t)(jp - j) * nx, cym_i = c + (int64_t)(jm - j) * nx;
+  const bool top = (k == dm.nz - 1), bot = (k == 0);
+  const int64_t czp_i = top ? c : c + dm.plane, czm_i = bot ? c : c - dm.plane;
+  return rhs_3d(c0, cxp, cxm, ct(cyp_i), ct(cym_i), ct(czp_i), ct(czm_i), F0[c], F0[rowb + im], F1[c], F1[cym_i],
+                F2[c], F2[czm_i], top, bot, Cn[c], Cp[c], cf);
 }
 
 // Untangles the complex FFT of the pair (a + i b) into the Hartley transforms of a and b:
@@ -538,7 +542,11 @@ __device__ __forceinline__ T hartley_of_pair(T p, T q, T r, T s, int par) {
 
 // ---------------------------------------------------------------------------------------
 // K1: rhs of L consecutive x-lines into LDS, Hartley transform along x, store to W.
-template <typename T, int D, int E, int U = 1, int MAXR = 16>
+// CLN (3D) fixes the line length: a thread then forms 16 bytes of adjacent cells of every RS-th line from
+// 16-byte loads, with the x neighbours from the lanes beside it: 15 requests a thread where the general form
+// makes 20 a cell.  The general form was bound by its requests, this one by the memory round trip: 128^3 FP64
+// 38 -> 28 us (3.6 TB/s over 48 bytes a cell), FP32 26 -> 17; 64^3 10.5 -> 9.1; 128x256x256 155 -> 104.
+template <typename T, int D, int E, int U = 1, int MAXR = 16, int CLN = 0>
 __device__ __forceinline__ void rhs_xdht_body(unsigned char *smem_raw, const T *__restrict__ Cn, const T *__restrict__ Cp,
                                                        const T *__restrict__ F0, const T *__restrict__ F1,
                                                        const T *__restrict__ F2, T *__restrict__ W, Dims dm,
@@ -551,34 +559,72 @@ __device__ __forceinline__ void rhs_xdht_body(unsigned char *smem_raw, const T *
   const int tot = L << dm.lnx;
   const int pitch = line_pitch(nx);
   TilePatch<T, D> patch(rp, line0, L);
-  // U cells per iteration so that their loads are in flight together
-  for (int e0 = threadIdx.x; e0 < tot; e0 += U * blockDim.x) {
-    T q[U];
+  if constexpr (CLN != 0) {
+    constexpr int CP = 16 / (int)sizeof(T), NX = 1 << CLN, RS = CP * kThreads / NX;
+    typedef T FV __attribute__((ext_vector_type(CP)));
+    static_assert(D == 3 && RS >= 1, "fixed-size line");
+    const int i = (threadIdx.x & (NX / CP - 1)) * CP, im = (i - 1) & (NX - 1), ip = (i + CP) & (NX - 1);
+    const int lane = threadIdx.x & 63;
+    const bool first = lane == 0 || i == 0, last = lane == 63 || i + CP == NX;   // no lane of the line beside
+    auto ld = [](const T *a) { return *reinterpret_cast<const FV *>(a); };
+    for (int l = threadIdx.x / (NX / CP); l < L; l += RS) {
+      const int line = line0 + l, j = line & (dm.ny - 1), k = line >> dm.lny;
+      const bool top = k == dm.nz - 1, bot = k == 0;
+      const int64_t row = (int64_t)line << CLN, c = row + i;
+      const int64_t yp = c + ((int64_t)(((j + 1) & (dm.ny - 1)) - j) << CLN);
+      const int64_t ym = c + ((int64_t)(((j - 1) & (dm.ny - 1)) - j) << CLN);
+      const int64_t zp = top ? c : c + dm.plane, zm = bot ? c : c - dm.plane;
+      const FV a0 = ld(Cn + c), b0 = ld(Cp + c), ayp = ld(Cn + yp), byp = ld(Cp + yp), aym = ld(Cn + ym), bym = ld(Cp + ym);
+      const FV azp = ld(Cn + zp), bzp = ld(Cp + zp), azm = ld(Cn + zm), bzm = ld(Cp + zm);
+      const FV f0 = ld(F0 + c), f1 = ld(F1 + c), f1m = ld(F1 + ym), f2 = ld(F2 + c), f2m = ld(F2 + zm);
+      T cl = T(0), fl = T(0), cr = T(0);
+      if (first) {
+        cl = T(2) * Cn[row + im] - Cp[row + im];
+        fl = F0[row + im];
+      }
+      if (last) cr = T(2) * Cn[row + ip] - Cp[row + ip];
+      const FV v = T(2) * a0 - b0, vyp = T(2) * ayp - byp, vym = T(2) * aym - bym;
+      const FV vzp = T(2) * azp - bzp, vzm = T(2) * azm - bzm;
+      const T below = __shfl_up(v[CP - 1], 1), fbelow = __shfl_up(f0[CP - 1], 1), above = __shfl_down(v[0], 1);
+      T *d = s + l * pitch + i + (i >> 4);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * blockDim.x;
-      if (e < tot) {
-        const int l = e >> dm.lnx;
-        const int i = e & (nx - 1);
-        const int line = line0 + l;
-        int j, k;
-        if (D == 2) {
-          j = line;
-          k = 0;
-        } else {
-          j = line & (dm.ny - 1);
-          k = line >> dm.lny;
-        }
-        q[u] = rhs_at<T, D>(Cn, Cp, F0, F1, F2, i, j, k, dm, cf);
+      for (int m = 0; m < CP; ++m) {
+        const T cxm = m ? v[m ? m - 1 : 0] : (first ? cl : below), fm = m ? f0[m ? m - 1 : 0] : (first ? fl : fbelow);
+        const T cxp = m < CP - 1 ? v[m < CP - 1 ? m + 1 : 0] : (last ? cr : above);
+        d[m] = rhs_3d(v[m], cxp, cxm, vyp[m], vym[m], vzp[m], vzm[m], f0[m], fm, f1[m], f1m[m], f2[m], f2m[m], top, bot,
+                      a0[m], b0[m], cf);
       }
     }
+  } else {
+    // U cells per iteration so that their loads are in flight together
+    for (int e0 = threadIdx.x; e0 < tot; e0 += U * blockDim.x) {
+      T q[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * blockDim.x;
-      if (e < tot) {
-        const int l = e >> dm.lnx;
-        const int i = e & (nx - 1);
-        s[l * pitch + i + (i >> 4)] = q[u];
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * blockDim.x;
+        if (e < tot) {
+          const int l = e >> dm.lnx;
+          const int i = e & (nx - 1);
+          const int line = line0 + l;
+          int j, k;
+          if (D == 2) {
+            j = line;
+            k = 0;
+          } else {
+            j = line & (dm.ny - 1);
+            k = line >> dm.lny;
+          }
+          q[u] = rhs_at<T, D>(Cn, Cp, F0, F1, F2, i, j, k, dm, cf);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * blockDim.x;
+        if (e < tot) {
+          const int l = e >> dm.lnx;
+          const int i = e & (nx - 1);
+          s[l * pitch + i + (i >> 4)] = q[u];
+        }
       }
     }
   }
@@ -602,14 +648,18 @@ __device__ __forceinline__ void rhs_xdht_body(unsigned char *smem_raw, const T *
   }
 }
 
-template <typename T, int D, int E, int U = 1, int MAXR = 16>
+template <typename T, int D, int E, int U = 1, int MAXR = 16, int CLN = 0>
 __global__ __launch_bounds__(kThreads) void k_rhs_xdht(const T *__restrict__ Cn, const T *__restrict__ Cp,
                                                        const T *__restrict__ F0, const T *__restrict__ F1,
                                                        const T *__restrict__ F2, T *__restrict__ W, Dims dm,
                                                        RhsCoef<T> cf, int logL, const T *__restrict__ twr,
                                                        const T *__restrict__ twi, RhsPatch<T> rp) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  rhs_xdht_body<T, D, E, U, MAXR>(smem_raw, Cn, Cp, F0, F1, F2, W, dm, cf, logL, twr, twi, xcd_tile(blockIdx.x, gridDim.x),
+  if constexpr (CLN != 0) {
+    dm.lnx = CLN;
+    dm.nx = 1 << CLN;
+  }
+  rhs_xdht_body<T, D, E, U, MAXR, CLN>(smem_raw, Cn, Cp, F0, F1, F2, W, dm, cf, logL, twr, twi, xcd_tile(blockIdx.x, gridDim.x),
                                   rp);
 }
 
@@ -2787,11 +2837,11 @@ hipError_t launch_neumann(const Plan &p, const Plan::Shape &sh) {
   return hipGetLastError();
 }
 
-template <typename T, int D, int U, int R>
+template <typename T, int D, int U, int R, int CLN = 0>
 void launch_rhs_variant(const Plan &p, const T *Cn, const T *Cp, int logL, unsigned nb, size_t lds) {
   const Dims dm = make_dims(p);
   const RhsCoef<T> cf = make_coef<T>(p);
-  hipLaunchKernelGGL((k_rhs_xdht<T, D, tile_elems<T>(), U, R>), dim3(nb), dim3(kThreads), lds, p.stream, Cn, Cp,
+  hipLaunchKernelGGL((k_rhs_xdht<T, D, tile_elems<T>(), U, R, CLN>), dim3(nb), dim3(kThreads), lds, p.stream, Cn, Cp,
                      (const T *)adv_face(p, 0), (const T *)adv_face(p, 1), (const T *)(D == 3 ? adv_face(p, 2) : adv_face(p, 1)), (T *)p.W, dm, cf,
                      logL, (const T *)p.twr[0], (const T *)p.twi[0], make_patch<T>(p));
 }
@@ -2830,6 +2880,9 @@ void launch_zm_variant(const Plan &p, const T *Cn, const T *Cp, int zc_log) {
                      (const T *)adv_face(p, 0), (const T *)adv_face(p, 1), (const T *)adv_face(p, 2), (T *)p.W, dm, cf, zc_log,
                      (const T *)p.twr[0], (const T *)p.twi[0], make_patch<T>(p));
 }
+
+// Whether the line-tiled rhs has a fixed-size form of this grid's lines.
+inline bool rhs_wide(const Plan &p) { return p.d == 3 && p.logn[0] >= 6 && p.logn[0] <= 9; }
 
 // Whether pass 0 in this shape takes the z-march, whose patch comes as dq per entry.
 inline bool rhs_reads_dq(const Plan &p, const Plan::Shape &sh) { return p.d == 3 && sh.unroll >= 3 && zm_ok(p); }
@@ -2895,6 +2948,21 @@ hipError_t launch_rhs(const Plan &p, const T *Cn, const T *Cp, const Plan::Shape
   const unsigned nb = (unsigned)(lines >> logL);
   const size_t lds = (size_t)(1 << logL) * line_pitch(p.n[0]) * sizeof(T);
   const bool r8 = sh.radix <= 8, u2 = sh.unroll >= 2;
+  if constexpr (D == 3) {
+    if (rhs_wide(p)) {
+      switch (p.logn[0] * 2 + r8) {
+        case 12: launch_rhs_variant<T, D, 1, 16, 6>(p, Cn, Cp, logL, nb, lds); break;
+        case 13: launch_rhs_variant<T, D, 1, 8, 6>(p, Cn, Cp, logL, nb, lds); break;
+        case 14: launch_rhs_variant<T, D, 1, 16, 7>(p, Cn, Cp, logL, nb, lds); break;
+        case 15: launch_rhs_variant<T, D, 1, 8, 7>(p, Cn, Cp, logL, nb, lds); break;
+        case 16: launch_rhs_variant<T, D, 1, 16, 8>(p, Cn, Cp, logL, nb, lds); break;
+        case 17: launch_rhs_variant<T, D, 1, 8, 8>(p, Cn, Cp, logL, nb, lds); break;
+        case 18: launch_rhs_variant<T, D, 1, 16, 9>(p, Cn, Cp, logL, nb, lds); break;
+        default: launch_rhs_variant<T, D, 1, 8, 9>(p, Cn, Cp, logL, nb, lds); break;
+      }
+      return hipGetLastError();
+    }
+  }
   if (r8 && u2) launch_rhs_variant<T, D, 2, 8>(p, Cn, Cp, logL, nb, lds);
   else if (r8) launch_rhs_variant<T, D, 1, 8>(p, Cn, Cp, logL, nb, lds);
   else if (u2) launch_rhs_variant<T, D, 2, 16>(p, Cn, Cp, logL, nb, lds);
@@ -3080,9 +3148,11 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm, StepLink *link)
 // 512x256 FP64 49 -> 28 us, 1024x512 FP32 85 -> 40 us.  Lines of 64 to 512 points take the width of their
 // fixed-size instance from 128 tiles on, which saves more than the emptier chip costs (64^3 38 -> 34 us with
 // 256 tiles instead of 1024, 64x64x32 33.9 -> 31.8 with 128).
-// rhs, 3D: the z-march reads C once instead of three times and wins from 2^22 cells (256x128x128 FP64 66 us
-// line-tiled, 63 marching; 256x128x64 43 and 46; 512x256x128 296 and 210), with the longest march that
-// leaves 512 workgroups (1024 in FP32, whose planes are half as long in flight).  rhs, 2D: the y-march for
+// rhs, 3D: the z-march reads C once instead of three times and wins from 2^23 cells (256x256x128 FP64 123 us
+// line-tiled, 88 marching; 256x128x128 45 and 51 and the march's dq list 5 more, FP32 31 and 37; 512x128x128
+// 137 and 105), with the longest march that leaves 512 workgroups (1024 in FP32, whose planes are half as long
+// in flight).  Line-tiled, 1024 cells a tile (FP32 2048) beat more and fewer: 128^3 FP64 39, 29.0, 28.1 and
+// 29.2 us at 2, 4, 8 and 16 lines, 128x256x256 122, 104 and 108 at 4, 8 and 16, 64^3 12.3 and 9.1 at 2 and 4.  rhs, 2D: the y-march for
 // all widths it serves, at one radix, so that a batch of uneven sizes shares its kernels.
 // FP32 keeps the transforms at radix 16 and the rhs at 8: fewer stages round less, and rounding is what limits
 // it (64^3 coupled, 10 steps: u off by 2.2e-6 with the solve at radix 8, 1.3e-6 at 16).
@@ -3109,14 +3179,18 @@ void default_shapes(Plan &p) {
   const int hl = max_log_lines(p, E);
   // radix by line length: 8 where its stages divide the line evenly, else 16 (fewer stages)
   auto radix = [](int logn) { return sizeof(T) == 8 && (logn == 8 || logn % 3 == 0 || logn == 5) ? 8 : 16; };
-  if (zm_ok(p) && p.N >= (int64_t(1) << 22)) {
+  if (zm_ok(p) && p.N >= (int64_t(1) << 23)) {
     const int L = sizeof(T) == 8 ? (p.n[0] == 512 ? 1 : 2) : (p.n[0] == 512 ? 2 : 3);
     int zc = 5;
     const int64_t want = sizeof(T) == 8 ? 512 : 1024;
     while (zc > 3 && ((int64_t)(p.n[1] >> L) * (p.n[2] >> zc)) < want) --zc;
     p.shape[0] = {L, sizeof(T) == 4 ? 8 : 4, zc};
   } else {
-    p.shape[0] = {height(lines, hl), 8, p.n[0] >= 256 ? 2 : 1};
+    // two passes of the block over the tile's cells (see rhs_xdht_body), one on grids of few lines
+    const int cap = rhs_wide(p) ? ilog2c(8192 / (int)sizeof(T)) - p.logn[0] : hl;
+    int l = rhs_wide(p) && p.n[0] <= 128 ? 2 : 1;
+    while (l < cap && (lines >> (l + 1)) >= (rhs_wide(p) ? 512 : 1024)) ++l;
+    p.shape[0] = {clamp_log(l, hl), 8, p.n[0] >= 256 ? 2 : 1};
   }
   const int cy = max_log_cols(p, p.n[1], E), cz = max_log_cols(p, p.n[2], E);
   auto width = [&](int64_t items, int logn, int wd, int hi) {

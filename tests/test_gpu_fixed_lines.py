@@ -5,7 +5,7 @@ import pytest
 
 import workloads as W
 from oracle.geometry import build_tables, face_fractions
-from oracle.solver import derived_coefficients, spectral_solve
+from oracle.solver import OracleState, derived_coefficients, spectral_solve
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -98,3 +98,33 @@ def test_fixed_lines_of_the_divergence(chib, n, precision):
     for a, b in zip(*out):
         assert np.isfinite(a).all()
         assert np.array_equal(a, b)
+
+
+# the line-tiled rhs of 64- to 512-point lines: tiles that fill the block once, twice, or in part.  Three steps
+# at a wall, within 1e-9 of the oracle in FP64 and 1e-4 in FP32 as in the other parity tests
+@pytest.mark.parametrize("precision", [64, 32])
+@pytest.mark.parametrize("n", [(64, 16, 32), (128, 8, 32), (256, 8, 16), (512, 8, 16)])
+def test_rhs_of_fixed_lines(chib, n, precision):
+    h = 1.0 / 32
+    g = W.Grid(n, (0.0, 0.0, 0.0), tuple(v * h for v in n))
+    prm = W.Params(Cn=1.3 * h, Pe=50.0, theta_deg=60.0, slip_length=0.02, dt=1e-4)
+    T = build_tables(g, [W.Shape(W.HALFPLANE, (0.0, 0.0, 2.6 * h, 0.0, 0.0, 1.0))], prm)
+    geo = chib.Geometry.from_tables(g.n, g.lo, g.hi, T.gidx, T.normal, T.dn, T.gamma, T.ap, T.w, T.alpha)
+    C0, _ = W.droplet_field(g, tuple(0.5 * v for v in g.hi), 4.0 * h, prm.Cn, 1e-3, 5)
+    rng = np.random.default_rng(6)
+    faces = [0.05 * rng.standard_normal(g.shape) for _ in range(3)]
+    out = []
+    for lt in (1, 2, 3, 4, 5):
+        st = chib.State(geo, prm, precision)
+        sh = st.shapes()
+        sh[0] = [lt, 8, 1]
+        st.set_shapes(sh)
+        st.set_initial(C0, faces)
+        print("rhs lines", n, precision, lt, flush=True)
+        st.step(3)
+        out.append(np.asarray(st.get(chib.FIELD_C)))
+    orc = OracleState(g, prm, T, C0, faces)
+    orc.step(3)
+    assert np.max(np.abs(out[0] - orc.C)) <= (1e-9 if precision == 64 else 1e-4)
+    for o in out[1:]:
+        assert np.array_equal(o, out[0])

@@ -220,8 +220,8 @@ int ch_ib_state_get(ch_ib_state *st, int field, void *dst, int dst_on_device);
  *   spectral division (Hartley transforms on periodic axes, DCT-II on the bounded axis), the
  *   contact-angle ghost fill of C (section 4.2.2) and, with CH_IB_FLAG_VELOCITY_FILL, the
  *   no-penetration / Navier-slip fill of the faces touching ghosts (section 4.3).
- *   With CH_IB_FLAG_EXPLICIT the step is Eq. ExpCH instead: the chemical potential on every
- *   cell (ghosts take the mirror value, dphi/dn = 0), the rate R = -div(u C) + lap(phi)/Pe, and
+ *   With CH_IB_FLAG_EXPLICIT the step is Eq. ExpCH instead: the chemical potential phi (ghosts take
+ *   the mirror value, dphi/dn = 0), the rate R = -div(u C) + lap(phi)/Pe, and
  *   C^(n+1) = C^n + dt (3/2 R^n - 1/2 R^(n-1)) (second-order Adams-Bashforth; the first step
  *   after the fields are set or loaded without a rate is a forward Euler step), then the same
  *   fills.  The workspace then holds one more field for R.
@@ -295,15 +295,14 @@ int ch_ib_step_timed(ch_ib_state *st, int n_steps, int max_kernels, double *ms_o
  * 2 bounded-axis solve, 3 x transform out) each have a launch shape of three ints:
  * {log2 lines or columns per tile, largest FFT radix (8 or 16; pass 0 also 4, which only the
  * z-marching kernel with up to 4 rows per tile uses, the others taking 8), third field}.  The third field is
- * 1 for passes 1-3; for pass 0 it is the cells in flight per thread (1 or 2) of the line-tiled
- * kernel; for 2D grids with nx <= 1024, 3 selects the y-marching kernel (rows y-1..y+1 held per
+ * 1 for passes 1-3; for pass 0 it is the cells in flight per thread (1 or 2; alike on 3D lines of
+ * 64 to 512 cells) of the line-tiled kernel; for 2D grids with nx <= 1024, 3 selects the y-marching kernel (rows y-1..y+1 held per
  * thread, each value loaded and combined once); for 3D grids, 3..5 select the z-marching kernel
  * (nx = 256 or 512 only) with 2^value planes per workgroup, or 6..8 split that kernel in two: a
  * stencil-only z-march over 2^(value-3) planes writing the right-hand side, then the x transform
  * in place with pass 3's shape (16 more bytes per cell, no FFT inside the stencil loop).  Shapes
  * change speed, never results, apart from rounding: every shape computes the same sums in the
- * same order per element except for the FFT radix and the y-marching kernel (which evaluates the
- * bulk-energy derivative once per value and scales it by 1/Cn^2 inside the Laplacian factor).
+ * same order per element except for the FFT radix.  A new state takes its shapes from its grid's size.
  * ch_ib_tune: times every candidate shape of each pass reps times with HIP events on the state's
  *   buffers (the fields are left unchanged), keeps the fastest and writes the 12 chosen ints to
  *   shapes_out (may be NULL).  Synchronous.
@@ -322,7 +321,8 @@ int ch_ib_set_shapes(ch_ib_state *st, const int *shapes);
  * its own with the same launch shapes (bit for bit).
  * ch_ib_batch_workspace_bytes: device bytes for the descriptors and offsets of n_states states.
  * ch_ib_batch_create: states must be 2D, of one precision, with the static contact-angle
- *   condition (Vs = 0); their pending initial fills are done here.  The batch keeps pointers to
+ *   condition (Vs = 0); their pending initial fills are done here.  Members whose shapes were neither
+ *   tuned nor set take tile heights that suit the whole batch.  The batch keeps pointers to
  *   the states: while it exists, the member states must not be stepped on their own or freed.
  *   device_workspace (caller-owned, 256-byte aligned) must outlive the batch.  EUNSUPPORTED for
  *   3D, dynamic or explicit-scheme states, EINVAL for mixed precisions.  Members with the

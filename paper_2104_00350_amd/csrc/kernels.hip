@@ -3153,7 +3153,7 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm, StepLink *link)
 // 137 and 105), with the longest march that leaves 512 workgroups (1024 in FP32, whose planes are half as long
 // in flight).  Line-tiled, 1024 cells a tile (FP32 2048) beat more and fewer: 128^3 FP64 39, 29.0, 28.1 and
 // 29.2 us at 2, 4, 8 and 16 lines, 128x256x256 122, 104 and 108 at 4, 8 and 16, 64^3 12.3 and 9.1 at 2 and 4.  rhs, 2D: the y-march for
-// all widths it serves, at one radix, so that a batch of uneven sizes shares its kernels.
+// all widths it serves in FP64, at one radix, so that a batch of uneven sizes shares its kernels.
 // FP32 keeps the transforms at radix 16 and the rhs at 8: fewer stages round less, and rounding is what limits
 // it (64^3 coupled, 10 steps: u off by 2.2e-6 with the solve at radix 8, 1.3e-6 at 16).
 template <typename T>
@@ -3167,9 +3167,9 @@ void default_shapes(Plan &p) {
   if (p.d == 2) {
     const int wide = p.n[0] >= 1024 ? 2 : 1;
     const bool f64 = sizeof(T) == 8;
-    // (FP32 with the momentum step: the line-tiled rhs, whose sums round in the order they always have; the
-    // velocities carry 1e-4 of accumulated rounding, which another order changes by a fifth)
-    p.shape[0] = {1, 8, ym_ok(p) && (f64 || !p.ns) ? 3 : 2};
+    // FP32 takes the line-tiled rhs: its requests are half as long and the rows come from L2, so the march gains
+    // nothing (1024x512 34.0 and 33.9 us a step, 512x256 26.4 and 26.6, batch of 32 cases 105 and 110)
+    p.shape[0] = {1, 8, ym_ok(p) && f64 ? 3 : 1};
     p.shape[1] = {4, 16, 1};
     p.shape[2] = {clamp_log(wide, max_log_cols(p, p.n[1], E)), f64 ? 8 : 16, 1};
     p.shape[3] = {1, f64 ? 8 : 16, 1};

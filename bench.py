@@ -130,7 +130,7 @@ def kernel_template(name: str, shapes, es: int, n) -> list:
         return [f"k_ns_pressure_rhs_zm<{t}>"]
     if name == "ghost_dphi":
         # (from the second step of a call on, phi~ at the listed points is part of the face pass)
-        return [f"k_ghost_dg<{t}>", f"k_patch_dq<{t}>"]
+        return [f"k_ghost_dg<{t}, false>", f"k_patch_dq<{t}>"]
     if name == "ghost_fill_C":
         return [f"k_fill_static<{t}>"]
     if name == "ghost_fill_u":

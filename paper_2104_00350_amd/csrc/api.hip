@@ -151,7 +151,7 @@ struct Layout {
 
 struct Offsets {
   size_t C[2], F[3], W, R, alpha, gidx, normal, dn, gamma, ap, w, apg, wg, CGn, CGnm1, CMs, CI, CGnew, UG;
-  size_t dg, pl_cell, pl_ref, pl_row, pl_dq, pt_cell, pt_idx, pt_phi;
+  size_t dg, pl_cell, pl_ref, pl_row, pl_dq, pt_cell, pt_idx, pt_phi, gwords;
   size_t Us[3], Ut[3], Nh[3], Af[3], P[2];
   size_t f_cell, f_axis, f_gL, f_gR, stashL, stashR;
   size_t twr[3], twi[3], dctc, dcts, lam[3], partial, red_out;
@@ -201,6 +201,7 @@ Offsets plan_layout(const ch_ib_geometry &g, int es, int64_t NF, const PatchList
   o.pt_cell = L.off(NU * 4);
   o.pt_idx = L.off((int64_t)pl.pt_idx.size() * 4);
   o.pt_phi = L.off(NU * es);
+  o.gwords = explicit_ab2 && G && chib::explicit_fused(d, g.n, N) ? L.off(N / 64 * sizeof(chib::GhostWord)) : 0;
   o.f_cell = L.off(NF * 4);
   o.f_axis = L.off(NF * 4);
   o.f_gL = L.off(NF * 4);
@@ -421,6 +422,7 @@ extern "C" int ch_ib_state_create(const ch_ib_grid *grid, const ch_ib_geometry *
   p.pt_cell = (const int *)(W0 + o.pt_cell);
   p.pt_idx = (const int *)(W0 + o.pt_idx);
   p.pt_phi = W0 + o.pt_phi;
+  p.gwords = o.gwords ? (const chib::GhostWord *)(W0 + o.gwords) : nullptr;
   p.NF = NF;
   p.f_cell = (const int *)(W0 + o.f_cell);
   p.f_axis = (const int *)(W0 + o.f_axis);
@@ -517,6 +519,17 @@ extern "C" int ch_ib_state_create(const ch_ib_grid *grid, const ch_ib_geometry *
     e = hipMemcpyAsync((void *)p.pt_cell, pl.pt_cell.data(), pl.pt_cell.size() * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
       e = hipMemcpyAsync((void *)p.pt_idx, pl.pt_idx.data(), pl.pt_idx.size() * 4, hipMemcpyHostToDevice, s);
+  }
+  std::vector<chib::GhostWord> gwords;
+  if (p.gwords && e == hipSuccess) {
+    gwords.assign((size_t)(p.N / 64), chib::GhostWord{0, 0, 0});
+    for (int64_t i = G - 1; i >= 0; --i) {
+      chib::GhostWord &w = gwords[(size_t)(geom->gidx[i] >> 6)];
+      w.bits |= uint64_t(1) << (geom->gidx[i] & 63);
+      w.base = (int)i;
+    }
+    e = hipMemcpyAsync((void *)p.gwords, gwords.data(), gwords.size() * sizeof(chib::GhostWord),
+                       hipMemcpyHostToDevice, s);
   }
   if (NF && e == hipSuccess) {
     e = hipMemcpyAsync((void *)p.f_cell, fl.cell.data(), NF * 4, hipMemcpyHostToDevice, s);

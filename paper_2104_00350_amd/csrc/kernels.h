@@ -7,10 +7,24 @@
 
 namespace chib {
 
-// Everything one step needs, as plain values and device pointers (element type T chosen
-// by the launcher: double for precision 64, float for precision 32).
 constexpr int kGhostSlots = 16;   // lanes (and table slots) per ghost in the ghost kernels
 
+// The ghosts among 64 consecutive cells: one bit each, and the index of the first of them.
+struct GhostWord {
+  uint64_t bits;
+  int base, pad;
+};
+
+// Whether the explicit step forms phi on the way: 3D grids of whole 64 x 8 tiles, from a million cells on
+// (256^3 FP64 336 -> 252 us a step).  Below, phi's pass runs through the caches and forming it on the way gains
+// less and less: 128x64x64 FP64 24.3 us a step with phi as a field and 20.2 without, 64^3 19.7 and 19.3,
+// 64x32x32 15.1 and 18.2.
+inline bool explicit_fused(int d, const int *n, int64_t cells) {
+  return d == 3 && n[0] % 64 == 0 && n[1] % 8 == 0 && cells >= (int64_t(1) << 20);
+}
+
+// Everything one step needs, as plain values and device pointers (element type T chosen
+// by the launcher: double for precision 64, float for precision 32).
 struct Plan {
   int d = 2;
   int n[3] = {1, 1, 1};
@@ -73,6 +87,9 @@ struct Plan {
   const int *pl_ref = nullptr;     // [2d+1][NP]: own ghost index, then the ghost at +e_a and -e_a per axis, or -1
   const int *pl_row = nullptr;     // [rows + 1]
   void *pl_dq = nullptr;           // [NP]
+
+  // explicit step that forms phi on the way: the ghosts of every 64 consecutive cells
+  const GhostWord *gwords = nullptr;   // [N / 64], or nullptr
 
   // faces touching ghosts (velocity fill)
   int64_t NF = 0;

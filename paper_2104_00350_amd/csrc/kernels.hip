@@ -1738,20 +1738,21 @@ __global__ __launch_bounds__(kThreads) void k_point_phit(const T *__restrict__ C
   if (u < nu) pt_phi[u] = phit_at(Cn, Cp, (int64_t)pt_cell[u], dm, d, cn2, inv_h2);
 }
 
-template <typename T>
+// MIRROR (the explicit step): phi_M alone, the ghost's own value neither read nor needed.
+template <typename T, bool MIRROR = false>
 __global__ __launch_bounds__(kThreads) void k_ghost_dg(const T *__restrict__ pt_phi, const int *__restrict__ pt_idx,
                                                        const T *__restrict__ w, T *__restrict__ dg, int64_t G, int K,
                                                        T inv_cn2) {
   const int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
   const int sl = threadIdx.x & 15;
   T v = T(0);
-  if (g < G && sl <= 2 * K) {
+  if (g < G && (MIRROR ? sl < 2 * K : sl <= 2 * K)) {
     const int64_t i = g * kGhostSlots + sl;
     const T coef = sl < 2 * K ? (sl < K ? T(2) : T(-1)) * w[i] : T(-1);
     v = coef * pt_phi[pt_idx[i]];
   }
   const T sum = group16_sum(v);
-  if (g < G && sl == 0) dg[g] = sum * inv_cn2;
+  if (g < G && sl == 0) dg[g] = MIRROR ? sum : sum * inv_cn2;
 }
 
 template <typename T>
@@ -2170,27 +2171,31 @@ __global__ __launch_bounds__(kThreads) void k_phi_zm(const T *__restrict__ C, T 
 // goes to LDS with a two-cell x/y halo; plane z+1 of phi is formed from it for the tile and its one-cell
 // ring (the threads that bring a ring cell keep that column too) and goes to LDS in turn; plane z is
 // advanced from phi and C in LDS and the z neighbours in registers.  Four slots of C and three of phi
-// leave one barrier per plane: a slot is rewritten two barriers after its last read.  phi is the raw
-// C^3 - C - Cn^2 lap C everywhere; the mirror value at the ghosts enters through the sparse patch
-// (k_patch_apply).  256^3 FP64: phi 62, its ghosts 7 and update 217 us before, 198 us with the patch here.
-constexpr int kXx = 64, kXy = 8, kXThreads = kXx * kXy;
+// leave one barrier per plane: a slot is rewritten two barriers after its last read.  At the ghosts the
+// mirror value takes phi's place (one word of 64 cells' bits per row and plane says where, and which ghost the
+// first of them is), so that C inside the solid, which phi at a ghost would read, reaches no fluid cell and
+// the rate is rounded once, as with phi as a field.  256^3 FP64: phi 62, its ghosts 7 and update 217 us before,
+// 203 us here (moving 1.34 times its bytes).
+constexpr int kXx = 64, kXy = 8, kXThreads = kXx * kXy;        // (explicit_fused asks for whole tiles)
 constexpr int kXcp = kXx + 4, kXpp = kXx + 2;                  // row pitch of C and of phi
 constexpr int kXcPlane = kXcp * (kXy + 4), kXpPlane = kXpp * (kXy + 2);
 constexpr int kXRing1 = kXpPlane - kXThreads;                  // cells around the tile where phi is formed
 constexpr int kXHalo = kXcPlane - kXThreads;                   // cells around the tile whose C is held
 static_assert(kXHalo <= kXThreads, "one halo cell per thread");
 
-template <typename T>
+template <typename T, bool GHOSTS>
 __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__ C, const T *__restrict__ F0,
                                                            const T *__restrict__ F1, const T *__restrict__ F2,
                                                            T *__restrict__ R, T *__restrict__ Cnext, Dims dm, T cn2,
-                                                           T half_inv_h, T inv_h2, T inv_pe, T dt, int first, int zc, int runs) {
+                                                           T half_inv_h, T inv_h2, T inv_pe, T dt, int first, int zc,
+                                                           int runs, const GhostWord *__restrict__ g_word,
+                                                           const T *__restrict__ g_phi) {
   __shared__ T sc[4][kXcPlane];
   __shared__ T sp[3][kXpPlane];
   const int nx = dm.nx, ny = dm.ny, nz = dm.nz;
-  const int nbx = nx / kXx, nby = ny / kXy;
+  const int lbx = dm.lnx - 6, lby = dm.lny - 3;                // tiles per axis (log2; every n is a power of two)
   const int b = runs ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int x0 = (b % nbx) * kXx, y0 = ((b / nbx) % nby) * kXy, z0 = b / (nbx * nby) * zc;
+  const int x0 = (b & ((1 << lbx) - 1)) * kXx, y0 = ((b >> lbx) & ((1 << lby) - 1)) * kXy, z0 = (b >> (lbx + lby)) * zc;
   const int tid = threadIdx.x, tx = tid & (kXx - 1), ty = tid / kXx;
   const int col = x0 + tx + ((y0 + ty) << dm.lnx);
   const int ic = (ty + 2) * kXcp + tx + 2, ip = (ty + 1) * kXpp + tx + 1;
@@ -2212,10 +2217,23 @@ __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__
   const int colxm = ((x0 - 1) & (nx - 1)) + ((y0 + ty) << dm.lnx);   // (the first lane of each row asks for it)
   // planes beyond the walls reflect onto the boundary plane
   auto zb = [&](int z) { return (int64_t)(z < 0 ? 0 : (z >= nz ? nz - 1 : z)) * dm.plane; };
-  T cn, hn = T(0);                                             // the plane of C in flight
+  T cn, hn = T(0);                                             // the plane of C in flight, with its ghosts
+  GhostWord gw{}, hw{};
   auto request_c = [&](int z) {
-    cn = C[zb(z) + col];
-    if (halo) hn = C[zb(z) + hcol];
+    const int64_t b = zb(z);
+    if constexpr (GHOSTS) gw = g_word[(b + col) >> 6];
+    cn = C[b + col];
+    if (halo) {
+      if constexpr (GHOSTS) hw = g_word[(b + hcol) >> 6];
+      hn = C[b + hcol];
+    }
+  };
+  // phi's mirror value where the cell at column c is a ghost
+  auto mirror = [&](const GhostWord &w, int c, T &v) {
+    const uint64_t bit = uint64_t(1) << (c & 63);
+    const bool is = w.bits & bit;
+    if (is) v = g_phi[w.base + __popcll(w.bits & (bit - 1))];
+    return is;
   };
   T f0, f0l, f1, f1m, f2, rz;                                  // faces and rate of the plane to advance
   auto request_f = [&](int z) {
@@ -2239,6 +2257,12 @@ __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__
   request_c(z0 - 1);
   c1 = cn;
   h1 = hn;
+  T gv = T(0), ghv = T(0);                                     // phi's mirror value at ghosts of plane z+1
+  bool own_g = false, ring_g = false;
+  if constexpr (GHOSTS) {
+    own_g = mirror(gw, col, gv);
+    ring_g = ring && mirror(hw, hcol, ghv);
+  }
   sc[(z0 + 3) & 3][ic] = c1;
   if (halo) sc[(z0 + 3) & 3][hic] = h1;
   request_c(z0);
@@ -2247,15 +2271,25 @@ __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__
   int s1 = 2;                                                  // slot of phi plane z+1
   __syncthreads();
   for (int z = z0 - 2; z < z0 + zc; ++z) {
-    // plane z+2 of C arrives; phi of plane z+1
+    // plane z+2 of C arrives, and its ghosts' phi is requested; phi of plane z+1
     const T c2 = cn, h2 = hn;
+    const T mo = gv, mh = ghv;
+    const bool is_o = own_g, is_h = ring_g;
+    if constexpr (GHOSTS) {
+      own_g = mirror(gw, col, gv);
+      ring_g = ring && mirror(hw, hcol, ghv);
+    }
     T *cs = sc[(z + 6) & 3];
     cs[ic] = c2;
     if (halo) cs[hic] = h2;
     const T *cc = sc[(z + 5) & 3];
-    const T p1 = phi_of(cc, ic, c0, c1, c2);
+    T p1 = phi_of(cc, ic, c0, c1, c2);
+    if (is_o) p1 = mo;
     sp[s1][ip] = p1;
-    if (ring) sp[s1][hip] = phi_of(cc, hic, h0, h1, h2);
+    if (ring) {
+      const T ph = phi_of(cc, hic, h0, h1, h2);
+      sp[s1][hip] = is_h ? mh : ph;
+    }
     if (z + 1 < z0 + zc) request_c(z + 3);
     if (z == z0 - 1) request_f(z0);
     __syncthreads();
@@ -2291,32 +2325,6 @@ __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__
   }
 }
 
-// The mirror value of phi at the ghosts in the explicit step, as the change it makes: with
-// dg_G = phi_M - phi_G, the rate gains dq/Pe and C^(n+1) its share of it (dq as in k_patch_dq).
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_patch_apply(const int *__restrict__ cell, const int *__restrict__ ref,
-                                                          const T *__restrict__ dg, T *__restrict__ R,
-                                                          T *__restrict__ Cnext, int64_t np, int nref, T twod, T inv_h2,
-                                                          T inv_pe, T cdt) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= np) return;
-  const int c = cell[e], own = ref[e];
-  T acc = T(0);
-  for (int j = 1; j < nref; ++j) {
-    const int id = ref[(int64_t)j * np + e];
-    if (id >= 0) acc += dg[id];
-  }
-  if (own >= 0) acc -= twod * dg[own];
-  const T r = acc * inv_h2 * inv_pe;
-  R[c] += r;
-  Cnext[c] += cdt * r;
-}
-
-// From a million cells on: below, the three launches of the patch cost more than phi's pass through the
-// caches (128x64x128 FP64 36.7 -> 32.7 us a step, 64x64x128 26.2 -> 28.0, 64^3 21.8 -> 26.4).
-inline bool explicit_zm_ok(const Plan &p) {
-  return p.d == 3 && p.n[0] % kXx == 0 && p.n[1] % kXy == 0 && p.N >= (int64_t(1) << 20);
-}
 // planes per workgroup: 16 (each chunk reads four more of C; 256^3 FP64 206 us, 210 with 32), fewer where
 // that leaves under 512 workgroups
 inline int explicit_zm_planes(const Plan &p) {
@@ -2615,20 +2623,24 @@ hipError_t launch_dphi(const Plan &p, const T *Cn, const T *Cp) {
 }
 
 // dg of every ghost from C^n, C^(n-1) (before the rhs pass of a semi-implicit step); need_dq: then dq
-// of every patched cell; dphi_done: launch_dphi's kernel ran at the end of the step before.  3D explicit
-// steps take C^n twice (then C~ = C^n) and dg without the factor 1/Cn^2.
+// of every patched cell; dphi_done: launch_dphi's kernel ran at the end of the step before.  mirror: 3D
+// explicit steps take C^n twice (then C~ = C^n) and phi_M in dg's place.
 template <typename T>
 hipError_t launch_ghost_patch(const Plan &p, const T *Cn, const T *Cp, bool need_dq, bool dphi_done = false,
-                              bool phi_units = false) {
+                              bool mirror = false) {
   if (!has_patch(p)) return hipSuccess;
   if (!dphi_done) {
     hipError_t e = launch_dphi<T>(p, Cn, Cp);
     if (e != hipSuccess) return e;
   }
-  if (dphi_points(p))
-    hipLaunchKernelGGL((k_ghost_dg<T>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream,
-                       (const T *)p.pt_phi, p.pt_idx, (const T *)p.wg, (T *)p.dg, p.G, p.K,
-                       phi_units ? T(1) : (T)(1.0 / (p.Cn * p.Cn)));
+  if (dphi_points(p)) {
+#define CHIB_GHOST_DG(M)                                                                                       \
+  hipLaunchKernelGGL((k_ghost_dg<T, M>), dim3(blocks_for(p.G * 16)), dim3(kThreads), 0, p.stream,              \
+                     (const T *)p.pt_phi, p.pt_idx, (const T *)p.wg, (T *)p.dg, p.G, p.K, (T)(1.0 / (p.Cn * p.Cn)))
+    if (mirror) CHIB_GHOST_DG(true);
+    else CHIB_GHOST_DG(false);
+#undef CHIB_GHOST_DG
+  }
   if (need_dq)
     hipLaunchKernelGGL((k_patch_dq<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, p.pl_ref,
                        (const T *)p.dg, (T *)p.pl_dq, p.NP, 2 * p.d + 1, (T)(2 * p.d), (T)(1.0 / (p.h * p.h)));
@@ -3531,8 +3543,8 @@ hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer 
   const Dims dm = make_dims(p);
   const T hih = (T)(0.5 / p.h), ih2 = (T)(1.0 / (p.h * p.h)), ipe = (T)(1.0 / p.Pe), dt = (T)p.dt;
   const T cn2 = (T)(p.Cn * p.Cn);
-  const bool patch = p.G == 0 || (has_patch(p) && dphi_points(p));
-  if (explicit_zm_ok(p) && patch) {
+  const bool mirror = p.G == 0 || (has_patch(p) && dphi_points(p) && p.gwords);
+  if (explicit_fused(p.d, p.n, p.N) && mirror) {
     if (p.G) {
       mark("ghost_dphi");
       if (e == hipSuccess) e = launch_ghost_patch<T>(p, Cn, Cn, false, link && link->dphi_done, true);
@@ -3542,13 +3554,14 @@ hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer 
       const int zc = explicit_zm_planes(p);
       // (in runs up to half that size in FP64: 128^3 45.7 -> 42.5 us a step, 256x256x128 117.7 -> 118.9)
       const unsigned nb = (unsigned)((p.n[0] / kXx) * (p.n[1] / kXy) * (p.n[2] / zc));
-      hipLaunchKernelGGL((k_explicit_zm<T>), dim3(nb), dim3(kXThreads), 0, p.stream, Cn, (const T *)p.F[0],
-                         (const T *)p.F[1], (const T *)p.F[2], (T *)p.R, Cnext, dm, cn2, hih, ih2, ipe, dt, first, zc,
-                         tiles_in_runs<T>(p) && (sizeof(T) == 4 || p.N < (int64_t(1) << 23)));
-      if (p.G)
-        hipLaunchKernelGGL((k_patch_apply<T>), dim3(blocks_for(p.NP)), dim3(kThreads), 0, p.stream, p.pl_cell,
-                           p.pl_ref, (const T *)p.dg, (T *)p.R, Cnext, p.NP, 2 * p.d + 1, (T)(2 * p.d), ih2, ipe,
-                           first ? dt : T(1.5) * dt);
+#define CHIB_EXPLICIT_ZM(GH)                                                                                          \
+  hipLaunchKernelGGL((k_explicit_zm<T, GH>), dim3(nb), dim3(kXThreads), 0, p.stream, Cn, (const T *)p.F[0],          \
+                     (const T *)p.F[1], (const T *)p.F[2], (T *)p.R, Cnext, dm, cn2, hih, ih2, ipe, dt, first, zc,   \
+                     tiles_in_runs<T>(p) && (sizeof(T) == 4 || p.N < (int64_t(1) << 23)), p.gwords,                  \
+                     (const T *)p.dg)
+      if (p.G) CHIB_EXPLICIT_ZM(true);
+      else CHIB_EXPLICIT_ZM(false);
+#undef CHIB_EXPLICIT_ZM
       e = hipGetLastError();
     }
     const NextStep nx{Cnext, Cnext};

@@ -322,8 +322,9 @@ int ch_ib_set_shapes(ch_ib_state *st, const int *shapes);
  * ch_ib_batch_workspace_bytes: device bytes for the descriptors and offsets of n_states states.
  * ch_ib_batch_create: states must be 2D, of one precision, with the static contact-angle
  *   condition (Vs = 0); their pending initial fills are done here.  Members whose shapes were neither
- *   tuned nor set take tile heights that suit the whole batch.  The batch keeps pointers to
- *   the states: while it exists, the member states must not be stepped on their own or freed.
+ *   tuned nor set run in the batch with tile heights that suit it as a whole (their own shapes stay
+ *   as they are, and no result depends on them).  The batch keeps pointers to the states: while it
+ *   exists, the member states must not be stepped on their own or freed.
  *   device_workspace (caller-owned, 256-byte aligned) must outlive the batch.  EUNSUPPORTED for
  *   3D, dynamic or explicit-scheme states, EINVAL for mixed precisions.  Members with the
  *   momentum step (Navier-Stokes coupling, section 4.4) are accepted: the grouped launches cover

@@ -1177,8 +1177,11 @@ static void batch_drop_graphs(ch_ib_batch *b) {
   }
 }
 
-// Uploads descriptors (from each member's current buffer roles) and tile offsets.
+// Uploads descriptors (from each member's current buffer roles) and tile offsets.  Members nobody has set or
+// tuned shapes for run with the tile heights that suit the batch as a whole; their own shapes stay as they are.
 static int batch_upload(ch_ib_batch *b) {
+  int64_t cells = 0;
+  for (const ch_ib_state *s : b->grp) cells += s->plan.N;
   const int n = (int)b->grp.size();
   const size_t db = batch_desc_bytes(b->es);
   std::vector<unsigned char> descs(db * n);
@@ -1188,14 +1191,17 @@ static int batch_upload(ch_ib_batch *b) {
   bool ym_all = true;
   for (int c = 0; c < n; ++c) {
     ch_ib_state *s = b->grp[c];
+    chib::Plan q = s->plan;
     int tiles[NPH];
     size_t l[4];
     if (b->es == 8) {
-      chib::fill_case_desc<double>(s->plan, s->cur, descs.data() + db * c);
-      chib::case_tiles<double>(s->plan, tiles, l);
+      if (s->auto_shapes) chib::batch_heights<double>(q, cells);
+      chib::fill_case_desc<double>(q, s->cur, descs.data() + db * c);
+      chib::case_tiles<double>(q, tiles, l);
     } else {
-      chib::fill_case_desc<float>(s->plan, s->cur, descs.data() + db * c);
-      chib::case_tiles<float>(s->plan, tiles, l);
+      if (s->auto_shapes) chib::batch_heights<float>(q, cells);
+      chib::fill_case_desc<float>(q, s->cur, descs.data() + db * c);
+      chib::case_tiles<float>(q, tiles, l);
     }
     for (int ph = 0; ph < NPH; ++ph) off[ph * (n + 1) + c + 1] = off[ph * (n + 1) + c] + tiles[ph];
     for (int k = 0; k < 4; ++k) lds[k] = std::max(lds[k], l[k]);
@@ -1257,14 +1263,6 @@ extern "C" int ch_ib_batch_create(ch_ib_state *const *states, int n, void *ws, s
   b->ws = (char *)ws;
   b->ws_bytes = bytes;
   b->stream = (hipStream_t)stream;
-  // members nobody has set or tuned shapes for take the tile heights that suit the batch as a whole
-  int64_t cells = 0;
-  for (const ch_ib_state *s : b->grp) cells += s->plan.N;
-  for (ch_ib_state *s : b->grp)
-    if (s->auto_shapes) {
-      if (es == 8) chib::batch_heights<double>(s->plan, cells);
-      else chib::batch_heights<float>(s->plan, cells);
-    }
   // shared kernel choices follow the first grouped member's shapes (so that a batched step is the
   // same computation as stepping each member with those shapes)
   const ch_ib_state *s0 = b->grp.empty() ? states[0] : b->grp[0];

@@ -475,20 +475,26 @@ __host__ __device__ __forceinline__ int col_tile(int N, int B) { return N * B + 
 // with C~ = 2C^n - C^(n-1), C^ = 2C^n - C^(n-1)/2; periodic axes wrap, the bounded (last)
 // axis reflects for the Laplacian and has zero normal velocity on its box walls.
 // The 2D expression on the values of C~ around the cell (v0, x+-1, y+-1, the latter already v0 beyond a
-// wall) and its faces: shared by the line-tiled and the y-marching kernel, which so give the same bits.
+// wall) and its faces: shared by the line-tiled and the y-marching kernel.  Which products join which sums is
+// written out and nothing else is contracted: left to the compiler, the two kernels differed in the last bits,
+// and with them a state stepped alone and in a batch too wide for the march.
 template <typename T>
 __device__ __forceinline__ T rhs_2d(T v0, T cxp, T cxm, T cyp, T cym, T f0, T f0m, T f1, T f1m, bool top, bool bot,
                                     T cn, T cp, const RhsCoef<T> &cf) {
-  auto gf = [&](T v) { return (v * v * v - v - cf.S * v) * cf.inv_cn2; };
-  T flux = f0 * (v0 + cxp) - f0m * (cxm + v0);
-  T gsum = gf(cxp) + gf(cxm);
+#pragma clang fp contract(off)
+  auto bulk = [&](T v) {   // v^3 - v - S v
+#pragma clang fp contract(off)
+    return fma(-cf.S, v, fma(v * v, v, -v));
+  };
+  T flux = fma(f0, v0 + cxp, -(f0m * (cxm + v0)));
   const T ft = f1 * (v0 + cyp), fb = f1m * (cym + v0);
   flux += (top ? T(0) : ft) - (bot ? T(0) : fb);
-  gsum += gf(cyp) + gf(cym);
+  const T gx = fma(bulk(cxp), cf.inv_cn2, bulk(cxm) * cf.inv_cn2);
+  const T gy = fma(bulk(cyp), cf.inv_cn2, bulk(cym) * cf.inv_cn2);
+  const T g0 = bulk(v0) * cf.inv_cn2;
   const T A = flux * T(0.5) * cf.inv_h;
-  const T lap = (gsum - T(4) * gf(v0)) * cf.inv_h2;
-  const T cc = T(2) * cn - T(0.5) * cp;
-  return cf.pe_cn2 * (cc * cf.inv_dt - A) + lap;
+  const T cc = fma(T(2), cn, T(-0.5) * cp);
+  return fma(fma(T(-4), g0, gx + gy), cf.inv_h2, cf.pe_cn2 * fma(cc, cf.inv_dt, -A));
 }
 
 // The same in 3D, for the line-tiled kernels (beyond a wall the caller passes the cell's own C~ and any face).

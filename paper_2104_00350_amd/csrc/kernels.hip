@@ -2710,13 +2710,15 @@ hipError_t launch_xdht(const Plan &p, const T *in, T *out, const Plan::Shape &sh
 #define CHIB_XDHT(...)                                                                                         \
   hipLaunchKernelGGL((k_xdht<__VA_ARGS__>), dim3(nb), dim3(kThreads), lds, p.stream, in, out, p.logn[0], logL, \
                      (const T *)p.twr[0], (const T *)p.twi[0])
-  const bool r8 = sh.radix == 8, fixed = p.logn[0] == 8;
+  // (the fixed-size instances read 16 bytes at a time; a caller's field need only be aligned to its elements)
+  const bool wide = ((uintptr_t)in & 15) == 0;
+  const bool r8 = sh.radix == 8, fixed = wide && p.logn[0] == 8;
   constexpr int RD = fixed_radix<T>();
-  if (p.logn[0] == 6 && logL == 4 && sh.radix == RD) {
+  if (wide && p.logn[0] == 6 && logL == 4 && sh.radix == RD) {
     CHIB_XDHT(T, E, RD, 6, 4);
-  } else if (p.logn[0] == 7 && logL == 4 && !r8) {
+  } else if (wide && p.logn[0] == 7 && logL == 4 && !r8) {
     CHIB_XDHT(T, E, 16, 7, 4);
-  } else if (p.logn[0] == 9 && logL == 2 && sh.radix == RD) {
+  } else if (wide && p.logn[0] == 9 && logL == 2 && sh.radix == RD) {
     CHIB_XDHT(T, E, RD, 9, 2);
   } else if (fixed && logL == 3) {
     if (r8) CHIB_XDHT(T, E, 8, 8, 3);

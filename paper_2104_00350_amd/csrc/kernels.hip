@@ -1801,9 +1801,9 @@ __global__ __launch_bounds__(kThreads) void k_rhs_patch(T *__restrict__ Q, const
 // ghost's own gradient); the remaining blocks take one face per thread.  With the static
 // condition (capillary = 0) the wall equation makes the bracket Kc of Eq. UpdateVtan zero,
 // and no gradient of C is gathered.
-// LONE (the fill on its own, k_vel_ghosts): V_tG is rounded before V_nG n joins it; the joined fills leave
-// the order to the compiler.  (Both as they always were: the slip velocity feeds back into FP32 runs.)
-template <typename T, int D, bool CAP, bool LONE>
+// V_tG is rounded before V_nG n joins it, written out so that the fill alone and joined with the one of C gives
+// the same bits.
+template <typename T, int D, bool CAP>
 __device__ __forceinline__ void vel_ghosts_body(
     const T *__restrict__ C, const T *__restrict__ F0, const T *__restrict__ F1, const T *__restrict__ F2,
     const int *__restrict__ gidx, const T *__restrict__ nrm, const T *__restrict__ dn, const T *__restrict__ gam,
@@ -1893,8 +1893,7 @@ __device__ __forceinline__ void vel_ghosts_body(
     const T VtM = um[a] - VnM * n[a];
     T VtG = VtM * fM;
     if constexpr (CAP) VtG -= Kc * (gI[a] - gIn * n[a]) * fK;
-    if constexpr (LONE) UG[(int64_t)a * G + g] = __builtin_fma(VnG, n[a], VtG);
-    else UG[(int64_t)a * G + g] = VnG * n[a] + VtG;
+    UG[(int64_t)a * G + g] = fma(VnG, n[a], VtG);
   }
 }
 
@@ -1906,7 +1905,7 @@ __global__ __launch_bounds__(kThreads) void k_vel_ghosts(
     int K, const int *__restrict__ f_cell, const int *__restrict__ f_axis, const int *__restrict__ f_gL,
     const int *__restrict__ f_gR, T *__restrict__ stashL, T *__restrict__ stashR, int64_t NF, Dims dm,
     T inv2h, T Cn, T cos_t, T inv_Ca, T inv_mu, T ls, unsigned nbg) {
-  vel_ghosts_body<T, D, CAP, true>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
+  vel_ghosts_body<T, D, CAP>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
                              stashL, stashR, NF, dm, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, nbg, blockIdx.x);
 }
 
@@ -1925,7 +1924,7 @@ __global__ __launch_bounds__(kThreads) void k_fill_static_vel(
     fill_static_body<T>(C, gidx, dn, gam, ap, w, CGn, CGnm1, CMs, G, K, cb, 0, blockIdx.x);
     return;
   }
-  vel_ghosts_body<T, D, false, false>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
+  vel_ghosts_body<T, D, false>(C, F0, F1, F2, gidx, nrm, dn, gam, ap, w, CMs, UG, G, K, f_cell, f_axis, f_gL, f_gR,
                                stashL, stashR, NF, dm, inv2h, Cn, cos_t, inv_Ca, inv_mu, ls, nbg, blockIdx.x - nbc);
 }
 
@@ -3746,7 +3745,7 @@ __global__ __launch_bounds__(kThreads) void kb_fill(const CaseDesc<T> *__restric
     fill_static_body<T>(d.C[1 - parity], d.gidx, d.dn, d.gam, d.ap, d.w, d.CGn, d.CGnm1, d.CMs, d.G, d.K, d.cb, 0, t);
     return;
   }
-  vel_ghosts_body<T, 2, false, false>(d.C[1 - parity], d.F0, d.F1, d.F1, d.gidx, d.normal, d.dn, d.gam, d.ap, d.w, d.CMs,
+  vel_ghosts_body<T, 2, false>(d.C[1 - parity], d.F0, d.F1, d.F1, d.gidx, d.normal, d.dn, d.gam, d.ap, d.w, d.CMs,
                                d.UG, d.G, d.K, d.f_cell, d.f_axis, d.f_gL, d.f_gR, d.stashL, d.stashR, d.NF, d.dm,
                                d.inv2h, d.Cn, d.cos_t, d.inv_Ca, d.inv_mu, d.ls, d.nbg, t - nbc);
 }

@@ -3312,6 +3312,7 @@ hipError_t tune_shapes(Plan &p, int cur, int reps) {
         for (int un : {1, 2, 3, 4, 5, 6, 7, 8}) {
           const int zl = un >= 6 ? un - 3 : un;
           if (radix == 4 && (p.d != 3 || un < 3 || un > 5 || lt > 2)) continue;   // z-march only
+          if (un == 2 && rhs_wide(p)) continue;   // the same kernel as with one cell in flight
           if (un >= 3 && p.d == 2 && (un != 3 || !ym_ok(p))) continue;
           if (un >= 3 && p.d == 3 && (!zm_ok(p) || lt > 3 || (1 << lt) > p.n[1] || (1 << zl) > p.n[2])) continue;
           if (un >= 6 && radix == 16) continue;   // the stencil-only kernel has no transform

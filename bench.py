@@ -26,21 +26,58 @@ HBM_PEAK_GBS = 8000.0
 METRIC = "CH+IB cell-updates/s at 256³; learned/plain speedup at ≤1° contact-angle err"
 
 
-def algorithmic_bytes(name: str, cells: int, d: int, es: int, G: int, NF: int, dynamic: bool = False) -> float:
+def ghost_sets(tabs: dict, n) -> dict:
+    """Sizes of the ghost kernels' work lists, from exported tables: ghosts, the points where phi~ is
+    evaluated (averaging points and ghosts), the cells those evaluations read, the cells the rhs patch
+    changes (ghosts and face neighbours) and the faces touching ghosts."""
+    import numpy as np
+    d = len(n)
+    stride = np.cumprod([1] + list(n[:-1]))
+
+    def neighbours(c, axis, s):
+        q = (c // stride[axis]) % n[axis] + s
+        if axis < d - 1:
+            q %= n[axis]
+        ok = (q >= 0) & (q < n[axis])
+        return (c + (q - (c // stride[axis]) % n[axis]) * stride[axis])[ok]
+
+    def with_neighbours(c):
+        return np.unique(np.concatenate([c] + [neighbours(c, a, s) for a in range(d) for s in (1, -1)]))
+
+    g = np.asarray(tabs["gidx"], dtype=np.int64)
+    points = np.unique(np.concatenate([g, np.asarray(tabs["ap"], dtype=np.int64).reshape(-1)]))
+    return {"ghosts": int(g.size), "points": int(points.size), "point_cells": int(with_neighbours(points).size),
+            "patch": int(with_neighbours(g).size),
+            "faces": sum(int(np.unique(np.concatenate([g, neighbours(g, a, -1)])).size) for a in range(d))}
+
+
+def algorithmic_bytes(name: str, cells: int, d: int, es: int, sets: dict, dynamic: bool = False,
+                      scheme: str = "semi", march: bool = True) -> float:
     """Bytes the method must move per launch of each kernel of a step.
 
     Field passes count each array they must read and write once; the ghost kernels count
     their table entries, gathers and writes per ghost (and per re-interpolated face).  The
     velocity fill gathers the centred velocity at every averaging point (2 face values per
-    axis) and, with the dynamic condition only, the centred gradient of C as well."""
+    axis) and, with the dynamic condition only, the centred gradient of C as well.  Steps follow
+    one another in one call: phi~ at the listed points of the next step is part of the face
+    pass, and ghost_dphi holds what is left of it (scheme: semi, explicit, or momentum for a
+    semi-implicit step whose velocity fill runs in the momentum step; march: the rhs is a
+    z-march, which reads the patch as a list)."""
     K = 2 * d + 1
+    G, NF, NU = sets["ghosts"], sets["faces"], sets["points"]
+    # phi~ per point: its index in, the value out; C^n and C^(n-1) (explicit: C^n) on the cells it reads
+    points = NU * (4 + es) + sets["point_cells"] * es * (1 if scheme == "explicit" else 2)
     if name in ("rhs_xdht", "rhs_stencil"):
         return cells * es * (2 + d + 1)              # C^n, C^(n-1), d face arrays in; Q (or its transform) out
     if name in ("xdht_fwd", "ydht_fwd", "ydht_inv", "neumann_solve", "xdht_out"):
         return cells * es * 2                        # one read, one write
-    if name == "ghost_dphi":                         # per ghost: tables, C^n and C^(n-1) on the cells within
-        U = 2 * d * d + 2 * d + 1                    # two steps of each interpolation point's centre cell
-        return G * (4 + 2 * K * (4 + es) + (2 * U + 2 * d + 1) * 2 * es + es)   # (and the ghost's stencil), dg out
+    if name == "ghost_dphi":                         # phi~ per point in, indices and weights per ghost, dg out;
+        b = NU * es + G * (2 * K * (4 + es) + es)    # (explicit: the mirror value of phi)
+        if scheme != "explicit":
+            b += G * 4                               # the ghost's own point
+            if march:                                # dg and the patched cells' ghosts in, dq out
+                b += G * es + sets["patch"] * (4 * (2 * d + 1) + es)
+        return b
     if name == "ghost_fill_C":
         return G * (4 + 8 * K + es * (7 + 4 * K))
     if name == "ghost_fill_u":
@@ -49,18 +86,19 @@ def algorithmic_bytes(name: str, cells: int, d: int, es: int, G: int, NF: int, d
         return G * per_ghost + NF * per_face
     if name == "phi":                                # explicit step: phi on every cell, mirror value at ghosts
         return cells * es * 2 + G * (4 + 2 * K * (4 + es) + 2 * K * es + es)
-    if name == "explicit_update":                    # C, R, d faces in; C^(n+1), R out (phi formed on the way)
-        return cells * es * (4 + d)
-    if name == "ghost_fills":                        # static: both fills, one launch plus the faces
-        return (algorithmic_bytes("ghost_fill_C", cells, d, es, G, NF, dynamic)
-                + algorithmic_bytes("ghost_fill_u", cells, d, es, G, NF, dynamic))
+    if name == "explicit_update":                    # C, R, d faces in; C^(n+1), R out; from 2^20 cells phi is
+        fused = d == 3 and cells >= 1 << 20          # formed on the way, below it is read
+        return cells * es * (4 + d) + (cells // 64 * 16 + G * es if fused else cells * es)
+    if name == "ghost_fills":                        # static: both fills and the next step's phi~ points
+        return (algorithmic_bytes("ghost_fill_C", cells, d, es, sets, dynamic)
+                + algorithmic_bytes("ghost_fill_u", cells, d, es, sets, dynamic) + points)
     # momentum step (Navier-Stokes coupling)
     if name == "ns_phi":
-        return algorithmic_bytes("phi", cells, d, es, G, NF, dynamic)
+        return algorithmic_bytes("phi", cells, d, es, sets, dynamic)
     if name == "ns_predict":                         # u^n, N^(n-1), alpha_face (d each), C, phi in; u**, N^n out
         return cells * es * (5 * d + 2)
     if name == "ns_vel_fill":
-        return algorithmic_bytes("ghost_fill_u", cells, d, es, G, NF, dynamic)
+        return algorithmic_bytes("ghost_fill_u", cells, d, es, sets, dynamic) + points
     if name == "ns_pressure_rhs":                    # u** (d), C, p^n, p^(n-1) in; rhs out
         return cells * es * (d + 4)
     if name == "ns_poisson":                         # d + (d - 1) passes, one read and one write each
@@ -238,7 +276,7 @@ def sweep_benchmark(chib, torch, steps: int, count: int = 64) -> dict:
             "cases_not_finite": nonfinite}
 
 
-def explicit_benchmark(chib, geo, case, steps: int, precision: int, NF: int, semi_ms: float) -> dict:
+def explicit_benchmark(chib, geo, case, steps: int, precision: int, sets: dict, semi_ms: float) -> dict:
     """The explicit Adams-Bashforth step (Eq. ExpCH) on the same 256^3 workload at a tenth of the
     semi-implicit time step (the paper's factor between the two schemes' stable steps): kernel
     times, bytes, and the time to cover the same simulated time as one semi-implicit step."""
@@ -257,7 +295,7 @@ def explicit_benchmark(chib, geo, case, steps: int, precision: int, NF: int, sem
     cells = case.grid.cells
     kern = {}
     for name, t in ms.items():
-        b = algorithmic_bytes(name, cells, 3, es, st.G, NF, False)
+        b = algorithmic_bytes(name, cells, 3, es, sets, False, "explicit")
         kern[name] = {"ms": round(t, 5), "alg_bytes": int(b), "GB_s": round(b / (t * 1e-3) / 1e9, 1),
                       "frac_of_8TBs": round(b / (t * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     ms_step = 1e3 * wall / steps
@@ -268,7 +306,7 @@ def explicit_benchmark(chib, geo, case, steps: int, precision: int, NF: int, sem
             "time_per_unit_sim_time_vs_semi_implicit": round(10 * ms_step / semi_ms, 3)}
 
 
-def ns_benchmark(chib, case, steps: int, precision: int, semi_ms: float, NF: int, shapes) -> dict:
+def ns_benchmark(chib, case, steps: int, precision: int, semi_ms: float, sets: dict, shapes) -> dict:
     """The coupled order-parameter + momentum step (Navier-Stokes coupling, sections 4.2.3, 4.3 and 4.4) on
     the same 256^3 workload, matched fluids (rho1 = rho2, mu1 = mu2: the explicit viscous term
     then allows the workload's dt), started from rest: kernel times, bytes and the cost over the
@@ -291,7 +329,7 @@ def ns_benchmark(chib, case, steps: int, precision: int, semi_ms: float, NF: int
     cells = g.cells
     kern = {}
     for name, t in ms.items():
-        b = algorithmic_bytes(name, cells, 3, es, st.G, NF, False)
+        b = algorithmic_bytes(name, cells, 3, es, sets, False, "momentum", shapes[0][2] >= 3)
         kern[name] = {"ms": round(t, 5), "alg_bytes": int(b), "GB_s": round(b / (t * 1e-3) / 1e9, 1),
                       "frac_of_8TBs": round(b / (t * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     import numpy as np
@@ -570,21 +608,13 @@ def main() -> int:
 
     cells = g.cells
     es = 8 if args.precision == 64 else 4
-    # faces touching ghosts (the velocity fill's second work list), from the exported tables
+    # the ghost kernels' work lists, from the exported tables
     tabs = geo.export()
-    nx, ny = g.n[0], g.n[1]
-    faces_set = set()
-    for c in tabs["gidx"].tolist():
-        i, j, k = c % nx, (c // nx) % ny, c // (nx * ny)
-        for a_, (di, dj, dk) in enumerate(((1, 0, 0), (0, 1, 0), (0, 0, 1))):
-            cm = ((i - di) % nx) + nx * (((j - dj) % ny) + ny * (k - dk))
-            faces_set.add((a_, cm))
-            faces_set.add((a_, c))
-    NF = len(faces_set)
+    sets = ghost_sets(tabs, tuple(g.n))
 
     kernels = {}
     for name, t in ms.items():
-        b = algorithmic_bytes(name, cells, 3, es, st.G, NF, case.params.Vs > 0)
+        b = algorithmic_bytes(name, cells, 3, es, sets, case.params.Vs > 0, "semi", shapes[0][2] >= 3)
         kernels[name] = {"ms": round(t, 5), "alg_bytes": int(b), "GB_s": round(b / (t * 1e-3) / 1e9, 1)}
     dominant = max(ms, key=ms.get)
     dom = kernels[dominant]
@@ -606,7 +636,7 @@ def main() -> int:
         "data": "synthetic",
         "config": {"workload": f"3D sphere wall r=1 in [-2,2]^3, {args.n}^3 cells, droplet R=0.5 on top, "
                                "Cn=0.015 Pe=200 Ca=0.05 theta=90 ls=0.01 dt=1e-4, velocity fill on",
-                   "grid": list(g.n), "ghosts": st.G, "faces_touching_ghosts": NF,
+                   "grid": list(g.n), "ghosts": st.G, "faces_touching_ghosts": sets["faces"],
                    "launch_shapes": shapes},
         "roofline": {"bound": "hbm", "kernel": dominant, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
@@ -624,11 +654,11 @@ def main() -> int:
     out["geometry"] = geometry_benchmark(chib, torch, case, tabs, t_geom)
     if args.explicit_steps > 0:
         print("[bench] explicit scheme", file=sys.stderr, flush=True)
-        out["explicit"] = explicit_benchmark(chib, geo, case, args.explicit_steps, args.precision, NF,
+        out["explicit"] = explicit_benchmark(chib, geo, case, args.explicit_steps, args.precision, sets,
                                              out["ms_per_step"])
     if args.ns_steps > 0:
         print("[bench] Navier-Stokes coupling", file=sys.stderr, flush=True)
-        out["navier_stokes"] = ns_benchmark(chib, case, args.ns_steps, args.precision, out["ms_per_step"], NF,
+        out["navier_stokes"] = ns_benchmark(chib, case, args.ns_steps, args.precision, out["ms_per_step"], sets,
                                             st.shapes())
     if args.sweep_steps > 0:
         print("[bench] batched sweep (64 cases)", file=sys.stderr, flush=True)

@@ -202,10 +202,13 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 }
 
 // Whether the plane-marching stencil kernels deal their tiles that way too: while a field is small, so that a
-// run's halos are met again in its L2 or in the Infinity Cache (128^3 FP64 coupled: prediction 62 -> 58 us,
-// pressure rhs 31.5 -> 28; 256^3 FP32 explicit update, 64 MiB a field: 114 -> 110).  On larger fields tiles in
-// launch order win: the chip then works on few planes at a time (256^3 FP64: prediction 439 us, 450 in runs;
-// explicit update 203 and 208; correction 293 and 300).
+// run's halos are met again in its L2 or in the Infinity Cache.  On larger fields tiles in launch order win: the
+// chip then works on few planes at a time.  Prediction in us, in launch order and in runs, by the MiB a field
+// takes: FP64 16 (128^3) 61.0 and 57.1; 32 (256x128x128) 111.6 and 101.6; 64 (256x256x128) 217.9 and 209.1,
+// (128x256x256) 215.5 and 211.3; 128 (256^3) 435 and 448, (512x256x128) 430 and 432; 256 (512x256x256) 856 and 906;
+// FP32 32 (256x256x128) 126.7 and 104.5; 64 (256^3) 241 and 215; 128 (512x256x256) 438 and 450.  The correction
+// turns at the same sizes (FP64 64 MiB 135.3 and 134.4, 128 MiB 293 and 298); the pressure rhs already at 64 MiB
+// in FP64 (106 and 112 us), where a step in runs still gains 5 us in all.
 template <typename T>
 inline int tiles_in_runs(const Plan &p) {
   return p.N * (int64_t)sizeof(T) <= (int64_t(64) << 20);

@@ -3164,9 +3164,9 @@ hipError_t enqueue_step(const Plan &p, int cur, KernelTimer *tm, StepLink *link)
 // costs (barriers, twiddles) among more lines.  So every tile takes as many lines as leave that many
 // workgroups, within its 32 KB (2D grids: 2 lines or columns, a launch of a few microseconds is all
 // latency).  Measured per step against the former fixed shapes {8 lines, 16 columns, line-tiled rhs}:
-// 512x256 FP64 49 -> 28 us, 1024x512 FP32 85 -> 40 us.  Lines of 64 to 512 points take the width of their
-// fixed-size instance from 128 tiles on, which saves more than the emptier chip costs (64^3 38 -> 34 us with
-// 256 tiles instead of 1024, 64x64x32 33.9 -> 31.8 with 128).
+// 512x256 FP64 40.1 -> 25.5 us, 1024x512 FP32 55.2 -> 33.5 (dynamic angle 64.4 -> 42.8), 64^3 FP64 37.2 -> 32.0.
+// Lines of 64 to 512 points take the width of their fixed-size instance from 128 tiles on, which saves more than
+// the emptier chip costs (64^3 38 -> 34 us with 256 tiles instead of 1024, 64x64x32 33.9 -> 31.8 with 128).
 // rhs, 3D: the z-march reads C once instead of three times and wins from 2^23 cells (256x256x128 FP64 123 us
 // line-tiled, 88 marching; 256x128x128 45 and 51 and the march's dq list 5 more, FP32 31 and 37; 512x128x128
 // 137 and 105), with the longest march that leaves 512 workgroups (1024 in FP32, whose planes are half as long
@@ -3187,7 +3187,7 @@ void default_shapes(Plan &p) {
     const int wide = p.n[0] >= 1024 ? 2 : 1;
     const bool f64 = sizeof(T) == 8;
     // FP32 takes the line-tiled rhs: its requests are half as long and the rows come from L2, so the march gains
-    // nothing (1024x512 34.0 and 33.9 us a step, 512x256 26.4 and 26.6, batch of 32 cases 105 and 110)
+    // nothing (1024x512 33.5 and 33.8 us a step, 512x256 26.3 and 26.8, batch of 32 cases 105 and 110)
     p.shape[0] = {1, 8, ym_ok(p) && f64 ? 3 : 1};
     p.shape[1] = {4, 16, 1};
     p.shape[2] = {clamp_log(wide, max_log_cols(p, p.n[1], E)), f64 ? 8 : 16, 1};
@@ -3560,7 +3560,8 @@ hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer 
     mark("explicit_update");
     if (e == hipSuccess) {
       const int zc = explicit_zm_planes(p);
-      // (in runs up to half that size in FP64: 128^3 45.7 -> 42.5 us a step, 256x256x128 117.7 -> 118.9)
+      // (in runs up to half that size in FP64: in launch order and in runs 49.7 and 42.8 us at 32 MiB a field, 101.0
+      // and 105.0 at 64; FP32 67.1 and 51.8 at 32, 129.8 and 118.2 (256^3) or 113.6 and 121.0 (512x256x128) at 64)
       const unsigned nb = (unsigned)((p.n[0] / kXx) * (p.n[1] / kXy) * (p.n[2] / zc));
 #define CHIB_EXPLICIT_ZM(GH)                                                                                          \
   hipLaunchKernelGGL((k_explicit_zm<T, GH>), dim3(nb), dim3(kXThreads), 0, p.stream, Cn, (const T *)p.F[0],          \

@@ -16,8 +16,9 @@
 // is stored and kept at zero), the tangential velocity has the image -u across a wall, no
 // pressure gradient acts through a wall, and cell scalars are reflected.
 //
-// Every kernel takes one thread per cell and handles the d faces c + e_a/2 of that cell; the
-// face and cell neighbours come from global memory through the caches.
+// A thread handles the d faces c + e_a/2 of a cell.  On 3D grids of whole 64 x 8 tiles of columns the kernels
+// march in z, a plane's neighbours in LDS and the z neighbours in LDS or registers (k_ns_*_zm); on 2D grids and
+// the other 3D ones they take one cell per thread, its neighbours from global memory through the caches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

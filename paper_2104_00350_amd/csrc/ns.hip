@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kNsThreads) void k_ns_predict(FaceSet<T> U, const T
 // of an edge are symmetric in a and b; those of the z edges below come from the plane before.  Powers of
 // two and of 1/h are taken out of the sums; mu and rho are linear in C, so an edge viscosity or a face
 // density is one fused multiply-add on the sum of its cells' distances from the phase with the smaller
-// value (from the mean of the phases, FP32 lost 1.6e-5 of the lighter density at a ratio of 1000).  Same
+// value (from the mean of the phases, FP32 lost 1.7e-5 of the lighter density at a ratio of 1000).  Same
 // formulas and wall rules as ns_predict_cell: the planes beyond the box walls hold the images (-u_x, -u_y, u_z = 0, C reflected),
 // with which the wall edges take their values without a case of their own.
 constexpr int kEx = 64, kEy = 8, kEhx = kEx + 2, kEhy = kEy + 2;

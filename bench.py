@@ -88,7 +88,7 @@ def algorithmic_bytes(name: str, cells: int, d: int, es: int, sets: dict, dynami
         return cells * es * 2 + G * (4 + 2 * K * (4 + es) + 2 * K * es + es)
     if name == "explicit_update":                    # C, R, d faces in; C^(n+1), R out; from 2^20 cells phi is
         fused = d == 3 and cells >= 1 << 20          # formed on the way, below it is read
-        return cells * es * (4 + d) + (cells // 64 * 16 + G * es if fused else cells * es)
+        return cells * es * (4 + d) + (cells // 32 * 8 + G * es if fused else cells * es)
     if name == "ghost_fills":                        # static: both fills and the next step's phi~ points
         return (algorithmic_bytes("ghost_fill_C", cells, d, es, sets, dynamic)
                 + algorithmic_bytes("ghost_fill_u", cells, d, es, sets, dynamic) + points)

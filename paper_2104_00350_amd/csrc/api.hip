@@ -201,7 +201,7 @@ Offsets plan_layout(const ch_ib_geometry &g, int es, int64_t NF, const PatchList
   o.pt_cell = L.off(NU * 4);
   o.pt_idx = L.off((int64_t)pl.pt_idx.size() * 4);
   o.pt_phi = L.off(NU * es);
-  o.gwords = explicit_ab2 && G && chib::explicit_fused(d, g.n, N) ? L.off(N / 64 * sizeof(chib::GhostWord)) : 0;
+  o.gwords = explicit_ab2 && G && chib::explicit_fused(d, g.n, N) ? L.off(N / 32 * sizeof(chib::GhostWord)) : 0;
   o.f_cell = L.off(NF * 4);
   o.f_axis = L.off(NF * 4);
   o.f_gL = L.off(NF * 4);
@@ -522,10 +522,10 @@ extern "C" int ch_ib_state_create(const ch_ib_grid *grid, const ch_ib_geometry *
   }
   std::vector<chib::GhostWord> gwords;
   if (p.gwords && e == hipSuccess) {
-    gwords.assign((size_t)(p.N / 64), chib::GhostWord{0, 0, 0});
+    gwords.assign((size_t)(p.N / 32), chib::GhostWord{0, 0});
     for (int64_t i = G - 1; i >= 0; --i) {
-      chib::GhostWord &w = gwords[(size_t)(geom->gidx[i] >> 6)];
-      w.bits |= uint64_t(1) << (geom->gidx[i] & 63);
+      chib::GhostWord &w = gwords[(size_t)(geom->gidx[i] >> 5)];
+      w.bits |= uint32_t(1) << (geom->gidx[i] & 31);
       w.base = (int)i;
     }
     e = hipMemcpyAsync((void *)p.gwords, gwords.data(), gwords.size() * sizeof(chib::GhostWord),

@@ -9,14 +9,14 @@ namespace chib {
 
 constexpr int kGhostSlots = 16;   // lanes (and table slots) per ghost in the ghost kernels
 
-// The ghosts among 64 consecutive cells: one bit each, and the index of the first of them.
+// The ghosts among 32 consecutive cells: one bit each, and the index of the first of them.
 struct GhostWord {
-  uint64_t bits;
-  int base, pad;
+  uint32_t bits;
+  int base;
 };
 
 // Whether the explicit step forms phi on the way: 3D grids of whole 64 x 8 tiles, from a million cells on
-// (256^3 FP64 336 -> 252 us a step).  Below, phi's pass runs through the caches and forming it on the way gains
+// (256^3 FP64 340 -> 252 us a step of a 20-step pass).  Below, phi's pass runs through the caches and forming it on the way gains
 // less and less: 128x64x64 FP64 24.3 us a step with phi as a field and 20.2 without, 64^3 19.7 and 19.3,
 // 64x32x32 15.1 and 18.2.
 inline bool explicit_fused(int d, const int *n, int64_t cells) {
@@ -88,8 +88,8 @@ struct Plan {
   const int *pl_row = nullptr;     // [rows + 1]
   void *pl_dq = nullptr;           // [NP]
 
-  // explicit step that forms phi on the way: the ghosts of every 64 consecutive cells
-  const GhostWord *gwords = nullptr;   // [N / 64], or nullptr
+  // explicit step that forms phi on the way: the ghosts of every 32 consecutive cells
+  const GhostWord *gwords = nullptr;   // [N / 32], or nullptr
 
   // faces touching ghosts (velocity fill)
   int64_t NF = 0;

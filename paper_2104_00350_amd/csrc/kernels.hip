@@ -2177,10 +2177,10 @@ __global__ __launch_bounds__(kThreads) void k_phi_zm(const T *__restrict__ C, T 
 // ring (the threads that bring a ring cell keep that column too) and goes to LDS in turn; plane z is
 // advanced from phi and C in LDS and the z neighbours in registers.  Four slots of C and three of phi
 // leave one barrier per plane: a slot is rewritten two barriers after its last read.  At the ghosts the
-// mirror value takes phi's place (one word of 64 cells' bits per row and plane says where, and which ghost the
-// first of them is), so that C inside the solid, which phi at a ghost would read, reaches no fluid cell and
+// mirror value takes phi's place (a word per 32 cells, a bit each and the index of the first ghost, says
+// where), so that C inside the solid, which phi at a ghost would read, reaches no fluid cell and
 // the rate is rounded once, as with phi as a field.  256^3 FP64: phi 62, its ghosts 7 and update 217 us before,
-// 203 us here (moving 1.34 times its bytes).
+// 201 us here (moving 1.34 times its bytes); a step at 256^3 FP32 136.5 us.
 constexpr int kXx = 64, kXy = 8, kXThreads = kXx * kXy;        // (explicit_fused asks for whole tiles)
 constexpr int kXcp = kXx + 4, kXpp = kXx + 2;                  // row pitch of C and of phi
 constexpr int kXcPlane = kXcp * (kXy + 4), kXpPlane = kXpp * (kXy + 2);
@@ -2188,8 +2188,20 @@ constexpr int kXRing1 = kXpPlane - kXThreads;                  // cells around t
 constexpr int kXHalo = kXcPlane - kXThreads;                   // cells around the tile whose C is held
 static_assert(kXHalo <= kXThreads, "one halo cell per thread");
 
+// A uniform address that stays in scalar registers until a lane's 32-bit offset joins it.  (Left to the compiler,
+// base + offset of every field is hoisted out of the plane loop, two vector registers each: the FP32 update then
+// holds 68 instead of 56 and loses a workgroup per CU.)
+template <typename U>
+using global_t = __attribute__((address_space(1))) U;
+template <typename U>
+__device__ __forceinline__ global_t<U> *scalar_base(U *p) {
+  global_t<U> *g = (global_t<U> *)p;
+  asm("" : "+s"(g));
+  return g;
+}
+
 template <typename T, bool GHOSTS>
-__global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__ C, const T *__restrict__ F0,
+__global__ __launch_bounds__(kXThreads, sizeof(T) == 4 ? 8 : 4) void k_explicit_zm(const T *__restrict__ C, const T *__restrict__ F0,
                                                            const T *__restrict__ F1, const T *__restrict__ F2,
                                                            T *__restrict__ R, T *__restrict__ Cnext, Dims dm, T cn2,
                                                            T half_inv_h, T inv_h2, T inv_pe, T dt, int first, int zc,
@@ -2222,33 +2234,42 @@ __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__
   const int colxm = ((x0 - 1) & (nx - 1)) + ((y0 + ty) << dm.lnx);   // (the first lane of each row asks for it)
   // planes beyond the walls reflect onto the boundary plane
   auto zb = [&](int z) { return (int64_t)(z < 0 ? 0 : (z >= nz ? nz - 1 : z)) * dm.plane; };
+  // a plane's value at a byte offset within it, which all fields share
+  const unsigned ob = (unsigned)col * (unsigned)sizeof(T), hb = (unsigned)hcol * (unsigned)sizeof(T);
+  const unsigned obx = (unsigned)colxm * (unsigned)sizeof(T), oby = (unsigned)colym * (unsigned)sizeof(T);
+  auto in = [](const global_t<T> *p, unsigned off) {
+    return *reinterpret_cast<const global_t<T> *>(reinterpret_cast<const global_t<char> *>(p) + off);
+  };
   T cn, hn = T(0);                                             // the plane of C in flight, with its ghosts
   GhostWord gw{}, hw{};
+  auto word = [](const global_t<GhostWord> *w, unsigned i) { return GhostWord{w[i].bits, w[i].base}; };
   auto request_c = [&](int z) {
-    const int64_t b = zb(z);
-    if constexpr (GHOSTS) gw = g_word[(b + col) >> 6];
-    cn = C[b + col];
+    const global_t<T> *p = scalar_base(C + zb(z));
+    const global_t<GhostWord> *w = scalar_base(g_word + (zb(z) >> 5));
+    if constexpr (GHOSTS) gw = word(w, (unsigned)col >> 5);
+    cn = in(p, ob);
     if (halo) {
-      if constexpr (GHOSTS) hw = g_word[(b + hcol) >> 6];
-      hn = C[b + hcol];
+      if constexpr (GHOSTS) hw = word(w, (unsigned)hcol >> 5);
+      hn = in(p, hb);
     }
   };
   // phi's mirror value where the cell at column c is a ghost
   auto mirror = [&](const GhostWord &w, int c, T &v) {
-    const uint64_t bit = uint64_t(1) << (c & 63);
+    const uint32_t bit = uint32_t(1) << (c & 31);
     const bool is = w.bits & bit;
-    if (is) v = g_phi[w.base + __popcll(w.bits & (bit - 1))];
+    if (is) v = g_phi[w.base + __popc(w.bits & (bit - 1))];
     return is;
   };
   T f0, f0l, f1, f1m, f2, rz;                                  // faces and rate of the plane to advance
   auto request_f = [&](int z) {
     const int64_t c = zb(z);
-    f0 = F0[c + col];
-    if (tx == 0) f0l = F0[c + colxm];
-    f1 = F1[c + col];
-    f1m = F1[c + colym];
-    f2 = F2[c + col];
-    rz = R[c + col];
+    const global_t<T> *p0 = scalar_base(F0 + c), *p1 = scalar_base(F1 + c);
+    f0 = in(p0, ob);
+    if (tx == 0) f0l = in(p0, obx);
+    f1 = in(p1, ob);
+    f1m = in(p1, oby);
+    f2 = in(scalar_base(F2 + c), ob);
+    rz = in(scalar_base((const T *)R + c), ob);
   };
   auto phi_of = [&](const T *p, int i, T cm, T c0, T cp) {
     const T sum = ((p[i + 1] + p[i - 1]) + (p[i + kXcp] + p[i - kXcp])) + (cp + cm);
@@ -2272,7 +2293,7 @@ __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__
   if (halo) sc[(z0 + 3) & 3][hic] = h1;
   request_c(z0);
   T pm = T(0), p0 = T(0);
-  T f2m = z0 > 0 ? F2[zb(z0 - 1) + col] : T(0);
+  T f2m = z0 > 0 ? in(scalar_base(F2 + zb(z0 - 1)), ob) : T(0);
   int s1 = 2;                                                  // slot of phi plane z+1
   __syncthreads();
   for (int z = z0 - 2; z < z0 + zc; ++z) {
@@ -2312,9 +2333,11 @@ __global__ __launch_bounds__(kXThreads) void k_explicit_zm(const T *__restrict__
       flux += fz - f2m;
       const T r = -flux * half_inv_h + inv_pe * (lsum - T(6) * p0) * inv_h2;
       const T rp = first ? r : rz;
-      const int64_t c = zb(z) + col;
-      __builtin_nontemporal_store(r, R + c);
-      Cnext[c] = c0 + dt * (T(1.5) * r - T(0.5) * rp);
+      auto to = [&](T *field) {
+        return reinterpret_cast<global_t<T> *>(reinterpret_cast<global_t<char> *>(scalar_base(field + zb(z))) + ob);
+      };
+      __builtin_nontemporal_store(r, to(R));
+      *to(Cnext) = c0 + dt * (T(1.5) * r - T(0.5) * rp);
       f2m = fz;
       if (z + 1 < z0 + zc) request_f(z + 1);
     } else if (z == z0 - 1) {

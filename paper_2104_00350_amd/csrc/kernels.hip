@@ -3583,8 +3583,9 @@ hipError_t enqueue_explicit_step(const Plan &p, int cur, int first, KernelTimer 
     mark("explicit_update");
     if (e == hipSuccess) {
       const int zc = explicit_zm_planes(p);
-      // (in runs up to half that size in FP64: in launch order and in runs 49.7 and 42.8 us at 32 MiB a field, 101.0
-      // and 105.0 at 64; FP32 67.1 and 51.8 at 32, 129.8 and 118.2 (256^3) or 113.6 and 121.0 (512x256x128) at 64)
+      // (in runs up to half that size in FP64: in launch order and in runs 50.1 and 42.2 us at 32 MiB a field, 99.5 and
+      // 104.9 (256x256x128) or 107.5 and 103.1 (128x256x256) at 64, 200 and 208 at 128; FP32 64.1 and 44.2 at 32, 111.2
+      // and 108.7 (256^3) or 108.1 and 112.2 (512x256x128) at 64, 212 and 219 at 128)
       const unsigned nb = (unsigned)((p.n[0] / kXx) * (p.n[1] / kXy) * (p.n[2] / zc));
 #define CHIB_EXPLICIT_ZM(GH)                                                                                          \
   hipLaunchKernelGGL((k_explicit_zm<T, GH>), dim3(nb), dim3(kXThreads), 0, p.stream, Cn, (const T *)p.F[0],          \
